@@ -925,19 +925,30 @@ struct F_k_gauss_jordan_lds {
 };
 
 // The inverse (right half of the reduced augmented matrix) in compact n x n
-// form, in FP64 and FP32.
+// form, in FP64 and FP32: row-major, and transposed with rows of zeros up to
+// a multiple of kCoarsePad.
 __device__ __forceinline__ void k_compact_inv_d(const Blk& wg, int n, const double* __restrict__ M,
-                                                double* __restrict__ inv, float* __restrict__ inv32) {
+                                                double* __restrict__ inv, double* __restrict__ invt,
+                                                float* __restrict__ inv32, float* __restrict__ invt32) {
     const int64_t idx = (int64_t)wg.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)n * n) return;
-    const int64_t r = idx / n, c = idx - r * n;
+    if (idx >= (int64_t)n * ((n + kCoarsePad - 1) / kCoarsePad * kCoarsePad)) return;
+    const int64_t c = idx / n, r = idx - c * n;
+    if (c >= n) {
+        invt[idx] = 0.0;
+        if (inv32) invt32[idx] = 0.0f;
+        return;
+    }
     const double v = M[r * 2 * n + n + c];
-    inv[idx] = v;
-    if (inv32) inv32[idx] = (float)v;
+    inv[r * n + c] = v;
+    invt[c * n + r] = v;
+    if (inv32) {
+        inv32[r * n + c] = (float)v;
+        invt32[c * n + r] = (float)v;
+    }
 }
 __global__ void k_compact_inv(int n, const double* __restrict__ M, double* __restrict__ inv,
-                              float* __restrict__ inv32) {
-    k_compact_inv_d(PF_BLK, n, M, inv, inv32);
+                              double* __restrict__ invt, float* __restrict__ inv32, float* __restrict__ invt32) {
+    k_compact_inv_d(PF_BLK, n, M, inv, invt, inv32, invt32);
 }
 struct F_k_compact_inv {
     static constexpr int kLB = 1024;
@@ -2313,6 +2324,7 @@ void cpr_plan(Sim& s, Bump& b) {
     const int64_t nc = s.mg.back().n;
     s.coarse_aug = b.take<double>((size_t)nc * 2 * nc);
     s.coarse_inv = b.take<double>((size_t)nc * nc);
+    s.coarse_inv_t = b.take<double>((size_t)nc * (nc + kCoarsePad));
     s.pb = b.take<double>(std::max(s.m.nw, 1));
     const bool ilu = s.opts.smoother == PF_SMOOTH_RBILU0;
     const int64_t ns = ilu_slot_count(s.m);
@@ -2322,6 +2334,7 @@ void cpr_plan(Sim& s, Bump& b) {
     s.Jdc = (ilu && !mixed) ? b.take<double>(18 * ns) : nullptr;
     if (mixed) {
         s.coarse_inv32 = b.take<float>((size_t)nc * nc);
+        s.coarse_inv_t32 = b.take<float>((size_t)nc * (nc + kCoarsePad));
         s.Jp32 = b.take<float>(21 * s.m.n);
         s.Joff16 = ilu ? b.take<uint16_t>(108 * ns) : nullptr;
         s.Dinv32 = b.take<float>(ilu ? 18 * ns : 9 * s.m.n);
@@ -2376,8 +2389,9 @@ void cpr_setup(Sim& s) {
         launch<F_k_gauss_jordan>(s, cs, k_gauss_jordan, dim3(1), dim3(1024), 0, (int)Cn.n, s.coarse_aug);
     }
     PF_LAUNCH_CHECK();
-    launch<F_k_compact_inv>(s, cs, k_compact_inv, dim3(grid_for(Cn.n * Cn.n)), dim3(kBlock), 0, (int)Cn.n,
-                            s.coarse_aug, s.coarse_inv, mixed ? s.coarse_inv32 : (float*)nullptr);
+    launch<F_k_compact_inv>(s, cs, k_compact_inv, dim3(grid_for(Cn.n * (Cn.n + kCoarsePad))), dim3(kBlock), 0, (int)Cn.n,
+                            s.coarse_aug, s.coarse_inv, s.coarse_inv_t, mixed ? s.coarse_inv32 : (float*)nullptr,
+                            mixed ? s.coarse_inv_t32 : (float*)nullptr);
     PF_LAUNCH_CHECK();
     if (side) PF_HIP(hipEventRecord(s.ev_join, s.aux));
     for (int l = 0; l + 1 < nl; ++l) {
@@ -2449,6 +2463,13 @@ int pre_sweeps(const Sim& s, const MGLevel& L) {
     return std::max(1, p);
 }
 
+// the coarsest inverse from the side stream, before its first use
+void join_coarse(Sim& s) {
+    if (!s.coarse_pending) return;
+    PF_HIP(hipStreamWaitEvent(s.stream, s.ev_join, 0));
+    s.coarse_pending = false;
+}
+
 // One V-cycle from level l.  At level 0 of the last cycle, pout receives the
 // level-0 correction in natural cell order.  first_done: the first colour-0
 // half-sweep of level l (from x = 0) was done with the restriction onto it.
@@ -2457,11 +2478,13 @@ void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_don
     const int nl = (int)s.mg.size();
     MGLevel& L = s.mg[l];
     const Dims g = dims_of(L);
-    if (l == nl - 1) {
-        if (s.coarse_pending) {
-            PF_HIP(hipStreamWaitEvent(s.stream, s.ev_join, 0));     // the inverse from the side stream
-            s.coarse_pending = false;
-        }
+    // levels [0, nt) have launches of their own, the rest is one launch
+    const int nt = nl <= kMaxChain ? mg_tail_first(s) : nl;
+    if (l == nt && nt < nl) {
+        join_coarse(s);
+        launch_mg_tail(s, l, 1, nullptr, 0, (T*)nullptr);
+    } else if (l == nl - 1) {
+        join_coarse(s);
         launch<F_k_coarse_apply<T>>(s, s.stream, k_coarse_apply<T>, dim3((unsigned)((L.n + 3) / 4)), dim3(256), 0,
                                     (int)L.n, Lv<T>::inv(s), Lv<T>::b(L), Lv<T>::x(L));
         PF_LAUNCH_CHECK();
@@ -2500,8 +2523,8 @@ void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_don
             // no post-smoothing: the whole upward pass is prolongation, done once from level 0
             if (l == 0) {
                 ProlongChain pc{};
-                pc.nl = nl;
-                for (int q = 1; q < nl; ++q) {
+                pc.nl = std::min(nl, nt + 1);       // level nt's correction holds the coarser ones
+                for (int q = 1; q < pc.nl; ++q) {
                     const MGLevel& F = s.mg[q - 1];
                     pc.sx[q] = pc.sx[q - 1] + (F.cx == 2);
                     pc.sy[q] = pc.sy[q - 1] + (F.cy == 2);
@@ -2531,6 +2554,8 @@ void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_don
 
 }  // namespace
 
+int mg_pre_sweeps(const Sim& s, int level) { return pre_sweeps(s, s.mg[level]); }
+
 void mg_smooth_once(Sim& s, int level, int colour, int zero_init) {
     zline_sweep<double>(s, s.mg[level], colour, zero_init);
 }
@@ -2543,6 +2568,11 @@ template <class T>
 T* pressure_cycles(Sim& s, const double* v, int cs = 0) {
     const DevModel& m = s.m;
     T* p = Lv<T>::pnat(s);
+    if (mg_tail_first(s) == 0) {
+        join_coarse(s);
+        launch_mg_tail(s, 0, std::max(1, s.opts.mg_cycles), v, cs, p);
+        return p;
+    }
     const bool fused = restrict_p_zline<T>(s, v, cs);
     if (!fused) {
         launch<F_k_restrict_p<T>>(s, s.stream, k_restrict_p<T>, dim3(grid_for(m.n)), dim3(kBlock), 0,

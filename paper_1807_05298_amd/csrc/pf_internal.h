@@ -26,6 +26,7 @@ constexpr int kBlock = 256;          // threads per block for cell sweeps
 constexpr int kMaxRestart = 64;
 constexpr int kRedBlocks = 1024;     // fixed partial-sum grid of the reductions
 constexpr int kDotChunk = 16;        // dot products per multi-dot launch
+constexpr int kCoarsePad = 16;       // rows of the transposed coarsest inverse: padded with zeros to a multiple
 constexpr int kPartSlots = kMaxRestart + 2;   // partial-sum slots: restart + 2 dot products
 
 // Everything a kernel needs to evaluate cell properties; passed by value.
@@ -229,6 +230,8 @@ struct Sim {
     double *coarse_aug;              // coarsest-level [A | I] -> [I | A^-1]
     double *coarse_inv;              // compact coarsest inverse (n x n)
     float *coarse_inv32;
+    double *coarse_inv_t;            // ... and transposed
+    float *coarse_inv_t32;
     float *Jp32;                     // mixed: FP32 P-columns of J (21 planes)
     double *Lc;                      // FP64 ILU: colour-split off-diagonal blocks (2 x 54 planes)
     double *Jdc;                     // FP64 ILU: colour-split diagonal blocks of J (2 x 9 planes)
@@ -349,8 +352,18 @@ void cpr_apply_spmv(Sim& s, const double* v, double* z, double* w);   // z = M^{
 bool cpr_colour_split(const Sim& s);  // cpr_apply_spmv takes and gives the colour-split layout
 void mg_smooth_once(Sim& s, int level, int colour, int zero_init);   // test hook
 int64_t mg_slot(const MGLevel& L, int ix, int iy, int iz);             // cell -> slot of a level
+int mg_pre_sweeps(const Sim& s, int level);                            // pre-smoothing sweeps of a level
 void mg_cycles_once(Sim& s, const double* v);   // test hook: s.pnat(32) = V-cycles(Pi_r v)
 void smoother_once(Sim& s, const double* f);    // test hook: s.t1 (FP64) / s.Z32 (mixed) = S f
+
+// ---- the bottom of the V-cycle in one workgroup (k_mg_tail.hip) ------------
+// First level that its launch takes (the number of levels: none)
+int mg_tail_first(const Sim& s);
+// cycles V-cycles from that level l0 down; l0 > 0: from the level's right-hand
+// side to its correction with the coarser ones added; l0 == 0: from v (natural
+// layout, or colour-split with cs) to p in natural cell order
+void launch_mg_tail(Sim& s, int l0, int cycles, const double* v, int cs, double* p);
+void launch_mg_tail(Sim& s, int l0, int cycles, const double* v, int cs, float* p);
 
 // ---- errors -----------------------------------------------------------------
 void set_error(const std::string& msg);
