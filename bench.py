@@ -36,16 +36,15 @@ KERNEL_BYTES = {
     "spmv": ("PF_K_SPMV", 2, 496),                # J 448 + x 24 in; y 24 out (x FP32 in mixed: 484)
     "zline": ("PF_K_ZLINE", 3, None),             # level-0 half-sweep, per active column set (below)
     "ilu": ("PF_K_ILU", 6, None),
-    # last ILU phase with the red rows of w = J z (which equal v there): Lc 384 + inverse diagonal 72 + z 24
-    # + p 8 + black z 24 + v 24 in, z 24 + w 24 out, per red cell (half the cells)
-    "red_spmv": ("PF_K_RED_SPMV", 8, (384 + 72 + 24 + 8 + 24 + 24 + 24 + 24) // 2),
-    # black rows of w = J z: Lc 384 + J diagonal 64 + z 24 + p 8 + red z 24 in, z (P plane) 8 + w 24 out,
-    # per black cell
-    "black_spmv": ("PF_K_BLACK_SPMV", 9, (384 + 64 + 24 + 8 + 24 + 8 + 24) // 2),
-    # FP64 stage residual of the red rows with the first ILU phase, from the colour-split copies of J:
-    # J_rr P-column 24 + off-diagonal P-columns 144 + v 24 + p 8 + border map 4 + D_r^{-1} 72 in, z 24 out,
-    # per red cell (the black rows' residual is formed in the forward black phase)
-    "stage_resid": ("PF_K_STAGE_RESID", 7, (24 + 144 + 24 + 8 + 4 + 72 + 24) // 2),
+    # last ILU phase (after which the red rows of w = J z are those of v): Lc 384 + inverse diagonal 72
+    # + black z 24 + v 24 + border map 4 in, z 24 out, per red cell (half the cells)
+    "red_spmv": ("PF_K_RED_SPMV", 8, (384 + 72 + 24 + 24 + 4 + 24) // 2),
+    # black rows of w = J z: Lc 384 + J diagonal 64 + z 24 + red z 24 + border map 4 in, w 24 out, per black cell
+    "black_spmv": ("PF_K_BLACK_SPMV", 9, (384 + 64 + 24 + 24 + 4 + 24) // 2),
+    # FP64 first ILU phase on the pressure stage's residual, from the colour-split copies of J: off-diagonal
+    # P-columns 144 + v 24 + black p 8 + border map 4 + D_r^{-1} 72 in, z 24 out, per red cell (the black rows'
+    # residual is formed in the forward black phase)
+    "stage_resid": ("PF_K_STAGE_RESID", 7, (144 + 24 + 8 + 4 + 72 + 24) // 2),
 }
 
 
@@ -357,7 +356,7 @@ def main():
     ap.add_argument("--smoother", default="rbilu0", choices=["bjac", "rbilu0"])
     ap.add_argument("--order", default="pf", choices=["pf", "fp"])
     ap.add_argument("--profile-kernel", default=None, choices=sorted(KERNEL_BYTES),
-                    help="kernel timed for the roofline (default: red_spmv, the last ILU phase with the red rows of w = J z, in FP64 with the ILU(0) smoother in PF order; spmv otherwise)")
+                    help="kernel timed for the roofline (default: red_spmv, the last ILU phase, in FP64 with the ILU(0) smoother in PF order; spmv otherwise)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-mixed", action="store_true",
                     help="skip the mixed-precision run of the same schedule (300^3 workload)")

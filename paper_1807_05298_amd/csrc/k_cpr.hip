@@ -690,9 +690,7 @@ struct F_k_gather_p {
 // post-smoothing: x_0 += P_0 (x_1 + P_1 (x_2 + ...)).  Box aggregation with
 // factors 1 or 2 per direction composes to shifts (floor(floor(i/2)/2) =
 // i >> 2), so a level-0 cell reads its aggregate on every coarser level.
-// Summed from the coarsest level down, as the nested form associates.  With
-// p given, the sum goes to p in natural cell order instead of back into x_0
-// (the last cycle).
+// Summed from the coarsest level down, as the nested form associates.
 constexpr int kMaxChain = 32;
 struct ProlongChain {
     int nl;
@@ -701,16 +699,11 @@ struct ProlongChain {
     const void* x[kMaxChain];
 };
 
-// NL > 0: exactly NL levels, the level loop unrolled so that every level's
-// load issues at once; NL == 0: pc.nl levels.
+// The levels' values at a cell, summed.  NL > 0: exactly NL levels, the level
+// loop unrolled so that every level's load issues at once; NL == 0: pc.nl
+// levels.
 template <class T, int NL>
-__device__ __forceinline__ void k_prolong_chain_d(const Blk& wg, Dims f, ProlongChain pc, T* __restrict__ x,
-                                                  T* __restrict__ p) {
-    const int64_t nf = (int64_t)f.nx * f.ny * f.nz;
-    const int64_t i = xcd_block(wg) * blockDim.x + threadIdx.x;
-    if (i >= nf) return;
-    int ix, iy, iz;
-    cell_coords(f, i, ix, iy, iz);
+__device__ __forceinline__ T chain_sum(const ProlongChain& pc, int ix, int iy, int iz) {
     T sum = 0;
     if constexpr (NL > 0) {
         T v[NL > 0 ? NL : 1];
@@ -725,12 +718,22 @@ __device__ __forceinline__ void k_prolong_chain_d(const Blk& wg, Dims f, Prolong
             sum = static_cast<const T*>(pc.x[l])[I] + sum;
         }
     }
-    const int64_t j = lv_index(f, ix, iy, iz);
-    if (p) p[i] = x[j] + sum;
-    else x[j] += sum;
+    return sum;
+}
+
+// The last cycle: x_0 plus the sum to p in natural cell order.
+template <class T, int NL>
+__device__ __forceinline__ void k_prolong_chain_d(const Blk& wg, Dims f, ProlongChain pc, const T* __restrict__ x,
+                                                  T* __restrict__ p) {
+    const int64_t nf = (int64_t)f.nx * f.ny * f.nz;
+    const int64_t i = xcd_block(wg) * blockDim.x + threadIdx.x;
+    if (i >= nf) return;
+    int ix, iy, iz;
+    cell_coords(f, i, ix, iy, iz);
+    p[i] = x[lv_index(f, ix, iy, iz)] + chain_sum<T, NL>(pc, ix, iy, iz);
 }
 template <class T, int NL>
-__global__ void k_prolong_chain(Dims f, ProlongChain pc, T* __restrict__ x, T* __restrict__ p) {
+__global__ void k_prolong_chain(Dims f, ProlongChain pc, const T* __restrict__ x, T* __restrict__ p) {
     k_prolong_chain_d<T, NL>(PF_BLK, f, pc, x, p);
 }
 template <class T, int NL>
@@ -739,6 +742,89 @@ struct F_k_prolong_chain {
     template <class... A>
     __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
         k_prolong_chain_d<T, NL>(wg, a...);
+    }
+};
+
+// Between cycles (80 us on 300^3 for 190 with both colours):
+// x_0 += the sum on the colour-1 columns alone.  The next
+// cycle opens with a colour-0 half-sweep, which reads its own columns'
+// right-hand sides and the colour-1 values and overwrites the colour-0 ones.
+template <class T, int NL>
+__device__ __forceinline__ void k_prolong_half_d(const Blk& wg, Dims f, ProlongChain pc, T* __restrict__ x) {
+    const int hx = (f.nx + 1) >> 1;
+    const int64_t half = lv_half(f);
+    const int64_t sl = xcd_block(wg) * blockDim.x + threadIdx.x;
+    if (sl >= half) return;
+    const int64_t line = sl / hx;
+    const int iz = (int)(line / f.ny), iy = (int)(line - (int64_t)iz * f.ny);
+    const int ix = 2 * (int)(sl - line * hx) + ((iy + 1) & 1);
+    if (ix < f.nx) x[half + sl] += chain_sum<T, NL>(pc, ix, iy, iz);
+}
+template <class T, int NL>
+__global__ __launch_bounds__(256) void k_prolong_half(Dims f, ProlongChain pc, T* __restrict__ x) {
+    k_prolong_half_d<T, NL>(PF_BLK, f, pc, x);
+}
+template <class T, int NL>
+struct F_k_prolong_half {
+    static constexpr int kLB = 256;
+    template <class... A>
+    __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
+        k_prolong_half_d<T, NL>(wg, a...);
+    }
+};
+
+// The last cycle of a colour-split solve (97 us on 300^3 for 190 with the red
+// cells and the wells in another launch): x_0 plus the sum on the black cells
+// alone (in their slot order: the later stages need no red pressure), and in
+// the nw blocks after those the wells' bottom-hole pressures from their rows,
+// pb_w = (v_w - sum_perf dW/dP * p_cell) / D_w, one wavefront per well.
+template <int NL>
+__device__ __forceinline__ void k_prolong_black_d(const Blk& wg, Dims f, ProlongChain pc,
+                                                  const double* __restrict__ x, double* __restrict__ p, int ncb,
+                                                  const int32_t* __restrict__ wp_first,
+                                                  const int32_t* __restrict__ wp_idx,
+                                                  const int32_t* __restrict__ perf_cell,
+                                                  const double* __restrict__ Cw, const double* __restrict__ Dw,
+                                                  const double* __restrict__ vw, double* __restrict__ pb) {
+    if ((int)wg.x >= ncb) {
+        const int w = (int)wg.x - ncb;
+        if (threadIdx.x >= 64) return;
+        double s = 0.0;
+        for (int k = wp_first[w] + (int)threadIdx.x; k < wp_first[w + 1]; k += 64) {
+            const int q = wp_idx[k];
+            int ix, iy, iz;
+            cell_coords(f, perf_cell[q], ix, iy, iz);
+            s += Cw[3 * q] * (x[lv_index(f, ix, iy, iz)] + chain_sum<double, NL>(pc, ix, iy, iz));
+        }
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+        if (threadIdx.x == 0) pb[w] = (vw[w] - s) / Dw[w];
+        return;
+    }
+    const int hx = (f.nx + 1) >> 1;
+    const int64_t ns = (int64_t)hx * f.ny * f.nz;
+    const int64_t sl = xcd_block(Blk{wg.x, (uint32_t)ncb}) * blockDim.x + threadIdx.x;
+    if (sl >= ns) return;
+    const int64_t line = sl / hx;
+    const int iz = (int)(line / f.ny), iy = (int)(line - (int64_t)iz * f.ny);
+    const int ix = 2 * (int)(sl - line * hx) + ((1 + iy + iz) & 1);
+    if (ix < f.nx) p[sl] = x[lv_index(f, ix, iy, iz)] + chain_sum<double, NL>(pc, ix, iy, iz);
+}
+template <int NL>
+__global__ __launch_bounds__(256) void k_prolong_black(Dims f, ProlongChain pc, const double* __restrict__ x,
+                                                       double* __restrict__ p, int ncb,
+                                                       const int32_t* __restrict__ wp_first,
+                                                       const int32_t* __restrict__ wp_idx,
+                                                       const int32_t* __restrict__ perf_cell,
+                                                       const double* __restrict__ Cw, const double* __restrict__ Dw,
+                                                       const double* __restrict__ vw, double* __restrict__ pb) {
+    k_prolong_black_d<NL>(PF_BLK, f, pc, x, p, ncb, wp_first, wp_idx, perf_cell, Cw, Dw, vw, pb);
+}
+template <int NL>
+struct F_k_prolong_black {
+    static constexpr int kLB = 256;
+    template <class... A>
+    __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
+        k_prolong_black_d<NL>(wg, a...);
     }
 };
 
@@ -988,28 +1074,28 @@ struct F_k_coarse_apply {
 
 // Pressure restriction: water + oil residual of each cell, into the slots
 // of level 0.
-// The colour-split vector layout (pf_internal.h) on the finest grid's Dims:
-// slots per colour and the plane offset of a cell.
-__device__ __forceinline__ int64_t cs_half(const Dims& g) { return (int64_t)((g.nx + 1) >> 1) * g.ny * g.nz; }
-__device__ __forceinline__ int64_t cs_offset(const Dims& g, int ix, int iy, int iz) {
-    return ((ix + iy + iz) & 1) * cs_half(g) + ((int64_t)iy + (int64_t)g.ny * iz) * ((g.nx + 1) >> 1) + (ix >> 1);
+// v in natural order, or (cv.b set) in the colour-split layout (pf_internal.h):
+// a red cell's rows are alpha times u's.
+__device__ __forceinline__ double restrict_cs(const CsVec& cv, double alpha, int64_t ns, int64_t sl, int colour) {
+    return colour ? cv.b[sl] + cv.b[ns + sl] : alpha * (cv.u[sl] + cv.u[ns + sl]);
 }
 
 template <class T>
-__device__ __forceinline__ void k_restrict_p_d(const Blk& wg, Dims g, const double* __restrict__ v, T* __restrict__ b,
-                                               int cs) {
+__device__ __forceinline__ void k_restrict_p_d(const Blk& wg, Dims g, const double* __restrict__ v, CsVec cv,
+                                               T* __restrict__ b) {
     const int64_t n = (int64_t)g.nx * g.ny * g.nz;
     const int64_t i = xcd_block(wg) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     int ix, iy, iz;
     cell_coords(g, i, ix, iy, iz);
-    const int64_t vi = cs ? cs_offset(g, ix, iy, iz) : i;
-    const int64_t pl = cs ? 2 * cs_half(g) : n;
-    b[lv_index(g, ix, iy, iz)] = (T)(v[vi] + v[pl + vi]);
+    const int64_t ns = (int64_t)((g.nx + 1) >> 1) * g.ny * g.nz;
+    const int64_t sl = ((int64_t)iy + (int64_t)g.ny * iz) * ((g.nx + 1) >> 1) + (ix >> 1);
+    b[lv_index(g, ix, iy, iz)] =
+        cv.b ? (T)restrict_cs(cv, *cv.alpha, ns, sl, (ix + iy + iz) & 1) : (T)(v[i] + v[n + i]);
 }
 template <class T>
-__global__ void k_restrict_p(Dims g, const double* __restrict__ v, T* __restrict__ b, int cs) {
-    k_restrict_p_d<T>(PF_BLK, g, v, b, cs);
+__global__ void k_restrict_p(Dims g, const double* __restrict__ v, CsVec cv, T* __restrict__ b) {
+    k_restrict_p_d<T>(PF_BLK, g, v, cv, b);
 }
 template <class T>
 struct F_k_restrict_p {
@@ -1027,10 +1113,9 @@ struct F_k_restrict_p {
 // its slot (one of each colour, so every cell is visited once), stores both
 // and sweeps its colour-0 column from the values in its registers.
 template <int LMAX, class T>
-__device__ __forceinline__ void k_restrict_p_zline_d(const Blk& wg, Dims g, const double* __restrict__ v,
+__device__ __forceinline__ void k_restrict_p_zline_d(const Blk& wg, Dims g, const double* __restrict__ v, CsVec cv,
                                                      const T* __restrict__ A, const T* __restrict__ aux,
-                                                     T* __restrict__ b, T* __restrict__ x, int L, int nseg, int cpb,
-                                                     int cs) {
+                                                     T* __restrict__ b, T* __restrict__ x, int L, int nseg, int cpb) {
     __shared__ T sA[1024];
     __shared__ T sB[1024];
     const int t = threadIdx.x;
@@ -1046,8 +1131,10 @@ __device__ __forceinline__ void k_restrict_p_zline_d(const Blk& wg, Dims g, cons
         const int iy = tc / hx;
         const int ixh = tc - iy * hx;
         const int64_t half = lv_half(g), lstr = (int64_t)hx * g.ny;
-        const int64_t n = cs ? 2 * cs_half(g) : (int64_t)g.nx * g.ny * g.nz;
+        const int64_t n = (int64_t)g.nx * g.ny * g.nz;
         const int k0 = seg * L;
+        // the colour-split slot of a cell is that of its column's layer here
+        const double alpha = cv.b ? *cv.alpha : 0.0;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int ix = 2 * ixh + ((iy + q) & 1);
@@ -1056,9 +1143,15 @@ __device__ __forceinline__ void k_restrict_p_zline_d(const Blk& wg, Dims g, cons
             for (int j = 0; j < LMAX; ++j) {
                 const int iz = k0 + j;
                 if (j < L && iz < g.nz) {
-                    const int64_t i = cs ? cs_offset(g, ix, iy, iz) : ix + (int64_t)g.nx * (iy + (int64_t)g.ny * iz);
-                    const T r = (T)(v[i] + v[n + i]);
-                    b[q * half + tcol + (int64_t)iz * lstr] = r;
+                    const int64_t sl = tcol + (int64_t)iz * lstr;
+                    T r;
+                    if (cv.b) {
+                        r = (T)restrict_cs(cv, alpha, half, sl, (q + iz) & 1);
+                    } else {
+                        const int64_t i = ix + (int64_t)g.nx * (iy + (int64_t)g.ny * iz);
+                        r = (T)(v[i] + v[n + i]);
+                    }
+                    b[q * half + sl] = r;
                     if (q == 0) bin[j] = r;
                 }
             }
@@ -1067,11 +1160,11 @@ __device__ __forceinline__ void k_restrict_p_zline_d(const Blk& wg, Dims g, cons
     zline_seg_body<LMAX, T, true, true>(g, A, aux, b, x, 0, L, nseg, cpb, col0, t, sA, sB, bin);
 }
 template <int LMAX, class T>
-__global__ __launch_bounds__(1024) void k_restrict_p_zline(Dims g, const double* __restrict__ v,
+__global__ __launch_bounds__(1024) void k_restrict_p_zline(Dims g, const double* __restrict__ v, CsVec cv,
                                                            const T* __restrict__ A, const T* __restrict__ aux,
                                                            T* __restrict__ b, T* __restrict__ x, int L, int nseg,
-                                                           int cpb, int cs) {
-    k_restrict_p_zline_d<LMAX, T>(PF_BLK, g, v, A, aux, b, x, L, nseg, cpb, cs);
+                                                           int cpb) {
+    k_restrict_p_zline_d<LMAX, T>(PF_BLK, g, v, cv, A, aux, b, x, L, nseg, cpb);
 }
 template <int LMAX, class T>
 struct F_k_restrict_p_zline {
@@ -1753,18 +1846,33 @@ struct F_k_ilu_apply_t {
     }
 };
 
-// FP64 stage residual and forward ILU phases from the colour-split copies of
-// J.  The stage residual t = v - J (p, 0, 0) - B pb needs only the P-columns
-// of a row's blocks, and the black rows' off-diagonal blocks are read by the
-// forward black phase anyway: that phase forms its own rows' t from them, so
-// no t is stored and the P-columns of black rows are read once.  Subtraction
-// order as in stage_resid_cell and k_ilu_apply_t (all P-column terms in face
-// order, then the border, then the ILU sum).
-__device__ __forceinline__ void stage_border(const int32_t* __restrict__ pc_map, const int32_t* __restrict__ pc_first,
-                                             const int32_t* __restrict__ perf_well, const double* __restrict__ B,
-                                             const double* __restrict__ pb, int64_t i, double& t0, double& t1,
-                                             double& t2) {
-    const int32_t k = pc_map[i];
+// FP64 preconditioner and product from the colour-split copies of J (PF order).
+// With p the pressure stage's correction (pb in the well entries) and M = L U
+// of red-black ILU(0), z = p + M^{-1} (v - J p) and w = J z.  As D_r = J_rr,
+// with e the P unit vector:
+//   - the forward red phase is y_r = D_r^{-1} (v - J p)_r = z^f_r - p_r e with
+//       z^f_r = D_r^{-1} (v_r - sum J_rb e p_b - B_r pb);
+//   - the forward black phase takes v_b - (J p)_b - sum J_br y_r, in which the
+//     red p cancel:  y_b = D~_b^{-1} (v_b - J_bb e p_b - B_b pb - sum J_br z^f_r);
+//     z_b = y_b + p_b e;
+//   - the backward red phase solves the red rows of J z = v exactly:
+//       z_r = D_r^{-1} (v_r - sum J_rb z_b - B_r pb);
+//   - so w_r = v_r, and only w_b = J_bb z_b + sum J_br z_r + B_b pb is formed.
+// The red p are not needed at all, and since w_r = v_r the red part of every
+// Krylov vector is a multiple of the first one's (v_r = alpha u), so that the
+// Arnoldi process stores and reads the black cells and wells alone.
+// All four kernels are bound by HBM, by the blocks they stream (276, 560, 532
+// and 524 bytes a cell of their colour).  On 300^3, against the forms that
+// carried the red p and w_r and left B pb to launches of their own:
+// k_stage_red 888 -> 769 us, k_ilu_black_stage 1675 -> 1598, k_ilu_red_spmv
+// 1689 -> 1510, k_black_spmv 1550 -> 1492; on 300 cells two launches fewer of
+// 17 an iteration.
+//
+// The well border, B pb, by way of a cell's entry in pc_map (-1: none).
+__device__ __forceinline__ void sub_border(const int32_t* __restrict__ pc_first,
+                                           const int32_t* __restrict__ perf_well, const double* __restrict__ B,
+                                           const double* __restrict__ pb, int32_t k, double& t0, double& t1,
+                                           double& t2) {
     if (k < 0) return;
     double a0 = 0.0, a1 = 0.0, a2 = 0.0;
     for (int64_t q = pc_first[k]; q < pc_first[k + 1]; ++q) {
@@ -1778,11 +1886,10 @@ __device__ __forceinline__ void stage_border(const int32_t* __restrict__ pc_map,
     t2 = t2 - a2;
 }
 
-// The kernels below work on v, z and w in the colour-split layout (the
-// FP64 path in PF order; pf_internal.h): a cell of slot s and colour c has
-// its entries at e*lp + c*ns + s, and its neighbours, all of the other
-// colour, at the slots cs_nbr gives; p (the pressure-stage correction) stays
-// in natural cell order.  Pad slots (odd nx) are written zero.
+// Vectors are in the colour-split layout (pf_internal.h): entry e of slot s is
+// at e ns + s for red cells and 3 ns further on for black ones; a cell's
+// neighbours, all of the other colour, are at the slots cs_nbr gives.  Pad
+// slots (odd nx) are written zero.
 //
 // Slot of the neighbour across face q (-x, +x, -y, +y, -z, +z) in the other
 // colour's half: along x the neighbour shares the slot or the next/previous
@@ -1799,10 +1906,29 @@ __device__ __forceinline__ int64_t cs_nbr(const DevModel& m, int64_t s, int64_t 
     }
 }
 
-// Red slots: t_r, then the first phase z_r = D_r^{-1} t_r.
+// pc_map in the colour-split slots (2 ns, -1 in the pads)
+__device__ __forceinline__ void k_pc_map_cs_d(const Blk& wg, DevModel m, const int32_t* __restrict__ map,
+                                              int32_t* __restrict__ out) {
+    const int64_t q = (int64_t)wg.x * blockDim.x + threadIdx.x, ns = ilu_slots(m);
+    if (q >= 2 * ns) return;
+    const int c = q >= ns ? 1 : 0;
+    int64_t ix, iy, iz;
+    out[q] = ilu_slot_cell(m, c, q - c * ns, ix, iy, iz) ? map[ix + m.nx * iy + m.nxy * iz] : -1;
+}
+__global__ void k_pc_map_cs(DevModel m, const int32_t* __restrict__ map, int32_t* __restrict__ out) {
+    k_pc_map_cs_d(PF_BLK, m, map, out);
+}
+struct F_k_pc_map_cs {
+    static constexpr int kLB = 1024;
+    template <class... A>
+    __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
+        k_pc_map_cs_d(wg, a...);
+    }
+};
+
+// z^f_r on the red slots.
 __device__ __forceinline__ void k_stage_red_d(const Blk& wg, DevModel m, const double* __restrict__ Lc,
-                                              const double* __restrict__ Jdc, const double* __restrict__ Dc,
-                                              const double* __restrict__ v, const double* __restrict__ p,
+                                              const double* __restrict__ Dc, CsVec v, const double* __restrict__ p,
                                               const double* __restrict__ pb, const double* __restrict__ B,
                                               const int32_t* __restrict__ pc_map,
                                               const int32_t* __restrict__ pc_first,
@@ -1811,43 +1937,37 @@ __device__ __forceinline__ void k_stage_red_d(const Blk& wg, DevModel m, const d
     const int64_t ns = ilu_slots(m);
     if (v0 >= ns) return;
     const int64_t s = strip_slot(m, v0);
-    const int64_t lp = 2 * ns;
     int64_t ix, iy, iz;
     if (!ilu_slot_cell(m, 0, s, ix, iy, iz)) {
-        z[s] = 0.0; z[lp + s] = 0.0; z[2 * lp + s] = 0.0;
+        z[s] = 0.0; z[ns + s] = 0.0; z[2 * ns + s] = 0.0;
         return;
     }
-    const int64_t i = ix + m.nx * iy + m.nxy * iz;
-    const double pi = p[i];
-    const double* Jd = Jdc + s;
-    double t0 = v[s] - ilu_ld(Jd + 0 * ns) * pi;
-    double t1 = v[lp + s] - ilu_ld(Jd + 3 * ns) * pi;
-    double t2 = v[2 * lp + s] - ilu_ld(Jd + 6 * ns) * pi;
+    const double al = *v.alpha;
+    const int32_t pc = pc_map[s];
+    double t0 = al * v.u[s], t1 = al * v.u[ns + s], t2 = al * v.u[2 * ns + s];
     const bool ex[6] = {ix > 0, ix + 1 < m.nx, iy > 0, iy + 1 < m.ny, iz > 0, iz + 1 < m.nz};
-    const int64_t off[6] = {-1, 1, -(int64_t)m.nx, (int64_t)m.nx, -m.nxy, m.nxy};
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
         if (!ex[q]) continue;
-        const double pj = p[i + off[q]];
+        const double pj = p[cs_nbr(m, s, ix, q)];
         const double* Bq = Lc + (int64_t)(q * 9) * ns + s;
         t0 -= ilu_ld(Bq + 0 * ns) * pj;
         t1 -= ilu_ld(Bq + 3 * ns) * pj;
         t2 -= ilu_ld(Bq + 6 * ns) * pj;
     }
-    stage_border(pc_map, pc_first, perf_well, B, pb, i, t0, t1, t2);
+    sub_border(pc_first, perf_well, B, pb, pc, t0, t1, t2);
     const double* D = Dc + s;
     z[s] = D[0 * ns] * t0 + D[1 * ns] * t1 + D[2 * ns] * t2;
-    z[lp + s] = D[3 * ns] * t0 + D[4 * ns] * t1 + D[5 * ns] * t2;
-    z[2 * lp + s] = D[6 * ns] * t0 + D[7 * ns] * t1 + D[8 * ns] * t2;
+    z[ns + s] = D[3 * ns] * t0 + D[4 * ns] * t1 + D[5 * ns] * t2;
+    z[2 * ns + s] = D[6 * ns] * t0 + D[7 * ns] * t1 + D[8 * ns] * t2;
 }
 __global__ __launch_bounds__(256) void k_stage_red(DevModel m, const double* __restrict__ Lc,
-                                                   const double* __restrict__ Jdc, const double* __restrict__ Dc,
-                                                   const double* __restrict__ v, const double* __restrict__ p,
-                                                   const double* __restrict__ pb, const double* __restrict__ B,
-                                                   const int32_t* __restrict__ pc_map,
+                                                   const double* __restrict__ Dc, CsVec v,
+                                                   const double* __restrict__ p, const double* __restrict__ pb,
+                                                   const double* __restrict__ B, const int32_t* __restrict__ pc_map,
                                                    const int32_t* __restrict__ pc_first,
                                                    const int32_t* __restrict__ perf_well, double* __restrict__ z) {
-    k_stage_red_d(PF_BLK, m, Lc, Jdc, Dc, v, p, pb, B, pc_map, pc_first, perf_well, z);
+    k_stage_red_d(PF_BLK, m, Lc, Dc, v, p, pb, B, pc_map, pc_first, perf_well, z);
 }
 struct F_k_stage_red {
     static constexpr int kLB = 256;
@@ -1857,11 +1977,27 @@ struct F_k_stage_red {
     }
 };
 
-// Black slots: t_b from its blocks' P-columns and the border, then the
-// forward black phase y_b = D~_b^{-1} (t_b - sum J_br y_r), z_b = y_b.
+// sums of the off-diagonal blocks of one colour's cell times the neighbours' z
+__device__ __forceinline__ void off_diagonal(const DevModel& m, const double* __restrict__ L,
+                                             const double* __restrict__ z, int64_t ns, int64_t s, int64_t ix,
+                                             int64_t iy, int64_t iz, double& s0, double& s1, double& s2) {
+    const bool ex[6] = {ix > 0, ix + 1 < m.nx, iy > 0, iy + 1 < m.ny, iz > 0, iz + 1 < m.nz};
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+        if (!ex[q]) continue;
+        const int64_t r = cs_nbr(m, s, ix, q);
+        const double a = z[r], b = z[ns + r], c = z[2 * ns + r];
+        const double* Bq = L + (int64_t)(q * 9) * ns + s;
+        s0 += ilu_ld(Bq + 0 * ns) * a + ilu_ld(Bq + 1 * ns) * b + ilu_ld(Bq + 2 * ns) * c;
+        s1 += ilu_ld(Bq + 3 * ns) * a + ilu_ld(Bq + 4 * ns) * b;       // entry (oil, C) is zero
+        s2 += ilu_ld(Bq + 6 * ns) * a + ilu_ld(Bq + 7 * ns) * b + ilu_ld(Bq + 8 * ns) * c;
+    }
+}
+
+// z_b on the black slots, from z^f on the red ones.
 __device__ __forceinline__ void k_ilu_black_stage_d(const Blk& wg, DevModel m, const double* __restrict__ Lc,
                                                     const double* __restrict__ Jdc, const double* __restrict__ Dc,
-                                                    const double* __restrict__ v, const double* __restrict__ p,
+                                                    CsVec v, const double* __restrict__ p,
                                                     const double* __restrict__ pb, const double* __restrict__ B,
                                                     const int32_t* __restrict__ pc_map,
                                                     const int32_t* __restrict__ pc_first,
@@ -1870,50 +2006,32 @@ __device__ __forceinline__ void k_ilu_black_stage_d(const Blk& wg, DevModel m, c
     const int64_t ns = ilu_slots(m);
     if (v0 >= ns) return;
     const int64_t s = strip_slot(m, v0);
-    const int64_t lp = 2 * ns, o = ns + s;     // this cell's entries
+    double* zb = z + 3 * ns;
     int64_t ix, iy, iz;
     if (!ilu_slot_cell(m, 1, s, ix, iy, iz)) {
-        z[o] = 0.0; z[lp + o] = 0.0; z[2 * lp + o] = 0.0;
+        zb[s] = 0.0; zb[ns + s] = 0.0; zb[2 * ns + s] = 0.0;
         return;
     }
-    const int64_t i = ix + m.nx * iy + m.nxy * iz;
-    const double pi = p[i];
+    const double pi = p[s];
+    const int32_t pc = pc_map[ns + s];
     const double* Jd = Jdc + 9 * ns + s;
-    double t0 = v[o] - ilu_ld(Jd + 0 * ns) * pi;
-    double t1 = v[lp + o] - ilu_ld(Jd + 3 * ns) * pi;
-    double t2 = v[2 * lp + o] - ilu_ld(Jd + 6 * ns) * pi;
-    const bool ex[6] = {ix > 0, ix + 1 < m.nx, iy > 0, iy + 1 < m.ny, iz > 0, iz + 1 < m.nz};
-    const int64_t off[6] = {-1, 1, -(int64_t)m.nx, (int64_t)m.nx, -m.nxy, m.nxy};
+    double t0 = v.b[s] - ilu_ld(Jd + 0 * ns) * pi;
+    double t1 = v.b[ns + s] - ilu_ld(Jd + 3 * ns) * pi;
+    double t2 = v.b[2 * ns + s] - ilu_ld(Jd + 6 * ns) * pi;
     double s0 = 0, s1 = 0, s2 = 0;
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-        if (!ex[q]) continue;
-        const double pj = p[i + off[q]];
-        const int64_t r = cs_nbr(m, s, ix, q);          // red neighbour
-        const double a = z[r], b = z[lp + r], c = z[2 * lp + r];
-        const double* Bq = Lc + (int64_t)(54 + q * 9) * ns + s;
-        const double e0 = ilu_ld(Bq + 0 * ns), e1 = ilu_ld(Bq + 1 * ns), e2 = ilu_ld(Bq + 2 * ns);
-        const double e3 = ilu_ld(Bq + 3 * ns), e4 = ilu_ld(Bq + 4 * ns);   // entry (oil, C) is zero
-        const double e6 = ilu_ld(Bq + 6 * ns), e7 = ilu_ld(Bq + 7 * ns), e8 = ilu_ld(Bq + 8 * ns);
-        t0 -= e0 * pj;
-        t1 -= e3 * pj;
-        t2 -= e6 * pj;
-        s0 += e0 * a + e1 * b + e2 * c;
-        s1 += e3 * a + e4 * b;
-        s2 += e6 * a + e7 * b + e8 * c;
-    }
-    stage_border(pc_map, pc_first, perf_well, B, pb, i, t0, t1, t2);
+    off_diagonal(m, Lc + 54 * ns, z, ns, s, ix, iy, iz, s0, s1, s2);
+    sub_border(pc_first, perf_well, B, pb, pc, t0, t1, t2);
     t0 -= s0;
     t1 -= s1;
     t2 -= s2;
     const double* D = Dc + 9 * ns + s;
-    z[o] = D[0 * ns] * t0 + D[1 * ns] * t1 + D[2 * ns] * t2;
-    z[lp + o] = D[3 * ns] * t0 + D[4 * ns] * t1 + D[5 * ns] * t2;
-    z[2 * lp + o] = D[6 * ns] * t0 + D[7 * ns] * t1 + D[8 * ns] * t2;
+    zb[s] = D[0 * ns] * t0 + D[1 * ns] * t1 + D[2 * ns] * t2 + pi;
+    zb[ns + s] = D[3 * ns] * t0 + D[4 * ns] * t1 + D[5 * ns] * t2;
+    zb[2 * ns + s] = D[6 * ns] * t0 + D[7 * ns] * t1 + D[8 * ns] * t2;
 }
 __global__ __launch_bounds__(256) void k_ilu_black_stage(DevModel m, const double* __restrict__ Lc,
                                                          const double* __restrict__ Jdc,
-                                                         const double* __restrict__ Dc, const double* __restrict__ v,
+                                                         const double* __restrict__ Dc, CsVec v,
                                                          const double* __restrict__ p, const double* __restrict__ pb,
                                                          const double* __restrict__ B,
                                                          const int32_t* __restrict__ pc_map,
@@ -1930,68 +2048,41 @@ struct F_k_ilu_black_stage {
     }
 };
 
-// Flexible GMRES multiplies every preconditioned vector by J at once, so
-// with red-black ILU(0) the last two steps of the preconditioner carry the
-// product along.  Both kernels read only colour-split storage (Lc and Jdc
-// hold J itself): the red rows of the product need no blocks of J at all
-// (below), and the black rows read theirs once for the product.
-//
-// Red slots, after phase 1: z holds y_r on red and the smoother's z_b on
-// black cells.  The backward phase z_r = y_r - D_r^{-1} sum J_rb z_b, then
-// the pressure correction z_r += (p_r, 0, 0) (stored).  The red rows of the
-// product need no arithmetic: red-black ILU(0) leaves the red diagonal
-// blocks as they are (D_r = J_rr), so the factorisation M differs from J in
-// black rows only, and with z = p + M^{-1} (v - J p) (the well entries of z
-// being the pressure stage's pb) the red rows of J z are (J p)_r + (M z -
-// M p)_r = v_r.  w_r = v_r is stored; the well border is then added to the
-// black rows only.
+// z_r on the red slots, from z_b (the red rows of J z are then v_r).
 __device__ __forceinline__ void k_ilu_red_spmv_d(const Blk& wg, DevModel m, const double* __restrict__ Lc,
-                                                 const double* __restrict__ Dc, const double* __restrict__ v,
-                                                 const double* __restrict__ p, double* __restrict__ z,
-                                                 double* __restrict__ w) {
+                                                 const double* __restrict__ Dc, CsVec v,
+                                                 const double* __restrict__ pb, const double* __restrict__ B,
+                                                 const int32_t* __restrict__ pc_map,
+                                                 const int32_t* __restrict__ pc_first,
+                                                 const int32_t* __restrict__ perf_well, double* __restrict__ z) {
     const int64_t v0 = xcd_block(wg) * blockDim.x + threadIdx.x;
     const int64_t ns = ilu_slots(m);
     if (v0 >= ns) return;
     const int64_t s = strip_slot(m, v0);
-    const int64_t lp = 2 * ns;
     int64_t ix, iy, iz;
-    if (!ilu_slot_cell(m, 0, s, ix, iy, iz)) {
-        w[s] = 0.0; w[lp + s] = 0.0; w[2 * lp + s] = 0.0;
-        return;
-    }
-    const int64_t i = ix + m.nx * iy + m.nxy * iz;
-    const bool ex[6] = {ix > 0, ix + 1 < m.nx, iy > 0, iy + 1 < m.ny, iz > 0, iz + 1 < m.nz};
+    if (!ilu_slot_cell(m, 0, s, ix, iy, iz)) return;
+    const double al = *v.alpha;
+    const int32_t pc = pc_map[s];
+    double t0 = al * v.u[s], t1 = al * v.u[ns + s], t2 = al * v.u[2 * ns + s];
     double s0 = 0, s1 = 0, s2 = 0;
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-        if (!ex[q]) continue;
-        const int64_t r = ns + cs_nbr(m, s, ix, q);     // black neighbour
-        const double a = z[r], b = z[lp + r], c = z[2 * lp + r];
-        const double* B = Lc + (int64_t)(q * 9) * ns + s;
-        const double e0 = ilu_ld(B + 0 * ns), e1 = ilu_ld(B + 1 * ns), e2 = ilu_ld(B + 2 * ns);
-        const double e3 = ilu_ld(B + 3 * ns), e4 = ilu_ld(B + 4 * ns);   // entry (oil, C) is zero
-        const double e6 = ilu_ld(B + 6 * ns), e7 = ilu_ld(B + 7 * ns), e8 = ilu_ld(B + 8 * ns);
-        s0 += e0 * a + e1 * b + e2 * c;
-        s1 += e3 * a + e4 * b;
-        s2 += e6 * a + e7 * b + e8 * c;
-    }
-    const double t0 = -s0, t1 = -s1, t2 = -s2;
+    off_diagonal(m, Lc, z + 3 * ns, ns, s, ix, iy, iz, s0, s1, s2);
+    sub_border(pc_first, perf_well, B, pb, pc, t0, t1, t2);
+    t0 -= s0;
+    t1 -= s1;
+    t2 -= s2;
     const double* D = Dc + s;
-    const double z0 = z[s] + (D[0 * ns] * t0 + D[1 * ns] * t1 + D[2 * ns] * t2) + p[i];
-    const double z1 = z[lp + s] + (D[3 * ns] * t0 + D[4 * ns] * t1 + D[5 * ns] * t2);
-    const double z2 = z[2 * lp + s] + (D[6 * ns] * t0 + D[7 * ns] * t1 + D[8 * ns] * t2);
-    z[s] = z0;
-    z[lp + s] = z1;
-    z[2 * lp + s] = z2;
-    w[s] = v[s];
-    w[lp + s] = v[lp + s];
-    w[2 * lp + s] = v[2 * lp + s];
+    z[s] = D[0 * ns] * t0 + D[1 * ns] * t1 + D[2 * ns] * t2;
+    z[ns + s] = D[3 * ns] * t0 + D[4 * ns] * t1 + D[5 * ns] * t2;
+    z[2 * ns + s] = D[6 * ns] * t0 + D[7 * ns] * t1 + D[8 * ns] * t2;
 }
 __global__ __launch_bounds__(256) void k_ilu_red_spmv(DevModel m, const double* __restrict__ Lc,
-                                                      const double* __restrict__ Dc, const double* __restrict__ v,
-                                                      const double* __restrict__ p, double* __restrict__ z,
-                                                      double* __restrict__ w) {
-    k_ilu_red_spmv_d(PF_BLK, m, Lc, Dc, v, p, z, w);
+                                                      const double* __restrict__ Dc, CsVec v,
+                                                      const double* __restrict__ pb, const double* __restrict__ B,
+                                                      const int32_t* __restrict__ pc_map,
+                                                      const int32_t* __restrict__ pc_first,
+                                                      const int32_t* __restrict__ perf_well,
+                                                      double* __restrict__ z) {
+    k_ilu_red_spmv_d(PF_BLK, m, Lc, Dc, v, pb, B, pc_map, pc_first, perf_well, z);
 }
 struct F_k_ilu_red_spmv {
     static constexpr int kLB = 256;
@@ -2001,55 +2092,70 @@ struct F_k_ilu_red_spmv {
     }
 };
 
-// Black slots, after k_ilu_red_spmv: the pressure correction z_b += (p_b,
-// 0, 0) (stored) and w_b = J_bb z_b + sum J_br z_r over the final red
-// values.  The nw threads past the black slots set the well entries z_w =
-// pb (in PF order the smoother's well rows are zero).  The well border of
-// w follows in k_spmv_border.
+// w_b = J_bb z_b + sum J_br z_r + B pb on the black slots (blocks [0, ncb));
+// in the nw blocks after those the well entries z_w = pb and the well rows
+// w_w = sum C z_cell + D pb, one wavefront per well.
 __device__ __forceinline__ void k_black_spmv_d(const Blk& wg, DevModel m, const double* __restrict__ Lc,
-                                               const double* __restrict__ Jdc, const double* __restrict__ p,
-                                               const double* __restrict__ pb, double* __restrict__ z,
+                                               const double* __restrict__ Jdc, const double* __restrict__ pb,
+                                               const double* __restrict__ B, const int32_t* __restrict__ pc_map,
+                                               const int32_t* __restrict__ pc_first,
+                                               const int32_t* __restrict__ perf_well,
+                                               const int32_t* __restrict__ perf_cell,
+                                               const int32_t* __restrict__ wp_first,
+                                               const int32_t* __restrict__ wp_idx, const double* __restrict__ Cw,
+                                               const double* __restrict__ Dw, int ncb, double* __restrict__ z,
                                                double* __restrict__ w) {
-    const int64_t v0 = xcd_block(wg) * blockDim.x + threadIdx.x;
     const int64_t ns = ilu_slots(m);
-    if (v0 >= ns) {
-        if (v0 < ns + m.nw) z[3 * 2 * ns + (v0 - ns)] = pb[v0 - ns];
+    if ((int)wg.x >= ncb) {
+        const int k = (int)wg.x - ncb;
+        if (threadIdx.x >= 64) return;
+        double a = 0.0;
+        for (int q = wp_first[k] + (int)threadIdx.x; q < wp_first[k + 1]; q += 64) {
+            const int f = wp_idx[q];
+            const int64_t c = cs_index(m, perf_cell[f]);
+            a += Cw[3 * f] * z[c] + Cw[3 * f + 1] * z[ns + c] + Cw[3 * f + 2] * z[2 * ns + c];
+        }
+        for (int o = 32; o > 0; o >>= 1) a += __shfl_down(a, o, 64);
+        if (threadIdx.x == 0) {
+            z[6 * ns + k] = pb[k];
+            w[3 * ns + k] = a + Dw[k] * pb[k];
+        }
         return;
     }
+    const int64_t v0 = xcd_block(Blk{wg.x, (uint32_t)ncb}) * blockDim.x + threadIdx.x;
+    if (v0 >= ns) return;
     const int64_t s = strip_slot(m, v0);
-    const int64_t lp = 2 * ns, o = ns + s;
     int64_t ix, iy, iz;
     if (!ilu_slot_cell(m, 1, s, ix, iy, iz)) {
-        w[o] = 0.0; w[lp + o] = 0.0; w[2 * lp + o] = 0.0;
+        w[s] = 0.0; w[ns + s] = 0.0; w[2 * ns + s] = 0.0;
         return;
     }
-    const int64_t i = ix + m.nx * iy + m.nxy * iz;
-    const double z0 = z[o] + p[i], z1 = z[lp + o], z2 = z[2 * lp + o];
-    z[o] = z0;
+    const double* zb = z + 3 * ns;
+    const double z0 = zb[s], z1 = zb[ns + s], z2 = zb[2 * ns + s];
+    const int32_t pc = pc_map[ns + s];
     const double* Jd = Jdc + 9 * ns + s;
     double y0 = ilu_ld(Jd + 0 * ns) * z0 + ilu_ld(Jd + 1 * ns) * z1 + ilu_ld(Jd + 2 * ns) * z2;
-    double y1 = ilu_ld(Jd + 3 * ns) * z0 + ilu_ld(Jd + 4 * ns) * z1;   // entry (oil, C) is zero
+    double y1 = ilu_ld(Jd + 3 * ns) * z0 + ilu_ld(Jd + 4 * ns) * z1;       // entry (oil, C) is zero
     double y2 = ilu_ld(Jd + 6 * ns) * z0 + ilu_ld(Jd + 7 * ns) * z1 + ilu_ld(Jd + 8 * ns) * z2;
-    const bool ex[6] = {ix > 0, ix + 1 < m.nx, iy > 0, iy + 1 < m.ny, iz > 0, iz + 1 < m.nz};
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-        if (!ex[q]) continue;
-        const int64_t r = cs_nbr(m, s, ix, q);          // red neighbour
-        const double a = z[r], b = z[lp + r], c = z[2 * lp + r];
-        const double* B = Lc + (int64_t)(54 + q * 9) * ns + s;
-        y0 += ilu_ld(B + 0 * ns) * a + ilu_ld(B + 1 * ns) * b + ilu_ld(B + 2 * ns) * c;
-        y1 += ilu_ld(B + 3 * ns) * a + ilu_ld(B + 4 * ns) * b;   // entry (oil, C) is zero
-        y2 += ilu_ld(B + 6 * ns) * a + ilu_ld(B + 7 * ns) * b + ilu_ld(B + 8 * ns) * c;
-    }
-    w[o] = y0;
-    w[lp + o] = y1;
-    w[2 * lp + o] = y2;
+    off_diagonal(m, Lc + 54 * ns, z, ns, s, ix, iy, iz, y0, y1, y2);
+    y0 = -y0; y1 = -y1; y2 = -y2;
+    sub_border(pc_first, perf_well, B, pb, pc, y0, y1, y2);
+    w[s] = -y0;
+    w[ns + s] = -y1;
+    w[2 * ns + s] = -y2;
 }
 __global__ __launch_bounds__(256) void k_black_spmv(DevModel m, const double* __restrict__ Lc,
-                                                    const double* __restrict__ Jdc, const double* __restrict__ p,
-                                                    const double* __restrict__ pb, double* __restrict__ z,
+                                                    const double* __restrict__ Jdc, const double* __restrict__ pb,
+                                                    const double* __restrict__ B, const int32_t* __restrict__ pc_map,
+                                                    const int32_t* __restrict__ pc_first,
+                                                    const int32_t* __restrict__ perf_well,
+                                                    const int32_t* __restrict__ perf_cell,
+                                                    const int32_t* __restrict__ wp_first,
+                                                    const int32_t* __restrict__ wp_idx, const double* __restrict__ Cw,
+                                                    const double* __restrict__ Dw, int ncb, double* __restrict__ z,
                                                     double* __restrict__ w) {
-    k_black_spmv_d(PF_BLK, m, Lc, Jdc, p, pb, z, w);
+    k_black_spmv_d(PF_BLK, m, Lc, Jdc, pb, B, pc_map, pc_first, perf_well, perf_cell, wp_first, wp_idx, Cw, Dw, ncb, z,
+                   w);
 }
 struct F_k_black_spmv {
     static constexpr int kLB = 256;
@@ -2236,7 +2342,7 @@ bool zline_full_sweeps(Sim& s, const MGLevel& L, int zero_init, int sweeps) {
 // false (nothing launched) where level 0 is the coarsest or its segments
 // take the memory-staged kernel.
 template <class T>
-bool restrict_p_zline(Sim& s, const double* v, int cs) {
+bool restrict_p_zline(Sim& s, const double* v, const CsVec& cv) {
     const MGLevel& L = s.mg[0];
     if (s.mg.size() < 2 || !L.split) return false;
     const ZlShape z = zline_shape(s, L);
@@ -2246,14 +2352,14 @@ bool restrict_p_zline(Sim& s, const double* v, int cs) {
     T *b = Lv<T>::b(L), *x = Lv<T>::x(L);
     const dim3 blocks(z.blocks), threads(z.threads);
     if (z.lmax == 2)
-        launch<F_k_restrict_p_zline<2, T>>(s, s.stream, (k_restrict_p_zline<2, T>), blocks, threads, 0, g, v, A, aux,
-                                           b, x, z.len, z.nseg, z.cpb, cs);
+        launch<F_k_restrict_p_zline<2, T>>(s, s.stream, (k_restrict_p_zline<2, T>), blocks, threads, 0, g, v, cv, A,
+                                           aux, b, x, z.len, z.nseg, z.cpb);
     else if (z.lmax == 4)
-        launch<F_k_restrict_p_zline<4, T>>(s, s.stream, (k_restrict_p_zline<4, T>), blocks, threads, 0, g, v, A, aux,
-                                           b, x, z.len, z.nseg, z.cpb, cs);
+        launch<F_k_restrict_p_zline<4, T>>(s, s.stream, (k_restrict_p_zline<4, T>), blocks, threads, 0, g, v, cv, A,
+                                           aux, b, x, z.len, z.nseg, z.cpb);
     else
-        launch<F_k_restrict_p_zline<8, T>>(s, s.stream, (k_restrict_p_zline<8, T>), blocks, threads, 0, g, v, A, aux,
-                                           b, x, z.len, z.nseg, z.cpb, cs);
+        launch<F_k_restrict_p_zline<8, T>>(s, s.stream, (k_restrict_p_zline<8, T>), blocks, threads, 0, g, v, cv, A,
+                                           aux, b, x, z.len, z.nseg, z.cpb);
     PF_LAUNCH_CHECK();
     return true;
 }
@@ -2430,18 +2536,82 @@ void cpr_setup(Sim& s) {
 
 namespace {
 
+// The levels of the upward pass from level 0, the first nl of them.
 template <class T>
-void launch_prolong_chain(Sim& s, const Dims& g, const ProlongChain& pc, T* x, T* pout) {
-    const dim3 grid(grid_for((int64_t)g.nx * g.ny * g.nz)), block(kBlock);
+ProlongChain prolong_chain(const Sim& s, int nl) {
+    ProlongChain pc{};
+    pc.nl = nl;
+    for (int q = 1; q < nl; ++q) {
+        const MGLevel& F = s.mg[q - 1];
+        pc.sx[q] = pc.sx[q - 1] + (F.cx == 2);
+        pc.sy[q] = pc.sy[q - 1] + (F.cy == 2);
+        pc.sz[q] = pc.sz[q - 1] + (F.cz == 2);
+        pc.d[q] = dims_of(s.mg[q]);
+        pc.x[q] = Lv<T>::x(s.mg[q]);
+    }
+    return pc;
+}
+
+#define PF_CHAIN_CASES PF_CASE(1) PF_CASE(2) PF_CASE(3) PF_CASE(4) PF_CASE(5) PF_CASE(6) PF_CASE(7) PF_CASE(8) PF_CASE(9)
+
+// to p, natural order
+template <class T>
+void launch_prolong_chain(Sim& s, const ProlongChain& pc, T* p) {
+    const MGLevel& L = s.mg[0];
+    const dim3 grid(grid_for(L.n)), block(kBlock);
     switch (pc.nl) {
-#define PF_CASE(K)                                                                                        \
-    case K:                                                                                               \
-        launch<F_k_prolong_chain<T, K>>(s, s.stream, (k_prolong_chain<T, K>), grid, block, 0, g, pc, x, pout); \
+#define PF_CASE(K)                                                                                                 \
+    case K:                                                                                                        \
+        launch<F_k_prolong_chain<T, K>>(s, s.stream, (k_prolong_chain<T, K>), grid, block, 0, dims_of(L), pc,      \
+                                        (const T*)Lv<T>::x(L), p);                                                 \
         break;
-        PF_CASE(2) PF_CASE(3) PF_CASE(4) PF_CASE(5) PF_CASE(6) PF_CASE(7) PF_CASE(8) PF_CASE(9)
-        PF_CASE(10) PF_CASE(11) PF_CASE(12) PF_CASE(13) PF_CASE(14) PF_CASE(15) PF_CASE(16)
+        PF_CHAIN_CASES
 #undef PF_CASE
-        default: launch<F_k_prolong_chain<T, 0>>(s, s.stream, (k_prolong_chain<T, 0>), grid, block, 0, g, pc, x, pout);
+        default:
+            launch<F_k_prolong_chain<T, 0>>(s, s.stream, (k_prolong_chain<T, 0>), grid, block, 0, dims_of(L), pc,
+                                            (const T*)Lv<T>::x(L), p);
+    }
+    PF_LAUNCH_CHECK();
+}
+
+// into level 0's colour-1 columns
+template <class T>
+void launch_prolong_half(Sim& s, const ProlongChain& pc) {
+    const MGLevel& L = s.mg[0];
+    const dim3 grid(grid_for(L.ns / 2)), block(kBlock);
+    switch (pc.nl) {
+#define PF_CASE(K)                                                                                            \
+    case K:                                                                                                   \
+        launch<F_k_prolong_half<T, K>>(s, s.stream, (k_prolong_half<T, K>), grid, block, 0, dims_of(L), pc,   \
+                                       Lv<T>::x(L));                                                          \
+        break;
+        PF_CHAIN_CASES
+#undef PF_CASE
+        default:
+            launch<F_k_prolong_half<T, 0>>(s, s.stream, (k_prolong_half<T, 0>), grid, block, 0, dims_of(L), pc,
+                                           Lv<T>::x(L));
+    }
+    PF_LAUNCH_CHECK();
+}
+
+// to the black cells of p and the well pressures (vw: the well rows of v)
+void launch_prolong_black(Sim& s, const ProlongChain& pc, const double* vw) {
+    const MGLevel& L = s.mg[0];
+    const int ncb = (int)grid_for(cs_ns(s.m));
+    const dim3 grid(ncb + s.m.nw), block(kBlock);
+    switch (pc.nl) {
+#define PF_CASE(K)                                                                                             \
+    case K:                                                                                                    \
+        launch<F_k_prolong_black<K>>(s, s.stream, k_prolong_black<K>, grid, block, 0, dims_of(L), pc,          \
+                                     (const double*)L.x, s.pnat, ncb, s.wp_first, s.wp_idx, s.perf_cell, s.Cw, \
+                                     s.Dw, vw, s.pb);                                                          \
+        break;
+        PF_CHAIN_CASES
+#undef PF_CASE
+        default:
+            launch<F_k_prolong_black<0>>(s, s.stream, k_prolong_black<0>, grid, block, 0, dims_of(L), pc,
+                                         (const double*)L.x, s.pnat, ncb, s.wp_first, s.wp_idx, s.perf_cell, s.Cw,
+                                         s.Dw, vw, s.pb);
     }
     PF_LAUNCH_CHECK();
 }
@@ -2471,10 +2641,13 @@ void join_coarse(Sim& s) {
 }
 
 // One V-cycle from level l.  At level 0 of the last cycle, pout receives the
-// level-0 correction in natural cell order.  first_done: the first colour-0
-// half-sweep of level l (from x = 0) was done with the restriction onto it.
+// level-0 correction: in natural cell order, or with vw (the well rows of a
+// colour-split v) on the black cells, and the well pressures.  first_done: the
+// first colour-0 half-sweep of level l (from x = 0) was done with the
+// restriction onto it.
 template <class T>
-void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_done = false) {
+void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_done = false,
+            const double* vw = nullptr) {
     const int nl = (int)s.mg.size();
     MGLevel& L = s.mg[l];
     const Dims g = dims_of(L);
@@ -2482,7 +2655,7 @@ void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_don
     const int nt = nl <= kMaxChain ? mg_tail_first(s) : nl;
     if (l == nt && nt < nl) {
         join_coarse(s);
-        launch_mg_tail(s, l, 1, nullptr, 0, (T*)nullptr);
+        launch_mg_tail(s, l, 1, nullptr, nullptr, (T*)nullptr);
     } else if (l == nl - 1) {
         join_coarse(s);
         launch<F_k_coarse_apply<T>>(s, s.stream, k_coarse_apply<T>, dim3((unsigned)((L.n + 3) / 4)), dim3(256), 0,
@@ -2522,18 +2695,11 @@ void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_don
         if (post == 0 && nl <= kMaxChain) {
             // no post-smoothing: the whole upward pass is prolongation, done once from level 0
             if (l == 0) {
-                ProlongChain pc{};
-                pc.nl = std::min(nl, nt + 1);       // level nt's correction holds the coarser ones
-                for (int q = 1; q < pc.nl; ++q) {
-                    const MGLevel& F = s.mg[q - 1];
-                    pc.sx[q] = pc.sx[q - 1] + (F.cx == 2);
-                    pc.sy[q] = pc.sy[q - 1] + (F.cy == 2);
-                    pc.sz[q] = pc.sz[q - 1] + (F.cz == 2);
-                    pc.d[q] = dims_of(s.mg[q]);
-                    pc.x[q] = Lv<T>::x(s.mg[q]);
-                }
-                launch_prolong_chain<T>(s, g, pc, Lv<T>::x(L), pout);
-                PF_LAUNCH_CHECK();
+                // (level nt's correction holds the coarser ones)
+                const ProlongChain pc = prolong_chain<T>(s, std::min(nl, nt + 1));
+                if (vw) launch_prolong_black(s, pc, vw);
+                else if (pout) launch_prolong_chain<T>(s, pc, pout);
+                else launch_prolong_half<T>(s, pc);
             }
             return;
         }
@@ -2545,7 +2711,9 @@ void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_don
             zline_sweep<T>(s, L, 0, 0);
         }
     }
-    if (pout) {
+    if (vw) {
+        launch_prolong_black(s, prolong_chain<double>(s, 1), vw);
+    } else if (pout) {
         launch<F_k_gather_p<T>>(s, s.stream, k_gather_p<T>, dim3(grid_for(L.n)), dim3(kBlock), 0, g, Lv<T>::x(L),
                                 pout);
         PF_LAUNCH_CHECK();
@@ -2562,39 +2730,42 @@ void mg_smooth_once(Sim& s, int level, int colour, int zero_init) {
 
 namespace {
 
-// b = Pi_r v (water + oil rows of v, in the natural or, cs, the colour-split
-// layout); p = V-cycle(s) from p = 0.  Returns p in natural cell order.
+// b = Pi_r v (water + oil rows of v, natural layout, or of cv, colour-split);
+// p = V-cycle(s) from p = 0.  Returns p, in natural cell order or, for cv, on
+// the black cells in their slot order, with the well pressures in s.pb.
 template <class T>
-T* pressure_cycles(Sim& s, const double* v, int cs = 0) {
+T* pressure_cycles(Sim& s, const double* v, const CsVec* cv = nullptr) {
     const DevModel& m = s.m;
     T* p = Lv<T>::pnat(s);
+    const int cycles = std::max(1, s.opts.mg_cycles);
     if (mg_tail_first(s) == 0) {
         join_coarse(s);
-        launch_mg_tail(s, 0, std::max(1, s.opts.mg_cycles), v, cs, p);
+        launch_mg_tail(s, 0, cycles, v, cv, p);
         return p;
     }
-    const bool fused = restrict_p_zline<T>(s, v, cs);
+    const CsVec none{nullptr, nullptr, nullptr};
+    const bool fused = restrict_p_zline<T>(s, v, cv ? *cv : none);
     if (!fused) {
         launch<F_k_restrict_p<T>>(s, s.stream, k_restrict_p<T>, dim3(grid_for(m.n)), dim3(kBlock), 0,
-                                  dims_of(s.mg[0]), v, Lv<T>::b(s.mg[0]), cs);
+                                  dims_of(s.mg[0]), v, cv ? *cv : none, Lv<T>::b(s.mg[0]));
         PF_LAUNCH_CHECK();
     }
-    const int cycles = std::max(1, s.opts.mg_cycles);
-    for (int c = 0; c < cycles; ++c)
-        vcycle<T>(s, 0, c == 0 ? 1 : 0, c + 1 == cycles ? p : nullptr, fused && c == 0);
+    const double* vw = cv ? cv->b + 3 * cs_ns(m) : nullptr;
+    for (int c = 0; c < cycles; ++c) {
+        const bool last = c + 1 == cycles;
+        vcycle<T>(s, 0, c == 0 ? 1 : 0, last ? p : nullptr, fused && c == 0, last ? vw : nullptr);
+    }
     return p;
 }
 
 // Pressure stage: the V-cycles, then well pressures from the well rows.
 template <class T>
-const T* pressure_stage(Sim& s, const double* v, int cs = 0) {
+const T* pressure_stage(Sim& s, const double* v) {
     const DevModel& m = s.m;
-    const T* p = pressure_cycles<T>(s, v, cs);
+    const T* p = pressure_cycles<T>(s, v);
     if (m.nw > 0) {
-        // the well rows of v follow its three planes
-        const double* vw = v + 3 * (cs ? 2 * cs_ns(m) : m.n);
         launch<F_k_well_pb<T>>(s, s.stream, k_well_pb<T>, dim3(m.nw), dim3(64), 0, m, s.wp_first, s.wp_idx,
-                               s.perf_cell, s.Cw, s.Dw, vw, p, s.pb);
+                               s.perf_cell, s.Cw, s.Dw, v + 3 * m.n, p, s.pb);
         PF_LAUNCH_CHECK();
     }
     return p;
@@ -2722,46 +2893,49 @@ void ensure_j_natural(Sim& s) {
     s.j_nat = true;
 }
 
-// z = M^{-1} v and w = J~ z (FP64).  In PF order with the red-black ILU(0)
-// smoother (cpr_colour_split) v, z and w are in the colour-split layout and
-// the product rides on the last ILU phase (k_ilu_red_spmv, k_black_spmv);
-// otherwise, in natural order, cpr_apply and the plain product.
+void launch_pc_map_cs(Sim& s) {
+    launch<F_k_pc_map_cs>(s, s.stream, k_pc_map_cs, dim3(grid_for(2 * ilu_slot_count(s.m))), dim3(kBlock), 0, s.m,
+                          s.pc_map, s.pc_map_cs);
+    PF_LAUNCH_CHECK();
+}
+
+// z = M^{-1} v and w = J~ z (FP64), natural layout.
 void cpr_apply_spmv(Sim& s, const double* v, double* z, double* w) {
+    cpr_apply(s, v, z);
+    launch_spmv(s, z, w);
+}
+
+// The same in the colour-split layout (PF order, red-black ILU(0)); of w the
+// black rows and the wells: the red rows are those of v.
+void cpr_apply_spmv(Sim& s, const CsVec& v, double* z, double* w) {
     const DevModel& m = s.m;
-    if (!cpr_colour_split(s)) {
-        cpr_apply(s, v, z);
-        launch_spmv(s, z, w);
-        return;
-    }
-    const double* p = pressure_stage<double>(s, v, 1);
-    const int64_t ns = ilu_slot_count(m);
+    const double* p = pressure_cycles<double>(s, nullptr, &v);
+    const int ncb = (int)grid_for(ilu_slot_count(m));
     {
         ProfScope ps(s, PF_K_STAGE_RESID);
-        launch<F_k_stage_red>(s, s.stream, k_stage_red, dim3(grid_for(ns)), dim3(kBlock), 0, m, (const double*)s.Lc,
-                              (const double*)s.Jdc, (const double*)s.Dinv, v, p, s.pb, s.B, s.pc_map, s.pc_first,
-                              s.perf_well, z);
+        launch<F_k_stage_red>(s, s.stream, k_stage_red, dim3(ncb), dim3(kBlock), 0, m, s.Lc, s.Dinv, v, p, s.pb, s.B,
+                              s.pc_map_cs, s.pc_first, s.perf_well, z);
         PF_LAUNCH_CHECK();
     }
     {
         ProfScope ps(s, PF_K_ILU);
-        launch<F_k_ilu_black_stage>(s, s.stream, k_ilu_black_stage, dim3(grid_for(ns)), dim3(kBlock), 0, m,
-                                    (const double*)s.Lc, (const double*)s.Jdc, (const double*)s.Dinv, v, p, s.pb, s.B,
-                                    s.pc_map, s.pc_first, s.perf_well, z);
+        launch<F_k_ilu_black_stage>(s, s.stream, k_ilu_black_stage, dim3(ncb), dim3(kBlock), 0, m, s.Lc, s.Jdc,
+                                    s.Dinv, v, p, s.pb, s.B, s.pc_map_cs, s.pc_first, s.perf_well, z);
         PF_LAUNCH_CHECK();
     }
     {
         ProfScope ps(s, PF_K_RED_SPMV);
-        launch<F_k_ilu_red_spmv>(s, s.stream, k_ilu_red_spmv, dim3(grid_for(ns)), dim3(kBlock), 0, m,
-                                 (const double*)s.Lc, (const double*)s.Dinv, v, p, z, w);
+        launch<F_k_ilu_red_spmv>(s, s.stream, k_ilu_red_spmv, dim3(ncb), dim3(kBlock), 0, m, s.Lc, s.Dinv, v, s.pb,
+                                 s.B, s.pc_map_cs, s.pc_first, s.perf_well, z);
         PF_LAUNCH_CHECK();
     }
     {
         ProfScope ps(s, PF_K_BLACK_SPMV);
-        launch<F_k_black_spmv>(s, s.stream, k_black_spmv, dim3(grid_for(ns + m.nw)), dim3(kBlock), 0, m,
-                               (const double*)s.Lc, (const double*)s.Jdc, p, s.pb, z, w);
+        launch<F_k_black_spmv>(s, s.stream, k_black_spmv, dim3(ncb + m.nw), dim3(kBlock), 0, m, s.Lc, s.Jdc, s.pb, s.B,
+                               s.pc_map_cs, s.pc_first, s.perf_well, s.perf_cell, s.wp_first, s.wp_idx, s.Cw, s.Dw,
+                               ncb, z, w);
         PF_LAUNCH_CHECK();
     }
-    launch_spmv_border(s, z, w, 2);     // black rows and wells: the red rows are complete
 }
 
 // Mixed precision: FP32 multigrid and stage residual, BF16/FP32 smoother,

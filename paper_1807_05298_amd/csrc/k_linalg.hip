@@ -79,15 +79,12 @@ __device__ __forceinline__ void k_spmv_border_d(const Blk& wg, DevModel m, int n
                                                 const int32_t* __restrict__ wp_first,
                                                 const int32_t* __restrict__ wp_idx, const double* __restrict__ B,
                                                 const double* __restrict__ Cw, const double* __restrict__ Dw,
-                                                const TX* __restrict__ x, double* __restrict__ y, int cs) {
-    // plane length and a cell's offset in the natural (cs 0) or the colour-split
-    // layout (cs 1; cs 2: the cell rows of black cells only, the wells' rows all)
-    const int64_t n = cs ? 2 * cs_ns(m) : m.n;
+                                                const TX* __restrict__ x, double* __restrict__ y) {
+    const int64_t n = m.n;
     if ((int)wg.x < ncb) {
         const int64_t t = (int64_t)wg.x * blockDim.x + threadIdx.x;
         if (t >= m.npc) return;
-        const int64_t i = cs ? cs_index(m, pc_cell[t]) : pc_cell[t];
-        if (cs == 2 && i < cs_ns(m)) return;             // red rows left as they are
+        const int64_t i = pc_cell[t];
         double a0 = 0.0, a1 = 0.0, a2 = 0.0;
         for (int64_t k = pc_first[t]; k < pc_first[t + 1]; ++k) {
             const double pb = (double)x[3 * n + perf_well[k]];
@@ -104,7 +101,7 @@ __device__ __forceinline__ void k_spmv_border_d(const Blk& wg, DevModel m, int n
     double s = 0.0;
     for (int k = wp_first[w] + (int)threadIdx.x; k < wp_first[w + 1]; k += 64) {
         const int p = wp_idx[k];
-        const int64_t c = cs ? cs_index(m, perf_cell[p]) : perf_cell[p];
+        const int64_t c = perf_cell[p];
         s += Cw[3 * p] * (double)x[c] + Cw[3 * p + 1] * (double)x[n + c] + Cw[3 * p + 2] * (double)x[2 * n + c];
     }
     for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
@@ -118,9 +115,8 @@ __global__ __launch_bounds__(64) void k_spmv_border(DevModel m, int ncb, const i
                                                     const int32_t* __restrict__ wp_first,
                                                     const int32_t* __restrict__ wp_idx, const double* __restrict__ B,
                                                     const double* __restrict__ Cw, const double* __restrict__ Dw,
-                                                    const TX* __restrict__ x, double* __restrict__ y, int cs) {
-    k_spmv_border_d<TX>(PF_BLK, m, ncb, pc_cell, pc_first, perf_well, perf_cell, wp_first, wp_idx, B, Cw, Dw, x, y,
-                        cs);
+                                                    const TX* __restrict__ x, double* __restrict__ y) {
+    k_spmv_border_d<TX>(PF_BLK, m, ncb, pc_cell, pc_first, perf_well, perf_cell, wp_first, wp_idx, B, Cw, Dw, x, y);
 }
 template <class TX>
 struct F_k_spmv_border {
@@ -135,13 +131,12 @@ struct F_k_spmv_border {
 // back; wells copied.
 __device__ __forceinline__ void k_to_cs_d(const Blk& wg, DevModel m, const double* __restrict__ x,
                                           double* __restrict__ y, double scale) {
-    const int64_t ns = cs_ns(m), lp = 2 * ns;
+    const int64_t ns = cs_ns(m);
     const int64_t q = (int64_t)wg.x * blockDim.x + threadIdx.x;
-    if (q >= 3 * lp + m.nw) return;
-    if (q >= 3 * lp) { y[q] = scale * x[3 * m.n + (q - 3 * lp)]; return; }
-    const int64_t e = q / lp, r = q - e * lp;
-    const int c = r >= ns ? 1 : 0;
-    const int64_t sl = r - c * ns;
+    if (q >= 6 * ns + m.nw) return;
+    if (q >= 6 * ns) { y[q] = scale * x[3 * m.n + (q - 6 * ns)]; return; }
+    const int c = q >= 3 * ns ? 1 : 0;
+    const int64_t r = q - c * 3 * ns, e = r / ns, sl = r - e * ns;
     const int64_t hx = (m.nx + 1) >> 1;
     const int64_t line = sl / hx, t = sl - line * hx;
     const int64_t iz = line / m.ny, iy = line - iz * m.ny;
@@ -161,12 +156,12 @@ struct F_k_to_cs {
 
 __device__ __forceinline__ void k_from_cs_d(const Blk& wg, DevModel m, const double* __restrict__ x,
                                             double* __restrict__ y) {
-    const int64_t lp = 2 * cs_ns(m);
+    const int64_t ns = cs_ns(m);
     const int64_t q = (int64_t)wg.x * blockDim.x + threadIdx.x;
     if (q >= 3 * m.n + m.nw) return;
-    if (q >= 3 * m.n) { y[q] = x[3 * lp + (q - 3 * m.n)]; return; }
+    if (q >= 3 * m.n) { y[q] = x[6 * ns + (q - 3 * m.n)]; return; }
     const int64_t e = q / m.n, i = q - e * m.n;
-    y[q] = x[e * lp + cs_index(m, i)];
+    y[q] = x[e * ns + cs_index(m, i)];
 }
 __global__ void k_from_cs(DevModel m, const double* __restrict__ x, double* __restrict__ y) {
     k_from_cs_d(PF_BLK, m, x, y);
@@ -383,28 +378,44 @@ __device__ __forceinline__ double block_sum_fixed(double v, double* lds) {
 
 // One block per dot product: folds the partials.  mode 0: first CGS pass
 // (H(:,j) = h, slot nk holds |w|^2 -> wnorm0); mode 1: second pass (gated;
-// H(:,j) += h); mode 2: initial norm of a cycle (slot 0 only -> beta).
+// H(:,j) += h); mode 2: initial norm of a cycle (slot 0, plus slot 1 for the
+// red part u when red -> beta, gram).  In a colour-split solve the partials
+// cover the black cells and wells; the red parts are multiples of u (w's is
+// that of V[j] in the first pass: the red rows of J M^{-1} v are v), so their
+// share of a product is the product of the multiples and gram.  (On 300^3 the
+// update of a tenth column takes 755 us for 1599 over whole vectors.)
 __device__ __forceinline__ void k_dot_finish_d(const Blk& wg, int nk, int G, const double* __restrict__ part,
-                                               KrylovCtl* __restrict__ kc, int j, int mode, int first) {
+                                               KrylovCtl* __restrict__ kc, int j, int mode, int first, int red) {
     if (mode == 1 && kc->reorth == 0) return;
     __shared__ double lds[16];
     const int k = wg.x;
     double a = 0.0;
     for (int b = threadIdx.x; b < G; b += blockDim.x) a += part[(int64_t)k * G + b];
-    const double v = block_sum_fixed(a, lds);
+    const double vb = block_sum_fixed(a, lds);
+    double vr = 0.0;
+    if (mode == 2 && red) {
+        a = 0.0;
+        for (int b = threadIdx.x; b < G; b += blockDim.x) a += part[G + b];
+        __syncthreads();                 // block_sum_fixed is done with lds
+        vr = block_sum_fixed(a, lds);
+    }
     if (threadIdx.x != 0) return;
     constexpr int ld = kMaxRestart + 1;
     if (mode == 2) {
-        const double beta = sqrt(v);
+        const double beta = sqrt(vb + vr);
+        kc->gram = vr;
         kc->beta = beta;
         if (first) kc->beta0 = beta;
         for (int q = 0; q <= kMaxRestart; ++q) kc->g[q] = 0.0;
         kc->g[0] = beta;
         kc->inv_h = (beta > 0.0 && beta <= DBL_MAX) ? 1.0 / beta : 0.0;
+        kc->alpha[0] = vr > 0.0 ? kc->inv_h : 0.0;
         kc->rel = (kc->beta0 > 0.0) ? beta / kc->beta0 : 0.0;
         kc->breakdown = !(beta > 0.0 && beta <= DBL_MAX);
         return;
     }
+    const double aw = kc->alpha[mode == 0 ? j : j + 1];
+    const double v = vb + aw * ((k < nk ? kc->alpha[k] : aw) * kc->gram);
     if (k < nk) {
         kc->h[k] = v;
         if (mode == 0) kc->H[j * ld + k] = v;
@@ -414,8 +425,8 @@ __device__ __forceinline__ void k_dot_finish_d(const Blk& wg, int nk, int G, con
     }
 }
 __global__ __launch_bounds__(256) void k_dot_finish(int nk, int G, const double* __restrict__ part,
-                                                    KrylovCtl* __restrict__ kc, int j, int mode, int first) {
-    k_dot_finish_d(PF_BLK, nk, G, part, kc, j, mode, first);
+                                                    KrylovCtl* __restrict__ kc, int j, int mode, int first, int red) {
+    k_dot_finish_d(PF_BLK, nk, G, part, kc, j, mode, first, red);
 }
 struct F_k_dot_finish {
     static constexpr int kLB = 256;
@@ -519,11 +530,16 @@ __device__ __forceinline__ void k_arnoldi_close_d(const Blk& wg, int G, const do
     for (int b = threadIdx.x; b < G; b += blockDim.x) a += part[b];
     const double ss = block_sum_fixed(a, lds);
     if (threadIdx.x != 0) return;
-    const double wm = sqrt(ss);          // norm of w as stored
+    // w's multiple of u after this pass
+    const double sc = stage == 0 && fuse ? fused_scale(kc, j + 1) : 0.0;
+    double aw = kc->alpha[stage == 0 ? j : j + 1];
+    for (int k = 0; k <= j; ++k) aw -= kc->h[k] * kc->alpha[k];
+    if (sc > 0.0) aw *= sc;
+    kc->alpha[j + 1] = aw;
+    const double wm = sqrt(ss + aw * (aw * kc->gram));     // norm of w as stored
     double wn = wm;                      // h(j+1, j)
     kc->normalised = 0;
     if (stage == 0) {
-        const double sc = fuse ? fused_scale(kc, j + 1) : 0.0;
         if (sc > 0.0) {
             // w holds (w - V h) * sc: no second pass by construction
             kc->reorth = 0;
@@ -583,16 +599,17 @@ struct F_k_arnoldi_close {
     }
 };
 
-// out = v * kc->inv_h  (in place allowed)
+// out = v * kc->inv_h  (in place allowed); ja >= 0: and alpha[ja] with it
 __device__ __forceinline__ void k_scale_ctl_d(const Blk& wg, int64_t n, const double* __restrict__ v,
-                                              double* __restrict__ out, const KrylovCtl* __restrict__ kc) {
+                                              double* __restrict__ out, KrylovCtl* __restrict__ kc, int ja) {
     const double s = kc->inv_h;
+    if (ja >= 0 && wg.x == 0 && threadIdx.x == 0) kc->alpha[ja] *= s;
     for (int64_t i = (int64_t)wg.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)wg.n * blockDim.x)
         out[i] = v[i] * s;
 }
 __global__ void k_scale_ctl(int64_t n, const double* __restrict__ v, double* __restrict__ out,
-                            const KrylovCtl* __restrict__ kc) {
-    k_scale_ctl_d(PF_BLK, n, v, out, kc);
+                            KrylovCtl* __restrict__ kc, int ja) {
+    k_scale_ctl_d(PF_BLK, n, v, out, kc, ja);
 }
 struct F_k_scale_ctl {
     static constexpr int kLB = 1024;
@@ -659,13 +676,12 @@ unsigned stream_grid(int64_t n) {
 
 namespace {
 template <class TX>
-void spmv_border_t(Sim& s, const TX* x, double* y, int cs = 0) {
+void spmv_border_t(Sim& s, const TX* x, double* y) {
     const DevModel& m = s.m;
     const int ncb = (int)((m.npc + 63) / 64);
     if (ncb + m.nw > 0) {
         launch<F_k_spmv_border<TX>>(s, s.stream, k_spmv_border<TX>, dim3(ncb + m.nw), dim3(64), 0, m, ncb, s.pc_cell,
-                                    s.pc_first, s.perf_well, s.perf_cell, s.wp_first, s.wp_idx, s.B, s.Cw, s.Dw, x, y,
-                                    cs);
+                                    s.pc_first, s.perf_well, s.perf_cell, s.wp_first, s.wp_idx, s.B, s.Cw, s.Dw, x, y);
         PF_LAUNCH_CHECK();
     }
 }
@@ -681,8 +697,6 @@ void spmv_t(Sim& s, const TX* x, double* y) {
     spmv_border_t<TX>(s, x, y);
 }
 }  // namespace
-
-void launch_spmv_border(Sim& s, const double* x, double* y, int cs) { spmv_border_t<double>(s, x, y, cs); }
 
 void launch_to_cs(Sim& s, const double* x, double* y, double scale) {
     launch<F_k_to_cs>(s, s.stream, k_to_cs, dim3(grid_for(s.nvc)), dim3(kBlock), 0, s.m, x, y, scale);
@@ -730,14 +744,22 @@ void launch_bjac_apply(Sim& s, const double* r, double* z) {
 void launch_norm_to_ctl(Sim& s, const double* v, int first) {
     const int G = kRedBlocks;
     launch<F_k_mdot<1, false>>(s, s.stream, k_mdot<1, false>, dim3(G), dim3(kBlock), 0, s.nk, 0, 0,
-                               (const double*)nullptr, (int64_t)0, v, s.part, s.kc, 0, 1);
+                               (const double*)nullptr, (int64_t)0, v + s.ko, s.part, s.kc, 0, 1);
     PF_LAUNCH_CHECK();
-    launch<F_k_dot_finish>(s, s.stream, k_dot_finish, dim3(1), dim3(kBlock), 0, 0, G, s.part, s.kc, 0, 2, first);
+    if (s.ko > 0) {
+        // the red part of a colour-split vector
+        launch<F_k_mdot<1, false>>(s, s.stream, k_mdot<1, false>, dim3(G), dim3(kBlock), 0, s.ko, 0, 0,
+                                   (const double*)nullptr, (int64_t)0, v, s.part + G, s.kc, 0, 1);
+        PF_LAUNCH_CHECK();
+    }
+    launch<F_k_dot_finish>(s, s.stream, k_dot_finish, dim3(1), dim3(kBlock), 0, 0, G, s.part, s.kc, 0, 2, first,
+                           (int)(s.ko > 0));
     PF_LAUNCH_CHECK();
 }
 
 void launch_scale_by_ctl(Sim& s, const double* v, double* out, int /*which*/) {
-    launch<F_k_scale_ctl>(s, s.stream, k_scale_ctl, dim3(stream_grid(s.nk)), dim3(kBlock), 0, s.nk, v, out, s.kc);
+    launch<F_k_scale_ctl>(s, s.stream, k_scale_ctl, dim3(stream_grid(s.nk)), dim3(kBlock), 0, s.nk, v + s.ko,
+                          out + s.ko, s.kc, -1);
     PF_LAUNCH_CHECK();
 }
 
@@ -746,7 +768,7 @@ namespace {
 template <int KN>
 void mdot_launch(Sim& s, int nk, int k0, const double* w, int gated) {
     launch<F_k_mdot<KN, false>>(s, s.stream, k_mdot<KN, false>, dim3(kRedBlocks), dim3(kBlock), 0, s.nk, nk, k0,
-                                s.V, s.kst, w, s.part, s.kc, gated, KN);
+                                s.V + s.ko, s.kst, w + s.ko, s.part, s.kc, gated, KN);
     PF_LAUNCH_CHECK();
 }
 
@@ -758,7 +780,7 @@ void mdot_all(Sim& s, int nk, int nslots, const double* w, int gated) {
             // in a fusion group one kernel for every chunk size, so that
             // members at different iterations share launches
             launch<F_k_mdot<kDotChunk, true>>(s, s.stream, k_mdot<kDotChunk, true>, dim3(kRedBlocks), dim3(kBlock),
-                                              0, s.nk, nk, k0, s.V, s.kst, w, s.part, s.kc, gated, kn);
+                                              0, s.nk, nk, k0, s.V + s.ko, s.kst, w + s.ko, s.part, s.kc, gated, kn);
             continue;
         }
         switch (kn) {
@@ -772,8 +794,8 @@ void mdot_all(Sim& s, int nk, int nslots, const double* w, int gated) {
 
 template <int KN>
 void mupdate_launch(Sim& s, int nk, double* w, int gated, int fuse) {
-    launch<F_k_mupdate<KN>>(s, s.stream, k_mupdate<KN>, dim3(kRedBlocks), dim3(kBlock), 0, s.nk, nk, s.V, s.kst, w,
-                            s.part, s.kc, gated, fuse);
+    launch<F_k_mupdate<KN>>(s, s.stream, k_mupdate<KN>, dim3(kRedBlocks), dim3(kBlock), 0, s.nk, nk, s.V + s.ko, s.kst,
+                            w + s.ko, s.part, s.kc, gated, fuse);
     PF_LAUNCH_CHECK();
 }
 
@@ -809,7 +831,7 @@ void launch_arnoldi(Sim& s, int j, double* w) {
         ProfScope ps(s, PF_K_MDOT);
         mdot_all(s, nk, nk + 1, w, 0);
     }
-    launch<F_k_dot_finish>(s, s.stream, k_dot_finish, dim3(nk + 1), dim3(kBlock), 0, nk, G, s.part, s.kc, j, 0, 0);
+    launch<F_k_dot_finish>(s, s.stream, k_dot_finish, dim3(nk + 1), dim3(kBlock), 0, nk, G, s.part, s.kc, j, 0, 0, 0);
     PF_LAUNCH_CHECK();
     {
         ProfScope ps(s, PF_K_MUPDATE);
@@ -828,7 +850,7 @@ void launch_arnoldi_second(Sim& s, int j, double* w) {
     const int nk = j + 1;
     const int always = s.opts.reorth ? 1 : 0;
     mdot_all(s, nk, nk, w, 1);
-    launch<F_k_dot_finish>(s, s.stream, k_dot_finish, dim3(nk), dim3(kBlock), 0, nk, G, s.part, s.kc, j, 1, 0);
+    launch<F_k_dot_finish>(s, s.stream, k_dot_finish, dim3(nk), dim3(kBlock), 0, nk, G, s.part, s.kc, j, 1, 0, 0);
     PF_LAUNCH_CHECK();
     mupdate_any(s, nk, w, 1, 0);
     launch<F_k_arnoldi_close>(s, s.stream, k_arnoldi_close, dim3(1), dim3(kBlock), 0, G, s.part, s.kc, j, 1, always,
@@ -836,8 +858,9 @@ void launch_arnoldi_second(Sim& s, int j, double* w) {
     PF_LAUNCH_CHECK();
 }
 
-void launch_normalise(Sim& s, double* w) {
-    launch<F_k_scale_ctl>(s, s.stream, k_scale_ctl, dim3(stream_grid(s.nk)), dim3(kBlock), 0, s.nk, w, w, s.kc);
+void launch_normalise(Sim& s, int j, double* w) {
+    launch<F_k_scale_ctl>(s, s.stream, k_scale_ctl, dim3(stream_grid(s.nk)), dim3(kBlock), 0, s.nk, w + s.ko,
+                          w + s.ko, s.kc, j + 1);
     PF_LAUNCH_CHECK();
 }
 
@@ -848,10 +871,10 @@ void launch_solve_small(Sim& s, int k) {
 
 void launch_zcomb(Sim& s, int k, double* dx, bool first) {
     if (s.opts.precision == PF_PREC_MIXED)
-        launch<F_k_zcomb<float>>(s, s.stream, k_zcomb<float>, dim3(stream_grid(s.nk)), dim3(kBlock), 0, s.nk, k,
+        launch<F_k_zcomb<float>>(s, s.stream, k_zcomb<float>, dim3(stream_grid(s.nx)), dim3(kBlock), 0, s.nx, k,
                                  s.Z32, s.kst, s.kc, dx, (int)first);
     else
-        launch<F_k_zcomb<double>>(s, s.stream, k_zcomb<double>, dim3(stream_grid(s.nk)), dim3(kBlock), 0, s.nk, k,
+        launch<F_k_zcomb<double>>(s, s.stream, k_zcomb<double>, dim3(stream_grid(s.nx)), dim3(kBlock), 0, s.nx, k,
                                   s.Z, s.kst, s.kc, dx, (int)first);
     PF_LAUNCH_CHECK();
 }

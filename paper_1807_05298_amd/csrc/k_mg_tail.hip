@@ -53,17 +53,22 @@ struct TailLevel {
 template <class T> struct Tail {
     int nl;                          // smoothed levels
     int cycles;                      // V-cycles (more than one only when the first level is the finest)
-    int cs;                          // layout of v: 0 natural, 1 colour-split
     int nc, cnx, cny;                // coarsest level: cells, row and layer lengths
     int xo, bo, po, fb;              // LDS offsets: its x, b and partial sums; the first level's b
     TailLevel lv[kTailLevels];
     const T* A[kTailLevels];
     const T* aux[kTailLevels];
     const T* inv;                    // coarsest inverse, transposed, zero rows up to a multiple of kTailPad
-    const T* b;                      // right-hand side of the first level (null: formed from v)
-    const double* v;                 // the residual whose water and oil rows sum to it
+    const T* b;                      // right-hand side of the first level (null: formed from v or cv)
+    const double* v;                 // the residual whose water and oil rows sum to it, natural layout ...
+    CsVec cv;                        // ... or (v null) colour-split
     T* x;                            // out: the first level's correction with the coarser ones added (p null)
-    T* p;                            // out: the same in natural cell order
+    T* p;                            // out: the same in natural cell order, or (cv) on the black cells
+    // cv: the wells, whose pressures follow from their rows
+    int nw;
+    const int32_t *wp_first, *wp_idx, *perf_cell;
+    const double *Cw, *Dw, *vw;
+    double* pb;
 };
 
 // Lane i takes lane i - D (UP) or i + D of its row of 16 (DPP), 0 where there
@@ -271,8 +276,7 @@ __device__ __forceinline__ void tail_level(const Tail<T>& t, int l, int tid, T* 
     __syncthreads();
 }
 
-// x_l += P x_{l+1}; out: written to the result instead.  A barrier precedes
-// and (except after out) follows.
+// x_l += P x_{l+1}; out: also the result.  A barrier precedes and follows.
 template <class T, int LM>
 __device__ __forceinline__ void tail_upward(const Tail<T>& t, int l, int tid, T* lds, bool out) {
     const TailLevel g = t.lv[l];
@@ -295,21 +299,21 @@ __device__ __forceinline__ void tail_upward(const Tail<T>& t, int l, int tid, T*
                 val[q][j] = lds[g.xo + it.i0[q] + it.step(q, j)] + lds[j < it.len[q] ? base + Z * layer : xo];
             }
         }
-        T* dst = t.p ? t.p : t.x;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int ix = 2 * it.ixh + ((it.iy + q) & 1);
-            const int i0 = out && t.p ? ix + g.nx * (it.iy + g.ny * it.k0) : it.i0[q];
-            const int step = out && t.p ? g.nx * g.ny : it.cols;
 #pragma unroll
             for (int j = 0; j < LM; ++j)
                 if (j < it.len[q]) {
-                    if (out) dst[i0 + j * step] = val[q][j];
-                    else lds[g.xo + i0 + j * step] = val[q][j];
+                    const int i = it.i0[q] + j * it.cols, iz = it.k0 + j;
+                    if (!out || t.cv.b) lds[g.xo + i] = val[q][j];
+                    if (out && !t.p) t.x[i] = val[q][j];
+                    else if (out && !t.cv.b) t.p[ix + g.nx * (it.iy + g.ny * iz)] = val[q][j];
+                    else if (out && ((q + iz) & 1)) t.p[i - q * g.half] = val[q][j];      // a black cell's slot
                 }
         }
     }
-    if (!out) __syncthreads();
+    __syncthreads();
 }
 
 // Copies count elements to LDS without passing through registers: 16 bytes a
@@ -361,12 +365,16 @@ __device__ __forceinline__ void k_mg_tail_d(const Blk&, const Tail<T>& t) {
         tail_stage<T>(t.b, lds + t.fb, 2 * g0.half, tid);
     } else {
         // it is the finest: b = water + oil rows of v
-        const int layer = g0.nx * g0.ny, pl = t.cs ? 2 * g0.half : layer * g0.nz;
-        for (int i = tid; i < layer * g0.nz; i += kTailThreads) {
+        const int layer = g0.nx * g0.ny, cells = layer * g0.nz, ns = g0.half;
+        const double al = t.v ? 0.0 : *t.cv.alpha;
+        for (int i = tid; i < cells; i += kTailThreads) {
             const int iz = i / layer, rem = i - iz * layer, iy = rem / g0.nx, ix = rem - iy * g0.nx;
             const int sl = (iz * g0.ny + iy) * g0.hx + (ix >> 1);
-            const int vi = t.cs ? ((ix + iy + iz) & 1) * g0.half + sl : i;
-            lds[t.fb + ((ix + iy) & 1) * g0.half + sl] = (T)(t.v[vi] + t.v[pl + vi]);
+            double r;
+            if (t.v) r = t.v[i] + t.v[cells + i];
+            else if ((ix + iy + iz) & 1) r = t.cv.b[sl] + t.cv.b[ns + sl];
+            else r = al * (t.cv.u[sl] + t.cv.u[ns + sl]);
+            lds[t.fb + ((ix + iy) & 1) * g0.half + sl] = (T)r;
         }
     }
     // thread (q, r) takes its share of row r of the dense coarsest inverse
@@ -422,6 +430,19 @@ __device__ __forceinline__ void k_mg_tail_d(const Blk&, const Tail<T>& t) {
             const bool out = l == 0 && cyc + 1 == t.cycles;
             if (t.lv[l].len <= 2) tail_upward<T, 2>(t, l, tid, lds, out);
             else tail_upward<T, kTailLen>(t, l, tid, lds, out);
+        }
+    }
+    if (t.p && t.cv.b) {
+        // pb_w = (v_w - sum_perf dW/dP * p_cell) / D_w, a wavefront per well
+        for (int w = tid >> 6; w < t.nw; w += kTailThreads / 64) {
+            double s = 0.0;
+            for (int k = t.wp_first[w] + (tid & 63); k < t.wp_first[w + 1]; k += 64) {
+                const int f = t.wp_idx[k], c = t.perf_cell[f], row = c / g0.nx, ix = c - row * g0.nx;
+                const int iy = row % g0.ny;
+                s += t.Cw[3 * f] * (double)lds[g0.xo + ((ix + iy) & 1) * g0.half + row * g0.hx + (ix >> 1)];
+            }
+            for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+            if ((tid & 63) == 0) t.pb[w] = (t.vw[w] - s) / t.Dw[w];
         }
     }
 }
@@ -515,7 +536,7 @@ int tail_first(const Sim& s) {
 }
 
 template <class T>
-void tail_launch(Sim& s, int l0, int cycles, const double* v, int cs, T* p) {
+void tail_launch(Sim& s, int l0, int cycles, const double* v, const CsVec* cv, T* p) {
     Tail<T> t{};
     const size_t shm = tail_plan<T>(s, l0, t);
     for (int l = 0; l < t.nl; ++l) {
@@ -523,10 +544,17 @@ void tail_launch(Sim& s, int l0, int cycles, const double* v, int cs, T* p) {
         t.aux[l] = lvAux<T>(s.mg[l0 + l]);
     }
     t.cycles = cycles;
-    t.cs = cs;
     t.inv = coarseInv<T>(s);
-    t.b = v ? nullptr : lvB<T>(s.mg[l0]);
+    t.b = v || cv ? nullptr : lvB<T>(s.mg[l0]);
     t.v = v;
+    if (cv) {
+        t.cv = *cv;
+        t.nw = s.m.nw;
+        t.wp_first = s.wp_first; t.wp_idx = s.wp_idx; t.perf_cell = s.perf_cell;
+        t.Cw = s.Cw; t.Dw = s.Dw;
+        t.vw = cv->b + 3 * cs_ns(s.m);
+        t.pb = s.pb;
+    }
     t.x = lvX<T>(s.mg[l0]);
     t.p = p;
     launch<F_k_mg_tail<T>>(s, s.stream, k_mg_tail<T>, dim3(1), dim3(kTailThreads), shm, t);
@@ -539,11 +567,11 @@ int mg_tail_first(const Sim& s) {
     return s.opts.precision == PF_PREC_MIXED ? tail_first<float>(s) : tail_first<double>(s);
 }
 
-void launch_mg_tail(Sim& s, int l0, int cycles, const double* v, int cs, double* p) {
-    tail_launch<double>(s, l0, cycles, v, cs, p);
+void launch_mg_tail(Sim& s, int l0, int cycles, const double* v, const CsVec* cv, double* p) {
+    tail_launch<double>(s, l0, cycles, v, cv, p);
 }
-void launch_mg_tail(Sim& s, int l0, int cycles, const double* v, int cs, float* p) {
-    tail_launch<float>(s, l0, cycles, v, cs, p);
+void launch_mg_tail(Sim& s, int l0, int cycles, const double* v, const CsVec* cv, float* p) {
+    tail_launch<float>(s, l0, cycles, v, cv, p);
 }
 
 }  // namespace pf

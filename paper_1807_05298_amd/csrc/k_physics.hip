@@ -817,15 +817,14 @@ struct F_k_norm_finish {
 
 // Chopped Newton update of the cells (|dS| <= ds_max, C >= 0) with partial
 // maxima of the applied change in scaled units.
-// dx in the natural (cs 0) or the solver's colour-split layout (cs 1: planes
-// of 2 cs_ns slots, the wells after the three planes)
+// dx in the natural (cs 0) or the solver's colour-split layout (cs 1)
 __device__ __forceinline__ void k_update_part_d(const Blk& wg, DevModel m, double ds_max,
                                                 const double* __restrict__ dx, double* __restrict__ x,
                                                 double* __restrict__ part, int cs) {
     __shared__ double lds[3 * 16];
     double acc[3] = {0.0, 0.0, 0.0};
     const bool mx[3] = {true, true, true};
-    const int64_t n = m.n, lp = cs ? 2 * cs_ns(m) : n;
+    const int64_t n = m.n, lp = cs ? cs_ns(m) : n;
     for (int64_t i = (int64_t)wg.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)wg.n * blockDim.x) {
         const int64_t j = cs ? cs_index(m, i) : i;
@@ -869,7 +868,7 @@ __device__ __forceinline__ void k_update_finish_d(const Blk& wg, DevModel m, int
     if (threadIdx.x == 0) {
         double wm = 0.0;
         for (int w = 0; w < m.nw; ++w) {
-            const double d = dx[3 * (cs ? 2 * cs_ns(m) : m.n) + w];
+            const double d = dx[(cs ? 6 * cs_ns(m) : 3 * m.n) + w];
             x[3 * m.n + w] += d;
             wm = fmax(wm, safe_abs(d) / kBar);
         }

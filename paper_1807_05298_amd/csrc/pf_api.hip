@@ -239,7 +239,8 @@ size_t plan(Sim& s, char* base) {
     s.nvc = 6 * cs_ns(m) + m.nw;
     const int64_t kst = fp64 ? std::max(nv, s.nvc) : nv;
     s.kst = kst;
-    s.nk = nv;
+    s.nx = s.nk = nv;
+    s.ko = 0;
     s.V = b.take<double>((size_t)(mcap + 1) * kst);
     if (!fp64) {
         s.Z = nullptr;
@@ -249,6 +250,7 @@ size_t plan(Sim& s, char* base) {
         s.Z32 = nullptr;
     }
     s.t1 = b.take<double>(kst); s.t2 = b.take<double>(kst);
+    s.pc_map_cs = fp64 ? b.take<int32_t>(2 * cs_ns(m)) : nullptr;
     s.bcs = fp64 ? b.take<double>(s.nvc) : nullptr;
     s.xcs = fp64 ? b.take<double>(s.nvc) : nullptr;
     s.w = nullptr;
@@ -357,7 +359,9 @@ bool fgmres_cs(const Sim& s) { return s.Z && cpr_colour_split(s); }
 int fgmres(Sim& s, const double* b_nat, double tol, double* x_nat, double* rel, int max_it, bool in_cs = false) {
     const int m = std::min<int>(s.opts.restart, s.restart_cap);
     const bool cs = fgmres_cs(s);
-    s.nk = cs ? s.nvc : s.nv;
+    s.nx = cs ? s.nvc : s.nv;
+    s.ko = cs ? 3 * cs_ns(s.m) : 0;      // the red parts of the Krylov vectors are multiples of r0's
+    s.nk = s.nx - s.ko;
     const double* b = b_nat;
     double* x = x_nat;
     if (cs) {
@@ -379,11 +383,11 @@ int fgmres(Sim& s, const double* b_nat, double tol, double* x_nat, double* rel, 
                 launch_from_cs(s, x, s.t2);
                 launch_spmv(s, s.t2, s.t1);
                 launch_to_cs(s, s.t1, s.t2);
-                launch_axpby(s, s.nk, 1.0, b, -1.0, s.t2);
+                launch_axpby(s, s.nx, 1.0, b, -1.0, s.t2);
                 r0 = s.t2;
             } else {
                 launch_spmv(s, x, s.t1);
-                launch_axpby(s, s.nk, 1.0, b, -1.0, s.t1);
+                launch_axpby(s, s.nx, 1.0, b, -1.0, s.t1);
                 r0 = s.t1;
             }
         }
@@ -402,6 +406,8 @@ int fgmres(Sim& s, const double* b_nat, double tol, double* x_nat, double* rel, 
                 float* zj = s.Z32 + (int64_t)j * s.kst;
                 cpr_apply(s, vj, zj);
                 launch_spmv(s, zj, w);
+            } else if (cs) {
+                cpr_apply_spmv(s, CsVec{r0, vj + s.ko, s.kc->alpha + j}, s.Z + (int64_t)j * s.kst, w + s.ko);
             } else {
                 cpr_apply_spmv(s, vj, s.Z + (int64_t)j * s.kst, w);
             }
@@ -418,7 +424,7 @@ int fgmres(Sim& s, const double* b_nat, double tol, double* x_nat, double* rel, 
             k = j + 1;
             if (!std::isfinite(r_est)) throw InvalidArg{"non-finite Krylov residual"};
             if (bk || r_est <= tol || total >= max_it) { stop = true; break; }
-            if (!reinterpret_cast<const int32_t*>(s.hbuf + 1)[2]) launch_normalise(s, w);
+            if (!reinterpret_cast<const int32_t*>(s.hbuf + 1)[2]) launch_normalise(s, j, w);
         }
         launch_solve_small(s, k);
         launch_zcomb(s, k, x, !x_set);
@@ -426,9 +432,10 @@ int fgmres(Sim& s, const double* b_nat, double tol, double* x_nat, double* rel, 
         if (stop) break;
         first = false;
     }
-    if (!x_set) launch_fill(s, s.nk, 0.0, x);
+    if (!x_set) launch_fill(s, s.nx, 0.0, x);
     if (cs && !in_cs) launch_from_cs(s, x, x_nat);
-    s.nk = s.nv;
+    s.nx = s.nk = s.nv;
+    s.ko = 0;
     if (rel) *rel = r_est;
     return total;
 }
@@ -726,6 +733,7 @@ static pf_status create_sim(const pf_model_desc* d, const pf_solver_opts* o, voi
         // the (oil, C) entry of every Jacobian block is zero: its seven planes
         // are cleared once here and never written again (the assembly skips them)
         for (int f = 0; f < 7; ++f) launch_fill(s, n, 0.0, s.J + (int64_t)(f * 9 + 5) * n);
+        if (s.pc_map_cs) launch_pc_map_cs(s);
         launch_static(s);
         if (s.m.n_kperm > 0) launch_kperm(s);
         if (s.ads_hist) launch_fill(s, n, 0.0, s.ads_hist);
@@ -1175,7 +1183,10 @@ pf_status pf_precond_apply(pf_sim* h, const double* v, double* z, double* w) {
         // the solver's layout: v in, z and w out through the colour-split one
         upload(s, s.t1, v, s.nv * 8);
         launch_to_cs(s, s.t1, vd);
-        cpr_apply_spmv(s, vd, s.Z, wd);
+        launch_fill(s, 1, 1.0, s.kc->alpha);
+        const int64_t red = 3 * cs_ns(s.m);
+        cpr_apply_spmv(s, CsVec{vd, vd + red, s.kc->alpha}, s.Z, wd + red);
+        launch_copy(s, red, vd, wd);         // the red rows of the product are those of v
         launch_from_cs(s, s.Z, s.t1);
         launch_from_cs(s, wd, s.t2);
         PF_HIP(hipMemcpyAsync(z, s.t1, s.nv * 8, hipMemcpyDeviceToHost, s.stream));

@@ -155,6 +155,10 @@ struct KrylovCtl {
     double g[kMaxRestart + 1];
     double y[kMaxRestart];
     double h[kMaxRestart + 2];       // scratch column of dot products
+    // colour-split solves: the red part of every Krylov vector is a multiple of
+    // the cycle's residual's, V[k]_r = alpha[k] u, and gram = <u, u> (0 otherwise)
+    double alpha[kMaxRestart + 2];
+    double gram;
     double beta0;                    // initial residual norm of this solve
     double beta;                     // residual norm at the start of this cycle
     double wnorm0;                   // |w| before orthogonalisation
@@ -203,6 +207,7 @@ struct Sim {
     double *pvr, *Tx, *Ty, *Tz, *rscale;
     int32_t *perf_cell, *perf_well, *pc_cell, *pc_first, *wp_first, *wp_idx;
     int32_t *pc_map;                 // cell -> index into pc_cell, or -1
+    int32_t *pc_map_cs;              // the same in the colour-split layout (FP64 red-black ILU(0))
     double *perf_wi, *perf_depth;
     int32_t *w_ctrl, *w_inj, *w_dir;
     double *w_target, *w_cinj, *w_gamma, *w_zref, *w_scale, *w_rw, *w_skin;
@@ -218,9 +223,11 @@ struct Sim {
 
     // solver
     double *V, *Z, *w, *t1, *t2;
-    // Krylov vectors: current length nk (nv, or nvc in the colour-split layout)
-    // and the stride kst of the columns of V and Z (max(nv, nvc))
-    int64_t nk = 0, kst = 0, nvc = 0;
+    // Krylov vectors: length nx (nv, or nvc in the colour-split layout) and the
+    // stride kst of the columns of V and Z (max(nv, nvc)); the Arnoldi process
+    // works on nk entries of a column of V from entry ko (all of them, or the
+    // black cells and wells)
+    int64_t nx = 0, nk = 0, ko = 0, kst = 0, nvc = 0;
     double *bcs = nullptr, *xcs = nullptr;   // right-hand side and solution in the colour-split layout
     KrylovCtl* kc;
     double *part;                    // reduction partials
@@ -318,8 +325,6 @@ void launch_equilibrium(Sim& s, double datum_depth, double datum_p, double fwl_d
 // ---- linear algebra (k_linalg.hip) ----------------------------------------
 void launch_spmv(Sim& s, const double* x, double* y);
 void launch_spmv(Sim& s, const float* x, double* y);
-// the well border of y = J x alone; cs: 0 natural layout, 1 colour-split, 2 colour-split black cell rows and wells
-void launch_spmv_border(Sim& s, const double* x, double* y, int cs = 0);
 void launch_to_cs(Sim& s, const double* x, double* y, double scale = 1.0);   // natural -> colour-split, times scale
 void launch_from_cs(Sim& s, const double* x, double* y);          // colour-split -> natural layout
 void launch_axpby(Sim& s, int64_t n, double a, const double* x, double b, double* y);
@@ -337,7 +342,7 @@ void launch_norm_to_ctl(Sim& s, const double* v, int which);      // which 0: be
 void launch_scale_by_ctl(Sim& s, const double* v, double* out, int which);  // which 0: 1/beta, 1: inv_h
 void launch_arnoldi(Sim& s, int j, double* w);                     // first CGS pass of w against V[0..j]
 void launch_arnoldi_second(Sim& s, int j, double* w);              // second pass (when requested)
-void launch_normalise(Sim& s, double* w);                          // w /= h(j+1, j)
+void launch_normalise(Sim& s, int j, double* w);                   // V[j+1] = w / h(j+1, j)
 void launch_solve_small(Sim& s, int k);                             // y = H(0:k,0:k)^{-1} g
 void launch_zcomb(Sim& s, int k, double* dx, bool first = false);   // dx += Z y (first: dx = Z y)
 void launch_init_cycle(Sim& s, int first);
@@ -348,8 +353,15 @@ void cpr_plan(Sim& s, Bump& b);      // workspace of the preconditioner
 void cpr_setup(Sim& s);
 void cpr_apply(Sim& s, const double* v, double* z);
 void cpr_apply(Sim& s, const double* v, float* z);      // mixed precision
-void cpr_apply_spmv(Sim& s, const double* v, double* z, double* w);   // z = M^{-1} v, w = J z
-bool cpr_colour_split(const Sim& s);  // cpr_apply_spmv takes and gives the colour-split layout
+// A vector of the colour-split layout (black cells and wells at b, red cells
+// alpha times u), and z = M^{-1} v with the black rows and wells of w = J z (wb)
+struct CsVec {
+    const double *u, *b, *alpha;
+};
+void cpr_apply_spmv(Sim& s, const CsVec& v, double* z, double* wb);
+void cpr_apply_spmv(Sim& s, const double* v, double* z, double* w);   // natural layout: z = M^{-1} v, w = J z
+void launch_pc_map_cs(Sim& s);        // pc_map_cs from pc_map
+bool cpr_colour_split(const Sim& s);  // the FP64 solve runs in the colour-split layout
 void mg_smooth_once(Sim& s, int level, int colour, int zero_init);   // test hook
 int64_t mg_slot(const MGLevel& L, int ix, int iy, int iz);             // cell -> slot of a level
 int mg_pre_sweeps(const Sim& s, int level);                            // pre-smoothing sweeps of a level
@@ -361,9 +373,10 @@ void smoother_once(Sim& s, const double* f);    // test hook: s.t1 (FP64) / s.Z3
 int mg_tail_first(const Sim& s);
 // cycles V-cycles from that level l0 down; l0 > 0: from the level's right-hand
 // side to its correction with the coarser ones added; l0 == 0: from v (natural
-// layout, or colour-split with cs) to p in natural cell order
-void launch_mg_tail(Sim& s, int l0, int cycles, const double* v, int cs, double* p);
-void launch_mg_tail(Sim& s, int l0, int cycles, const double* v, int cs, float* p);
+// layout) or cv (colour-split) to p, in natural cell order or the black cells
+// alone with the well pressures
+void launch_mg_tail(Sim& s, int l0, int cycles, const double* v, const CsVec* cv, double* p);
+void launch_mg_tail(Sim& s, int l0, int cycles, const double* v, const CsVec* cv, float* p);
 
 // ---- errors -----------------------------------------------------------------
 void set_error(const std::string& msg);
@@ -406,23 +419,24 @@ void copy_h2d(Sim& s, void* dst, const void* src, size_t bytes);
 void copy_d2h(Sim& s, void* dst, const void* src, size_t bytes);
 void stream_sync(Sim& s);
 
-// Colour-split vector layout of the FP64 red-black ILU(0) path (PF order):
-// each of the three planes holds 2 ns entries, the red cells ((ix+iy+iz) even)
-// in slots [0, ns) and the black ones in [ns, 2 ns), both in the slot order
-// of the smoother's colour-split factors (x-lines of ceil(nx/2) slots, lines
-// in natural order; where nx is odd every other line has a pad slot, which
-// holds zero); the wells follow the three planes.  A kernel over the cells
-// of one colour then writes whole cache lines.
+// Colour-split vector layout of the FP64 red-black ILU(0) path (PF order): the
+// three planes (P, S, C) of the red cells ((ix+iy+iz) even), ns entries each,
+// then those of the black cells, both in the slot order of the smoother's
+// colour-split factors (x-lines of ceil(nx/2) slots, lines in natural order;
+// where nx is odd every other line has a pad slot, which holds zero), then the
+// wells.  A kernel over the cells of one colour writes whole cache lines, and
+// the black cells and wells, which is what the Arnoldi process works on, are
+// one run of 3 ns + nw entries.
 __host__ __device__ __forceinline__ int64_t cs_ns(const DevModel& m) {
     return (int64_t)((m.nx + 1) / 2) * m.ny * m.nz;
 }
-// plane offset of the cell with natural index i
+// offset of the P entry of the cell with natural index i (S and C: ns and 2 ns on)
 __device__ __forceinline__ int64_t cs_index(const DevModel& m, int64_t i) {
     const int64_t iz = i / m.nxy;
     const int64_t rem = i - iz * m.nxy;
     const int64_t iy = rem / m.nx;
     const int64_t ix = rem - iy * m.nx;
-    return ((ix + iy + iz) & 1) * cs_ns(m) + (iy + m.ny * iz) * ((m.nx + 1) >> 1) + (ix >> 1);
+    return ((ix + iy + iz) & 1) * 3 * cs_ns(m) + (iy + m.ny * iz) * ((m.nx + 1) >> 1) + (ix >> 1);
 }
 
 // XCD-aware block order: workgroups are dispatched round-robin over the 8
