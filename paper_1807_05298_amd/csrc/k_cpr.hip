@@ -862,7 +862,8 @@ struct F_k_coarse_build {
     }
 };
 
-// Gauss-Jordan with partial pivoting on the augmented matrix, one block.
+// Gauss-Jordan with partial pivoting on the augmented matrix, one block
+// (coarsest levels of more than kCoarseReg cells; the others: k_coarse.hip).
 __device__ __forceinline__ void k_gauss_jordan_d(const Blk& wg, int n, double* __restrict__ M) {
     __shared__ double fcol[1024];
     __shared__ double rv[16];
@@ -922,91 +923,6 @@ struct F_k_gauss_jordan {
     template <class... A>
     __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
         k_gauss_jordan_d(wg, a...);
-    }
-};
-
-
-// Gauss-Jordan with partial pivoting in LDS for n <= kGJLds (augmented n x 2n
-// matrix held in shared memory), result written back to M.
-constexpr int kGJLds = 96;
-__device__ __forceinline__ void k_gauss_jordan_lds_d(const Blk& wg, int n, double* __restrict__ M) {
-    extern __shared__ double sm[];
-    double* S = sm;                       // n x 2n
-    double* fcol = sm + 2 * n * n;        // n
-    __shared__ int piv;
-    const int W = 2 * n;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int lane = tid & 63, wv = tid >> 6, nwv = nt >> 6;
-    for (int idx = tid; idx < n * W; idx += nt) S[idx] = M[idx];
-    __syncthreads();
-    for (int k = 0; k < n; ++k) {
-        // pivot: largest |S[r][k]|, r >= k, by the first wavefront (ties to the lower row)
-        if (wv == 0) {
-            double best = -1.0;
-            int p = k;
-            for (int r = k + lane; r < n; r += 64) {
-                const double v = fabs(S[r * W + k]);
-                if (v > best) { best = v; p = r; }
-            }
-            for (int o = 32; o > 0; o >>= 1) {
-                const double ob = __shfl_down(best, o, 64);
-                const int op = __shfl_down(p, o, 64);
-                if (lane + o < 64 && (ob > best || (ob == best && op < p))) { best = ob; p = op; }
-            }
-            if (lane == 0) piv = p;
-        }
-        __syncthreads();
-        const int p = piv;
-        // Rows k and p (>= k) are zero left of column k, so every row
-        // operation of this step touches columns k .. W-1 only.
-        // read phase: rows k and p (thread per column) and column k (thread per row)
-        const double akk = S[k * W + k];
-        const double inv = 1.0 / S[p * W + k];
-        const int c0 = k + tid;
-        double ak = 0.0, ap = 0.0, fr = 0.0;
-        if (c0 < W) {
-            ak = S[k * W + c0];
-            ap = S[p * W + c0];
-        }
-        if (tid < n) fr = S[tid * W + k];
-        __syncthreads();
-        // write phase: swap rows k and p, scale the new pivot row, multipliers
-        if (c0 < W) {
-            S[p * W + c0] = ak;
-            S[k * W + c0] = ap * inv;
-        }
-        if (tid < n) fcol[tid] = tid == k ? 0.0 : (tid == p ? akk : fr);
-        __syncthreads();
-        // eliminate column k from every other row: wavefront per row, lanes
-        // over columns, the pivot row held in registers
-        double pk[3];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int c = k + lane + 64 * q;
-            pk[q] = c < W ? S[k * W + c] : 0.0;
-        }
-        for (int r = wv; r < n; r += nwv) {
-            const double f = fcol[r];
-            if (f != 0.0) {
-#pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    const int c = k + lane + 64 * q;
-                    if (c < W) S[r * W + c] -= f * pk[q];
-                }
-            }
-        }
-        __syncthreads();
-    }
-    for (int idx = tid; idx < n * W; idx += nt) M[idx] = S[idx];
-}
-__global__ __launch_bounds__(1024) void k_gauss_jordan_lds(int n, double* __restrict__ M) {
-    k_gauss_jordan_lds_d(PF_BLK, n, M);
-}
-struct F_k_gauss_jordan_lds {
-    static constexpr int kLB = 1024;
-    template <class... A>
-    __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
-        k_gauss_jordan_lds_d(wg, a...);
     }
 };
 
@@ -2428,7 +2344,7 @@ void cpr_plan(Sim& s, Bump& b) {
     s.pnat32 = mixed ? b.take<float>(s.m.n) : nullptr;
     s.Ap = s.mg[0].A;
     const int64_t nc = s.mg.back().n;
-    s.coarse_aug = b.take<double>((size_t)nc * 2 * nc);
+    s.coarse_aug = nc > kCoarseReg ? b.take<double>((size_t)nc * 2 * nc) : nullptr;
     s.coarse_inv = b.take<double>((size_t)nc * nc);
     s.coarse_inv_t = b.take<double>((size_t)nc * (nc + kCoarsePad));
     s.pb = b.take<double>(std::max(s.m.nw, 1));
@@ -2472,9 +2388,6 @@ void cpr_setup(Sim& s) {
         PF_LAUNCH_CHECK();
     }
     const MGLevel& Cn = s.mg.back();
-    launch<F_k_coarse_build>(s, s.stream, k_coarse_build, dim3(grid_for(Cn.n, 64)), dim3(64), 0, dims_of(Cn), Cn.A,
-                             s.coarse_aug);
-    PF_LAUNCH_CHECK();
     // the coarsest inverse (one workgroup, latency-bound) runs on the side
     // stream, from as soon as the coarsest operator exists, while the z-line
     // factorisations, the smoother set-up and the first V-cycle's way down
@@ -2486,19 +2399,19 @@ void cpr_setup(Sim& s) {
         PF_HIP(hipEventRecord(s.ev_fork, s.stream));
         PF_HIP(hipStreamWaitEvent(s.aux, s.ev_fork, 0));
     }
-    const size_t lds = (size_t)(2 * Cn.n * Cn.n + Cn.n) * sizeof(double);
-    if (Cn.n <= kGJLds && lds <= (size_t)s.max_lds) {
-        // 256 threads (>= 2n): a workgroup of 1024 waited for a compute unit with 16 free wave slots
-        // while the ILU set-up filled the GPU (300^3: 5.7 ms against 146 us)
-        launch<F_k_gauss_jordan_lds>(s, cs, k_gauss_jordan_lds, dim3(1), dim3(256), lds, (int)Cn.n, s.coarse_aug);
+    if (Cn.n <= kCoarseReg) {
+        launch_coarse_inverse(s, cs);
     } else {
+        launch<F_k_coarse_build>(s, cs, k_coarse_build, dim3(grid_for(Cn.n, 64)), dim3(64), 0, dims_of(Cn), Cn.A,
+                                 s.coarse_aug);
+        PF_LAUNCH_CHECK();
         launch<F_k_gauss_jordan>(s, cs, k_gauss_jordan, dim3(1), dim3(1024), 0, (int)Cn.n, s.coarse_aug);
+        PF_LAUNCH_CHECK();
+        launch<F_k_compact_inv>(s, cs, k_compact_inv, dim3(grid_for(Cn.n * (Cn.n + kCoarsePad))), dim3(kBlock), 0,
+                                (int)Cn.n, s.coarse_aug, s.coarse_inv, s.coarse_inv_t,
+                                mixed ? s.coarse_inv32 : (float*)nullptr, mixed ? s.coarse_inv_t32 : (float*)nullptr);
+        PF_LAUNCH_CHECK();
     }
-    PF_LAUNCH_CHECK();
-    launch<F_k_compact_inv>(s, cs, k_compact_inv, dim3(grid_for(Cn.n * (Cn.n + kCoarsePad))), dim3(kBlock), 0, (int)Cn.n,
-                            s.coarse_aug, s.coarse_inv, s.coarse_inv_t, mixed ? s.coarse_inv32 : (float*)nullptr,
-                            mixed ? s.coarse_inv_t32 : (float*)nullptr);
-    PF_LAUNCH_CHECK();
     if (side) PF_HIP(hipEventRecord(s.ev_join, s.aux));
     for (int l = 0; l + 1 < nl; ++l) {
         const MGLevel& L = s.mg[l];

@@ -26,6 +26,7 @@ constexpr int kBlock = 256;          // threads per block for cell sweeps
 constexpr int kMaxRestart = 64;
 constexpr int kRedBlocks = 1024;     // fixed partial-sum grid of the reductions
 constexpr int kDotChunk = 16;        // dot products per multi-dot launch
+constexpr int kCoarseReg = 96;       // largest coarsest level inverted in registers (k_coarse)
 constexpr int kCoarsePad = 16;       // rows of the transposed coarsest inverse: padded with zeros to a multiple
 constexpr int kPartSlots = kMaxRestart + 2;   // partial-sum slots: restart + 2 dot products
 
@@ -234,7 +235,7 @@ struct Sim {
     double *red;                     // reduction results (64 doubles)
     double *Dinv;                    // block Jacobi: 9N natural; ILU(0): 2 x 9 colour-split planes
     double *Ap;                      // pressure operator (7N) = level 0 of MG
-    double *coarse_aug;              // coarsest-level [A | I] -> [I | A^-1]
+    double *coarse_aug;              // coarsest-level [A | I] -> [I | A^-1] (above kCoarseReg cells)
     double *coarse_inv;              // compact coarsest inverse (n x n)
     float *coarse_inv32;
     double *coarse_inv_t;            // ... and transposed
@@ -377,6 +378,9 @@ int mg_tail_first(const Sim& s);
 // alone with the well pressures
 void launch_mg_tail(Sim& s, int l0, int cycles, const double* v, const CsVec* cv, double* p);
 void launch_mg_tail(Sim& s, int l0, int cycles, const double* v, const CsVec* cv, float* p);
+
+// the coarsest level's dense inverse on stream st (k_coarse.hip; at most kCoarseReg cells)
+void launch_coarse_inverse(Sim& s, hipStream_t st);
 
 // ---- errors -----------------------------------------------------------------
 void set_error(const std::string& msg);
