@@ -174,24 +174,6 @@ struct F_k_from_cs {
     }
 };
 
-// Small device-to-host read-backs of a fusion group: a kernel writes the
-// member's pinned host buffer.
-__device__ __forceinline__ void k_copy_words_d(const Blk& wg, const uint32_t* __restrict__ src,
-                                               uint32_t* __restrict__ dst, int n) {
-    for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x) dst[i] = src[i];
-}
-__global__ __launch_bounds__(64) void k_copy_words(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst,
-                                                   int n) {
-    k_copy_words_d(PF_BLK, src, dst, n);
-}
-struct F_k_copy_words {
-    static constexpr int kLB = 64;
-    template <class... A>
-    __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
-        k_copy_words_d(wg, a...);
-    }
-};
-
 __device__ __forceinline__ void k_axpby_d(const Blk& wg, int64_t n, double a, const double* __restrict__ x, double b,
                                           double* __restrict__ y) {
     for (int64_t i = (int64_t)wg.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)wg.n * blockDim.x)
@@ -376,6 +358,17 @@ __device__ __forceinline__ double block_sum_fixed(double v, double* lds) {
     return r;
 }
 
+// what the host reads of the control block
+__device__ __forceinline__ void post_ctl(const KrylovCtl* kc, const HostPost& p) {
+    if (!p.out) return;
+    p.out[0] = kc->rel;
+    int32_t* q = reinterpret_cast<int32_t*>(p.out + 1);
+    q[0] = kc->reorth;
+    q[1] = kc->breakdown;
+    q[2] = kc->normalised;
+    post_done(p);
+}
+
 // One block per dot product: folds the partials.  mode 0: first CGS pass
 // (H(:,j) = h, slot nk holds |w|^2 -> wnorm0); mode 1: second pass (gated;
 // H(:,j) += h); mode 2: initial norm of a cycle (slot 0, plus slot 1 for the
@@ -385,7 +378,8 @@ __device__ __forceinline__ double block_sum_fixed(double v, double* lds) {
 // share of a product is the product of the multiples and gram.  (On 300^3 the
 // update of a tenth column takes 755 us for 1599 over whole vectors.)
 __device__ __forceinline__ void k_dot_finish_d(const Blk& wg, int nk, int G, const double* __restrict__ part,
-                                               KrylovCtl* __restrict__ kc, int j, int mode, int first, int red) {
+                                               KrylovCtl* __restrict__ kc, int j, int mode, int first, int red,
+                                               HostPost post) {
     if (mode == 1 && kc->reorth == 0) return;
     __shared__ double lds[16];
     const int k = wg.x;
@@ -412,6 +406,7 @@ __device__ __forceinline__ void k_dot_finish_d(const Blk& wg, int nk, int G, con
         kc->alpha[0] = vr > 0.0 ? kc->inv_h : 0.0;
         kc->rel = (kc->beta0 > 0.0) ? beta / kc->beta0 : 0.0;
         kc->breakdown = !(beta > 0.0 && beta <= DBL_MAX);
+        post_ctl(kc, post);
         return;
     }
     const double aw = kc->alpha[mode == 0 ? j : j + 1];
@@ -425,8 +420,9 @@ __device__ __forceinline__ void k_dot_finish_d(const Blk& wg, int nk, int G, con
     }
 }
 __global__ __launch_bounds__(256) void k_dot_finish(int nk, int G, const double* __restrict__ part,
-                                                    KrylovCtl* __restrict__ kc, int j, int mode, int first, int red) {
-    k_dot_finish_d(PF_BLK, nk, G, part, kc, j, mode, first, red);
+                                                    KrylovCtl* __restrict__ kc, int j, int mode, int first, int red,
+                                                    HostPost post) {
+    k_dot_finish_d(PF_BLK, nk, G, part, kc, j, mode, first, red, post);
 }
 struct F_k_dot_finish {
     static constexpr int kLB = 256;
@@ -521,15 +517,8 @@ struct F_k_mupdate {
 // fuse: the first pass's update may have normalised w (fused_scale); then
 // h(j+1, j) is the predicted norm and w needs no further scaling unless its
 // measured norm strays from 1.
-__device__ __forceinline__ void k_arnoldi_close_d(const Blk& wg, int G, const double* __restrict__ part,
-                                                  KrylovCtl* __restrict__ kc, int j, int stage, int always_reorth,
-                                                  int fuse) {
-    if (stage == 1 && kc->reorth == 0) return;
-    __shared__ double lds[16];
-    double a = 0.0;
-    for (int b = threadIdx.x; b < G; b += blockDim.x) a += part[b];
-    const double ss = block_sum_fixed(a, lds);
-    if (threadIdx.x != 0) return;
+__device__ __forceinline__ void close_column(KrylovCtl* __restrict__ kc, double ss, int j, int stage,
+                                             int always_reorth, int fuse) {
     // w's multiple of u after this pass
     const double sc = stage == 0 && fuse ? fused_scale(kc, j + 1) : 0.0;
     double aw = kc->alpha[stage == 0 ? j : j + 1];
@@ -586,10 +575,22 @@ __device__ __forceinline__ void k_arnoldi_close_d(const Blk& wg, int G, const do
     kc->inv_h = ok ? (kc->normalised ? 1.0 : 1.0 / wm) : 0.0;
     kc->breakdown = !ok;
 }
+__device__ __forceinline__ void k_arnoldi_close_d(const Blk& wg, int G, const double* __restrict__ part,
+                                                  KrylovCtl* __restrict__ kc, int j, int stage, int always_reorth,
+                                                  int fuse, HostPost post) {
+    const bool skip = stage == 1 && kc->reorth == 0;
+    __shared__ double lds[16];
+    double a = 0.0;
+    for (int b = threadIdx.x; b < G; b += blockDim.x) a += part[b];
+    const double ss = block_sum_fixed(a, lds);
+    if (threadIdx.x != 0) return;
+    if (!skip) close_column(kc, ss, j, stage, always_reorth, fuse);
+    post_ctl(kc, post);
+}
 __global__ __launch_bounds__(256) void k_arnoldi_close(int G, const double* __restrict__ part,
                                                        KrylovCtl* __restrict__ kc, int j, int stage,
-                                                       int always_reorth, int fuse) {
-    k_arnoldi_close_d(PF_BLK, G, part, kc, j, stage, always_reorth, fuse);
+                                                       int always_reorth, int fuse, HostPost post) {
+    k_arnoldi_close_d(PF_BLK, G, part, kc, j, stage, always_reorth, fuse, post);
 }
 struct F_k_arnoldi_close {
     static constexpr int kLB = 256;
@@ -720,11 +721,6 @@ void launch_copy(Sim& s, int64_t n, const double* x, double* y) {
     PF_LAUNCH_CHECK();
 }
 
-void launch_copy_words(Sim& s, const void* src, void* dst, size_t bytes) {
-    launch<F_k_copy_words>(s, s.stream, k_copy_words, dim3(1), dim3(64), 0, (const uint32_t*)src, (uint32_t*)dst,
-                           (int)(bytes / 4));
-}
-
 void launch_fill(Sim& s, int64_t n, double v, double* y) {
     launch<F_k_fill>(s, s.stream, k_fill, dim3(stream_grid(n)), dim3(kBlock), 0, n, v, y);
     PF_LAUNCH_CHECK();
@@ -741,7 +737,7 @@ void launch_bjac_apply(Sim& s, const double* r, double* z) {
     PF_LAUNCH_CHECK();
 }
 
-void launch_norm_to_ctl(Sim& s, const double* v, int first) {
+void launch_norm_to_ctl(Sim& s, const double* v, int first, const HostPost& post) {
     const int G = kRedBlocks;
     launch<F_k_mdot<1, false>>(s, s.stream, k_mdot<1, false>, dim3(G), dim3(kBlock), 0, s.nk, 0, 0,
                                (const double*)nullptr, (int64_t)0, v + s.ko, s.part, s.kc, 0, 1);
@@ -753,7 +749,7 @@ void launch_norm_to_ctl(Sim& s, const double* v, int first) {
         PF_LAUNCH_CHECK();
     }
     launch<F_k_dot_finish>(s, s.stream, k_dot_finish, dim3(1), dim3(kBlock), 0, 0, G, s.part, s.kc, 0, 2, first,
-                           (int)(s.ko > 0));
+                           (int)(s.ko > 0), post);
     PF_LAUNCH_CHECK();
 }
 
@@ -822,7 +818,7 @@ void mupdate_any(Sim& s, int nk, double* w, int gated, int fuse) {
 // asked for it, so the usual iteration launches no second-pass kernels;
 // where the first pass's update did not already normalise w (kc->normalised),
 // launch_normalise then scales w into V[j+1].
-void launch_arnoldi(Sim& s, int j, double* w) {
+void launch_arnoldi(Sim& s, int j, double* w, const HostPost& post) {
     const int G = kRedBlocks;
     const int nk = j + 1;
     const int always = s.opts.reorth ? 1 : 0;
@@ -831,30 +827,32 @@ void launch_arnoldi(Sim& s, int j, double* w) {
         ProfScope ps(s, PF_K_MDOT);
         mdot_all(s, nk, nk + 1, w, 0);
     }
-    launch<F_k_dot_finish>(s, s.stream, k_dot_finish, dim3(nk + 1), dim3(kBlock), 0, nk, G, s.part, s.kc, j, 0, 0, 0);
+    launch<F_k_dot_finish>(s, s.stream, k_dot_finish, dim3(nk + 1), dim3(kBlock), 0, nk, G, s.part, s.kc, j, 0, 0, 0,
+                           HostPost{});
     PF_LAUNCH_CHECK();
     {
         ProfScope ps(s, PF_K_MUPDATE);
         mupdate_any(s, nk, w, 0, !always);
     }
     launch<F_k_arnoldi_close>(s, s.stream, k_arnoldi_close, dim3(1), dim3(kBlock), 0, G, s.part, s.kc, j, 0, always,
-                              !always);
+                              !always, always ? HostPost{} : post);
     PF_LAUNCH_CHECK();
-    if (always) launch_arnoldi_second(s, j, w);
+    if (always) launch_arnoldi_second(s, j, w, post);
 }
 
 // The second CGS pass (its kernels return at once unless the first pass's
 // test asked for it).
-void launch_arnoldi_second(Sim& s, int j, double* w) {
+void launch_arnoldi_second(Sim& s, int j, double* w, const HostPost& post) {
     const int G = kRedBlocks;
     const int nk = j + 1;
     const int always = s.opts.reorth ? 1 : 0;
     mdot_all(s, nk, nk, w, 1);
-    launch<F_k_dot_finish>(s, s.stream, k_dot_finish, dim3(nk), dim3(kBlock), 0, nk, G, s.part, s.kc, j, 1, 0, 0);
+    launch<F_k_dot_finish>(s, s.stream, k_dot_finish, dim3(nk), dim3(kBlock), 0, nk, G, s.part, s.kc, j, 1, 0, 0,
+                           HostPost{});
     PF_LAUNCH_CHECK();
     mupdate_any(s, nk, w, 1, 0);
     launch<F_k_arnoldi_close>(s, s.stream, k_arnoldi_close, dim3(1), dim3(kBlock), 0, G, s.part, s.kc, j, 1, always,
-                              0);
+                              0, post);
     PF_LAUNCH_CHECK();
 }
 

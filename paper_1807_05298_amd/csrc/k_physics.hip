@@ -776,10 +776,16 @@ struct F_k_norm_part {
     }
 };
 
+__device__ __forceinline__ void post_values(const double* v, int n, const HostPost& p) {
+    if (!p.out) return;
+    for (int k = 0; k < n; ++k) p.out[k] = v[k];
+    post_done(p);
+}
+
 // out: [0..2] max per equation, [3] max well row, [4] overall max, [5] 2-norm
 __device__ __forceinline__ void k_norm_finish_d(const Blk& wg, int64_t n, int nw, int nblk,
                                                 const double* __restrict__ v, const double* __restrict__ part,
-                                                double* __restrict__ out) {
+                                                double* __restrict__ out, HostPost post) {
     __shared__ double lds[4 * 16];
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     const bool mx[4] = {true, true, true, false};
@@ -801,11 +807,13 @@ __device__ __forceinline__ void k_norm_finish_d(const Blk& wg, int64_t n, int nw
         out[3] = wm;
         out[4] = fmax(fmax(acc[0], acc[1]), fmax(acc[2], wm));
         out[5] = (ss <= DBL_MAX) ? sqrt(ss) : INFINITY;
+        post_values(out, 6, post);
     }
 }
 __global__ __launch_bounds__(256) void k_norm_finish(int64_t n, int nw, int nblk, const double* __restrict__ v,
-                                                     const double* __restrict__ part, double* __restrict__ out) {
-    k_norm_finish_d(PF_BLK, n, nw, nblk, v, part, out);
+                                                     const double* __restrict__ part, double* __restrict__ out,
+                                                     HostPost post) {
+    k_norm_finish_d(PF_BLK, n, nw, nblk, v, part, out, post);
 }
 struct F_k_norm_finish {
     static constexpr int kLB = 256;
@@ -858,7 +866,7 @@ struct F_k_update_part {
 // out: [0] dP/bar, [1] dS, [2] dC/Cref, [3] dPb/bar, [4] max of all
 __device__ __forceinline__ void k_update_finish_d(const Blk& wg, DevModel m, int nblk, const double* __restrict__ dx,
                                                   double* __restrict__ x, const double* __restrict__ part,
-                                                  double* __restrict__ out, int cs) {
+                                                  double* __restrict__ out, int cs, HostPost post) {
     __shared__ double lds[3 * 16];
     double acc[3] = {0.0, 0.0, 0.0};
     const bool mx[3] = {true, true, true};
@@ -877,12 +885,13 @@ __device__ __forceinline__ void k_update_finish_d(const Blk& wg, DevModel m, int
         out[2] = acc[2];
         out[3] = wm;
         out[4] = fmax(fmax(acc[0], acc[1]), fmax(acc[2], wm));
+        post_values(out, 5, post);
     }
 }
 __global__ __launch_bounds__(256) void k_update_finish(DevModel m, int nblk, const double* __restrict__ dx,
                                                        double* __restrict__ x, const double* __restrict__ part,
-                                                       double* __restrict__ out, int cs) {
-    k_update_finish_d(PF_BLK, m, nblk, dx, x, part, out, cs);
+                                                       double* __restrict__ out, int cs, HostPost post) {
+    k_update_finish_d(PF_BLK, m, nblk, dx, x, part, out, cs, post);
 }
 struct F_k_update_finish {
     static constexpr int kLB = 256;
@@ -1151,21 +1160,22 @@ void launch_assemble(Sim& s, double dt, bool with_jacobian) {
     }
 }
 
-void launch_norms(Sim& s, const double* v, double* out) {
+void launch_norms(Sim& s, const double* v, double* out, const HostPost& post) {
     const int G = kRedBlocks;
     launch<F_k_norm_part>(s, s.stream, k_norm_part, dim3(G), dim3(kBlock), 0, s.m.n, v, s.part);
     PF_LAUNCH_CHECK();
-    launch<F_k_norm_finish>(s, s.stream, k_norm_finish, dim3(1), dim3(kBlock), 0, s.m.n, s.m.nw, G, v, s.part, out);
+    launch<F_k_norm_finish>(s, s.stream, k_norm_finish, dim3(1), dim3(kBlock), 0, s.m.n, s.m.nw, G, v, s.part, out,
+                            post);
     PF_LAUNCH_CHECK();
 }
 
-void launch_update(Sim& s, const double* dx, double* out, bool cs) {
+void launch_update(Sim& s, const double* dx, double* out, bool cs, const HostPost& post) {
     const int G = kRedBlocks;
     launch<F_k_update_part>(s, s.stream, k_update_part, dim3(G), dim3(kBlock), 0, s.m, s.opts.ds_max, dx, s.x, s.part,
                             (int)cs);
     PF_LAUNCH_CHECK();
     launch<F_k_update_finish>(s, s.stream, k_update_finish, dim3(1), dim3(kBlock), 0, s.m, G, dx, s.x, s.part, out,
-                              (int)cs);
+                              (int)cs, post);
     PF_LAUNCH_CHECK();
 }
 

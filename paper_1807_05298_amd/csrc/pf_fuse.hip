@@ -15,6 +15,8 @@
 #include "pf_internal.h"
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <condition_variable>
 #include <cstring>
 #include <map>
@@ -31,7 +33,7 @@ struct Fusion {
     std::vector<Sim*> members;
     int waiting = 0;                 // members at a synchronisation point
     bool flushing = false;
-    uint64_t gen = 0;                // issued batches of recorded work
+    std::atomic<uint64_t> gen{0};    // issued batches of recorded work
     std::string err;                 // error of the last issue (every member of it reports it)
     // the merged launches' tables: built in pinned host memory, copied once per issue
     uint8_t* h_tab = nullptr;
@@ -39,10 +41,30 @@ struct Fusion {
     void* d_tab = nullptr;
     size_t d_cap = 0;
     std::vector<uint8_t> tab;
+    unsigned long long *flag = nullptr, seq = 0;     // pinned: number of the last issue that ended
     int64_t n_issue = 0, n_ops = 0, n_launch = 0;
 };
 
 namespace {
+
+// the number of an issue, for the host, once everything before it has run
+__global__ void k_signal(unsigned long long* flag, unsigned long long seq) {
+    __threadfence_system();
+    __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Looks for done() for kPollTime, giving way to other threads; whether it came.
+constexpr std::chrono::microseconds kPollTime{2000};
+template <class Done>
+bool poll(Done done) {
+    const auto t0 = std::chrono::steady_clock::now();
+    for (;;) {
+        for (int k = 0; k < 64; ++k)
+            if (done()) return true;
+        if (std::chrono::steady_clock::now() - t0 > kPollTime) return false;
+        std::this_thread::yield();
+    }
+}
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -215,7 +237,20 @@ void issue(Fusion& F, const std::vector<Sim*>& mem) {
             F.n_launch++;
         }
     }
-    PF_HIP(hipStreamSynchronize(F.stream));
+    if (!F.flag) {
+        PF_HIP(hipHostMalloc((void**)&F.flag, 64, hipHostMallocCoherent));
+        *F.flag = 0;
+    }
+    // host operations may have copies to ordinary memory under way, which the runtime finishes
+    bool host = false;
+    for (const Planned& p : plan) host = host || p.host_op;
+    if (host) {
+        PF_HIP(hipStreamSynchronize(F.stream));
+    } else {
+        hipLaunchKernelGGL(k_signal, dim3(1), dim3(1), 0, F.stream, F.flag, ++F.seq);
+        PF_LAUNCH_CHECK();
+        poll_flag(F.flag, F.seq, F.stream);
+    }
     F.n_issue++;
 }
 
@@ -294,8 +329,22 @@ void fusion_sync(Sim& s) {
     const uint64_t g = F.gen;
     ++F.waiting;
     if (F.waiting == (int)F.members.size()) issue_all(F, lk);
-    else F.cv.wait(lk, [&] { return F.gen != g; });
+    else {
+        // the issue of a batch takes some 100 us, a wake-up tens of them: look for a while, then sleep
+        lk.unlock();
+        poll([&] { return F.gen.load(std::memory_order_acquire) != g; });
+        lk.lock();
+        F.cv.wait(lk, [&] { return F.gen != g; });
+    }
     if (!F.err.empty()) throw HipError{F.err};
+}
+
+void poll_flag(const unsigned long long* flag, unsigned long long seq, hipStream_t stream) {
+    const auto done = [=] { return __atomic_load_n(flag, __ATOMIC_ACQUIRE) == seq; };
+    // every 64th time through the runtime, which then takes back what it holds for finished launches
+    if ((seq & 63) != 0 && poll(done)) return;
+    PF_HIP(hipStreamSynchronize(stream));
+    if (!done()) throw HipError{"the GPU did not report the end of its work"};
 }
 
 void copy_h2d(Sim& s, void* dst, const void* src, size_t bytes) {
@@ -485,6 +534,7 @@ void pf_fusion_destroy(pf_fusion* h) {
         }
     }
     if (h->f.h_tab) (void)hipHostFree(h->f.h_tab);
+    if (h->f.flag) (void)hipHostFree(h->f.flag);
     if (h->f.d_tab) (void)hipFree(h->f.d_tab);
     delete h;
 }

@@ -26,6 +26,7 @@ constexpr int kBlock = 256;          // threads per block for cell sweeps
 constexpr int kMaxRestart = 64;
 constexpr int kRedBlocks = 1024;     // fixed partial-sum grid of the reductions
 constexpr int kDotChunk = 16;        // dot products per multi-dot launch
+constexpr int kPostFlag = 32;        // place of the flag in the read-back buffer
 constexpr int kCoarseReg = 96;       // largest coarsest level inverted in registers (k_coarse)
 constexpr int kCoarsePad = 16;       // rows of the transposed coarsest inverse: padded with zeros to a multiple
 constexpr int kPartSlots = kMaxRestart + 2;   // partial-sum slots: restart + 2 dot products
@@ -193,6 +194,19 @@ struct MGLevel {
     float* r32;
 };
 
+// Values for the host that a kernel writes itself, as its last act: to the
+// pinned read-back buffer, then seq to its flag, for which the host polls
+// (wait_post).  out null: nothing (a read-back buffer that is not pinned is
+// filled by a copy).
+struct HostPost {
+    double* out;
+    unsigned long long *flag, seq;
+};
+// by one thread, whose own stores the release orders
+__device__ __forceinline__ void post_done(const HostPost& p) {
+    __hip_atomic_store(p.flag, p.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 struct Sim {
     DevModel m;
     pf_solver_opts opts;
@@ -256,6 +270,7 @@ struct Sim {
 
     // host
     double* hbuf;                    // read-back buffer (64 doubles): pinned, or static (static_dev >= 0)
+    unsigned long long post_seq = 0; // last post's number; its flag is hbuf[kPostFlag]
     int static_dev = -1;             // device whose static workspace this simulator holds (-1: caller's)
     int device = 0;                  // device current at creation (its workspace and stream)
     bool coarse_pending = false;     // the coarsest inverse may still run on the side stream
@@ -317,8 +332,8 @@ struct Bump {
 void launch_static(Sim& s);
 void launch_accum(Sim& s, const double* x, double* M);
 void launch_assemble(Sim& s, double dt, bool with_jacobian);
-void launch_norms(Sim& s, const double* v, double* out);          // out[0..5]
-void launch_update(Sim& s, const double* dx, double* out, bool cs = false);   // out[0..4]; cs: dx colour-split
+void launch_norms(Sim& s, const double* v, double* out, const HostPost& post);   // out[0..5]
+void launch_update(Sim& s, const double* dx, double* out, bool cs, const HostPost& post);   // out[0..4]; cs: dx colour-split
 void launch_kperm(Sim& s);                                          // per-cell RRF, A_d,max
 void launch_ads_hist(Sim& s);                                       // take in the current state
 void launch_equilibrium(Sim& s, double datum_depth, double datum_p, double fwl_depth);
@@ -335,14 +350,15 @@ void launch_fill(Sim& s, int64_t n, double v, double* y);
 // the natural-order planes formed from it when a kernel needs them
 bool j_colour_split_mode(const Sim& s);
 void ensure_j_natural(Sim& s);
-void launch_copy_words(Sim& s, const void* src, void* dst, size_t bytes);   // bytes: a multiple of 4
 void launch_bjac_setup(Sim& s);
 void launch_bjac_apply(Sim& s, const double* r, double* z);
 // Krylov helpers
-void launch_norm_to_ctl(Sim& s, const double* v, int which);      // which 0: beta0+beta, 1: beta
+void launch_norm_to_ctl(Sim& s, const double* v, int which, const HostPost& post);   // which 0: beta0+beta, 1: beta
 void launch_scale_by_ctl(Sim& s, const double* v, double* out, int which);  // which 0: 1/beta, 1: inv_h
-void launch_arnoldi(Sim& s, int j, double* w);                     // first CGS pass of w against V[0..j]
-void launch_arnoldi_second(Sim& s, int j, double* w);              // second pass (when requested)
+// first CGS pass of w against V[0..j], and the second pass (when requested);
+// posts rel, then (int32) reorth, breakdown, normalised of the control block
+void launch_arnoldi(Sim& s, int j, double* w, const HostPost& post);
+void launch_arnoldi_second(Sim& s, int j, double* w, const HostPost& post);
 void launch_normalise(Sim& s, int j, double* w);                   // V[j+1] = w / h(j+1, j)
 void launch_solve_small(Sim& s, int k);                             // y = H(0:k,0:k)^{-1} g
 void launch_zcomb(Sim& s, int k, double* dx, bool first = false);   // dx += Z y (first: dx = Z y)
@@ -422,6 +438,9 @@ void launch(Sim& s, hipStream_t st, void (*k)(P...), dim3 grid, dim3 block, size
 void copy_h2d(Sim& s, void* dst, const void* src, size_t bytes);
 void copy_d2h(Sim& s, void* dst, const void* src, size_t bytes);
 void stream_sync(Sim& s);
+// Waits until *flag == seq, which the last kernel on the stream writes: polls,
+// and leaves a longer wait (or an error) to the runtime.
+void poll_flag(const unsigned long long* flag, unsigned long long seq, hipStream_t stream);
 
 // Colour-split vector layout of the FP64 red-black ILU(0) path (PF order): the
 // three planes (P, S, C) of the red cells ((ix+iy+iz) even), ns entries each,
