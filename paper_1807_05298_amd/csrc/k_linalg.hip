@@ -449,10 +449,9 @@ constexpr double kReorthEta = 0.1;
 // where the prediction is not trusted (severe cancellation, or the test
 // would call for the second pass); the update and the close compute it from
 // the same values in the same order, so they agree.
-__device__ __forceinline__ double fused_scale(const KrylovCtl* kc, int nk) {
+__device__ __forceinline__ double fused_scale(const double* h, double w0, int nk) {
     double hs = 0.0;
-    for (int k = 0; k < nk; ++k) hs += kc->h[k] * kc->h[k];
-    const double w0 = kc->wnorm0;
+    for (int k = 0; k < nk; ++k) hs += h[k] * h[k];
     const double p2 = w0 * w0 - hs;
     const bool ok = p2 > 0.0 && p2 <= DBL_MAX && p2 >= kReorthEta * kReorthEta * (w0 * w0);
     return ok ? 1.0 / sqrt(p2) : 0.0;
@@ -467,7 +466,7 @@ __device__ __forceinline__ void k_mupdate_d(const Blk& wg, int64_t nv, int nk, c
                                             const KrylovCtl* __restrict__ kc, int gated, int fuse) {
     if (gated && kc->reorth == 0) return;
     __shared__ double lds[16];
-    double sc = fuse ? fused_scale(kc, nk) : 0.0;
+    double sc = fuse ? fused_scale(kc->h, kc->wnorm0, nk) : 0.0;
     if (sc == 0.0) sc = 1.0;
     double ss = 0.0;
     if (KN > 0) {
@@ -517,17 +516,27 @@ struct F_k_mupdate {
 // fuse: the first pass's update may have normalised w (fused_scale); then
 // h(j+1, j) is the predicted norm and w needs no further scaling unless its
 // measured norm strays from 1.
-__device__ __forceinline__ void close_column(KrylovCtl* __restrict__ kc, double ss, int j, int stage,
-                                             int always_reorth, int fuse) {
+//
+// One thread's work, on values that its block has brought to LDS: from global
+// memory each of its loops paid a round trip an entry (over 17 columns 6.7 us
+// on average for 8.8).
+struct CloseShared {
+    double h[kMaxRestart + 1], alpha[kMaxRestart + 1], cs[kMaxRestart], sn[kMaxRestart], col[kMaxRestart + 1];
+    double red[16];
+};
+__device__ __forceinline__ void close_column(KrylovCtl* __restrict__ kc, const CloseShared& sh, double ss, int j,
+                                             int stage, int always_reorth, int fuse) {
+    const double wnorm0 = kc->wnorm0, gram = kc->gram, beta0 = kc->beta0, gj = kc->g[j];
     // w's multiple of u after this pass
-    const double sc = stage == 0 && fuse ? fused_scale(kc, j + 1) : 0.0;
-    double aw = kc->alpha[stage == 0 ? j : j + 1];
-    for (int k = 0; k <= j; ++k) aw -= kc->h[k] * kc->alpha[k];
+    const double sc = stage == 0 && fuse ? fused_scale(sh.h, wnorm0, j + 1) : 0.0;
+    double aw = stage == 0 ? sh.alpha[j] : kc->alpha[j + 1];
+    for (int k = 0; k <= j; ++k) aw -= sh.h[k] * sh.alpha[k];
     if (sc > 0.0) aw *= sc;
     kc->alpha[j + 1] = aw;
-    const double wm = sqrt(ss + aw * (aw * kc->gram));     // norm of w as stored
+    const double wm = sqrt(ss + aw * (aw * gram));       // norm of w as stored
     double wn = wm;                      // h(j+1, j)
     kc->normalised = 0;
+    bool normalised = false;
     if (stage == 0) {
         if (sc > 0.0) {
             // w holds (w - V h) * sc: no second pass by construction
@@ -535,12 +544,13 @@ __device__ __forceinline__ void close_column(KrylovCtl* __restrict__ kc, double 
             if (fabs(wm - 1.0) <= 1e-10) {
                 wn = 1.0 / sc;
                 kc->normalised = 1;
+                normalised = true;
             } else {
                 wn = wm / sc;
             }
         } else {
             // a large cancellation calls for a second pass
-            const int again = always_reorth || !(wm > kReorthEta * kc->wnorm0);
+            const int again = always_reorth || !(wm > kReorthEta * wnorm0);
             kc->reorth = again;
             if (again) {
                 kc->wnorm = wm;
@@ -551,14 +561,13 @@ __device__ __forceinline__ void close_column(KrylovCtl* __restrict__ kc, double 
     kc->wnorm = wn;
     constexpr int ld = kMaxRestart + 1;
     double* col = kc->H + j * ld;
-    col[j + 1] = wn;
+    double hj = sh.col[0];               // row i, the rotations of the rows above applied
     for (int i = 0; i < j; ++i) {
-        const double t0 = kc->cs[i] * col[i] + kc->sn[i] * col[i + 1];
-        const double t1 = -kc->sn[i] * col[i] + kc->cs[i] * col[i + 1];
-        col[i] = t0;
-        col[i + 1] = t1;
+        const double c = sh.cs[i], s = sh.sn[i], next = sh.col[i + 1];
+        col[i] = c * hj + s * next;
+        hj = -s * hj + c * next;
     }
-    const double hj = col[j], hj1 = col[j + 1];
+    const double hj1 = wn;
     const double r = hypot(hj, hj1);
     const double c = (r > 0.0) ? hj / r : 1.0;
     const double s = (r > 0.0) ? hj1 / r : 0.0;
@@ -566,25 +575,35 @@ __device__ __forceinline__ void close_column(KrylovCtl* __restrict__ kc, double 
     kc->sn[j] = s;
     col[j] = r;
     col[j + 1] = 0.0;
-    const double gj = kc->g[j];
     kc->g[j] = c * gj;
     kc->g[j + 1] = -s * gj;
-    kc->rel = (kc->beta0 > 0.0) ? fabs(kc->g[j + 1]) / kc->beta0 : 0.0;
+    kc->rel = (beta0 > 0.0) ? fabs(-s * gj) / beta0 : 0.0;
     const bool ok = wn > 1e-300 && wn <= DBL_MAX && r > 0.0 && r <= DBL_MAX && wm > 0.0 && wm <= DBL_MAX;
     // scale that turns the stored w into V[j+1] (1 when already normalised)
-    kc->inv_h = ok ? (kc->normalised ? 1.0 : 1.0 / wm) : 0.0;
+    kc->inv_h = ok ? (normalised ? 1.0 : 1.0 / wm) : 0.0;
     kc->breakdown = !ok;
 }
+
 __device__ __forceinline__ void k_arnoldi_close_d(const Blk& wg, int G, const double* __restrict__ part,
                                                   KrylovCtl* __restrict__ kc, int j, int stage, int always_reorth,
                                                   int fuse, HostPost post) {
     const bool skip = stage == 1 && kc->reorth == 0;
-    __shared__ double lds[16];
+    __shared__ CloseShared sh;
+    constexpr int ld = kMaxRestart + 1;
+    for (int k = threadIdx.x; k <= j; k += blockDim.x) {
+        sh.h[k] = kc->h[k];
+        sh.alpha[k] = kc->alpha[k];
+        sh.col[k] = kc->H[j * ld + k];
+        if (k < j) {
+            sh.cs[k] = kc->cs[k];
+            sh.sn[k] = kc->sn[k];
+        }
+    }
     double a = 0.0;
     for (int b = threadIdx.x; b < G; b += blockDim.x) a += part[b];
-    const double ss = block_sum_fixed(a, lds);
+    const double ss = block_sum_fixed(a, sh.red);        // (its barrier covers the copies)
     if (threadIdx.x != 0) return;
-    if (!skip) close_column(kc, ss, j, stage, always_reorth, fuse);
+    if (!skip) close_column(kc, sh, ss, j, stage, always_reorth, fuse);
     post_ctl(kc, post);
 }
 __global__ __launch_bounds__(256) void k_arnoldi_close(int G, const double* __restrict__ part,
@@ -620,22 +639,30 @@ struct F_k_scale_ctl {
     }
 };
 
-// y = R^{-1} g for the k x k upper triangle left by the rotations.
+// y = R^{-1} g for the k x k upper triangle left by the rotations, one
+// wavefront: lane i holds what is left of row i, and each column is taken off
+// all rows at once (17 columns 7.7 us, 28.0 by one thread).
 __device__ __forceinline__ void k_solve_small_d(const Blk& wg, KrylovCtl* kc, int k) {
-    if (threadIdx.x != 0 || wg.x != 0) return;
+    static_assert(kMaxRestart <= 64, "a lane for every row");
+    __shared__ double R[kMaxRestart * kMaxRestart];
     constexpr int ld = kMaxRestart + 1;
-    for (int i = k - 1; i >= 0; --i) {
-        double s = kc->g[i];
-        for (int q = i + 1; q < k; ++q) s -= kc->H[q * ld + i] * kc->y[q];
-        const double d = kc->H[i * ld + i];
-        kc->y[i] = (d != 0.0) ? s / d : 0.0;
+    const int i = threadIdx.x;
+    for (int q = i; q < k * k; q += 64) R[q] = kc->H[(q / k) * ld + q % k];
+    __syncthreads();
+    double s = i < k ? kc->g[i] : 0.0, y = 0.0;
+    const double d = i < k ? R[i * k + i] : 1.0;
+    for (int q = k - 1; q >= 0; --q) {
+        const double yq = __shfl(d != 0.0 ? s / d : 0.0, q, 64);
+        if (i == q) y = yq;
+        if (i < q) s -= R[q * k + i] * yq;
     }
+    if (i < k) kc->y[i] = y;
 }
-__global__ void k_solve_small(KrylovCtl* kc, int k) {
+__global__ __launch_bounds__(64) void k_solve_small(KrylovCtl* kc, int k) {
     k_solve_small_d(PF_BLK, kc, k);
 }
 struct F_k_solve_small {
-    static constexpr int kLB = 1024;
+    static constexpr int kLB = 64;
     template <class... A>
     __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
         k_solve_small_d(wg, a...);
@@ -738,7 +765,7 @@ void launch_bjac_apply(Sim& s, const double* r, double* z) {
 }
 
 void launch_norm_to_ctl(Sim& s, const double* v, int first, const HostPost& post) {
-    const int G = kRedBlocks;
+    const int G = red_grid(std::max(s.nk, s.ko));
     launch<F_k_mdot<1, false>>(s, s.stream, k_mdot<1, false>, dim3(G), dim3(kBlock), 0, s.nk, 0, 0,
                                (const double*)nullptr, (int64_t)0, v + s.ko, s.part, s.kc, 0, 1);
     PF_LAUNCH_CHECK();
@@ -763,7 +790,7 @@ namespace {
 
 template <int KN>
 void mdot_launch(Sim& s, int nk, int k0, const double* w, int gated) {
-    launch<F_k_mdot<KN, false>>(s, s.stream, k_mdot<KN, false>, dim3(kRedBlocks), dim3(kBlock), 0, s.nk, nk, k0,
+    launch<F_k_mdot<KN, false>>(s, s.stream, k_mdot<KN, false>, dim3(red_grid(s.nk)), dim3(kBlock), 0, s.nk, nk, k0,
                                 s.V + s.ko, s.kst, w + s.ko, s.part, s.kc, gated, KN);
     PF_LAUNCH_CHECK();
 }
@@ -775,8 +802,8 @@ void mdot_all(Sim& s, int nk, int nslots, const double* w, int gated) {
         if (s.fu) {
             // in a fusion group one kernel for every chunk size, so that
             // members at different iterations share launches
-            launch<F_k_mdot<kDotChunk, true>>(s, s.stream, k_mdot<kDotChunk, true>, dim3(kRedBlocks), dim3(kBlock),
-                                              0, s.nk, nk, k0, s.V + s.ko, s.kst, w + s.ko, s.part, s.kc, gated, kn);
+            launch<F_k_mdot<kDotChunk, true>>(s, s.stream, k_mdot<kDotChunk, true>, dim3(red_grid(s.nk)),
+                                              dim3(kBlock), 0, s.nk, nk, k0, s.V + s.ko, s.kst, w + s.ko, s.part, s.kc, gated, kn);
             continue;
         }
         switch (kn) {
@@ -790,8 +817,8 @@ void mdot_all(Sim& s, int nk, int nslots, const double* w, int gated) {
 
 template <int KN>
 void mupdate_launch(Sim& s, int nk, double* w, int gated, int fuse) {
-    launch<F_k_mupdate<KN>>(s, s.stream, k_mupdate<KN>, dim3(kRedBlocks), dim3(kBlock), 0, s.nk, nk, s.V + s.ko, s.kst,
-                            w + s.ko, s.part, s.kc, gated, fuse);
+    launch<F_k_mupdate<KN>>(s, s.stream, k_mupdate<KN>, dim3(red_grid(s.nk)), dim3(kBlock), 0, s.nk, nk, s.V + s.ko,
+                            s.kst, w + s.ko, s.part, s.kc, gated, fuse);
     PF_LAUNCH_CHECK();
 }
 
@@ -819,7 +846,7 @@ void mupdate_any(Sim& s, int nk, double* w, int gated, int fuse) {
 // where the first pass's update did not already normalise w (kc->normalised),
 // launch_normalise then scales w into V[j+1].
 void launch_arnoldi(Sim& s, int j, double* w, const HostPost& post) {
-    const int G = kRedBlocks;
+    const int G = red_grid(s.nk);
     const int nk = j + 1;
     const int always = s.opts.reorth ? 1 : 0;
     // pass 1: <V[k], w> for k <= j and <w, w>
@@ -843,7 +870,7 @@ void launch_arnoldi(Sim& s, int j, double* w, const HostPost& post) {
 // The second CGS pass (its kernels return at once unless the first pass's
 // test asked for it).
 void launch_arnoldi_second(Sim& s, int j, double* w, const HostPost& post) {
-    const int G = kRedBlocks;
+    const int G = red_grid(s.nk);
     const int nk = j + 1;
     const int always = s.opts.reorth ? 1 : 0;
     mdot_all(s, nk, nk, w, 1);

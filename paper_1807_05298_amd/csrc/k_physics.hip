@@ -712,7 +712,7 @@ struct F_k_well_rows {
 };
 
 // ---------------------------------------------------------------------------
-// Deterministic reductions: a fixed grid of kRedBlocks blocks, fixed
+// Deterministic reductions: a grid that follows from the size, fixed
 // grid-stride assignment, wavefront shuffles, then one finishing block that
 // folds the partials in index order.
 __device__ __forceinline__ double safe_abs(double v) {
@@ -1161,7 +1161,7 @@ void launch_assemble(Sim& s, double dt, bool with_jacobian) {
 }
 
 void launch_norms(Sim& s, const double* v, double* out, const HostPost& post) {
-    const int G = kRedBlocks;
+    const int G = red_grid(s.m.n);
     launch<F_k_norm_part>(s, s.stream, k_norm_part, dim3(G), dim3(kBlock), 0, s.m.n, v, s.part);
     PF_LAUNCH_CHECK();
     launch<F_k_norm_finish>(s, s.stream, k_norm_finish, dim3(1), dim3(kBlock), 0, s.m.n, s.m.nw, G, v, s.part, out,
@@ -1170,7 +1170,7 @@ void launch_norms(Sim& s, const double* v, double* out, const HostPost& post) {
 }
 
 void launch_update(Sim& s, const double* dx, double* out, bool cs, const HostPost& post) {
-    const int G = kRedBlocks;
+    const int G = red_grid(s.m.n);
     launch<F_k_update_part>(s, s.stream, k_update_part, dim3(G), dim3(kBlock), 0, s.m, s.opts.ds_max, dx, s.x, s.part,
                             (int)cs);
     PF_LAUNCH_CHECK();
