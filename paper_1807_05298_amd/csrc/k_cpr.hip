@@ -229,6 +229,56 @@ struct F_k_zline_setup {
 // times more threads than a thread-per-column sweep.  This variant keeps a
 // segment's layers in registers (L <= LMAX <= 8).
 //
+// The segmented solve itself: thread t holds segment seg of column c (t = seg
+// cpb + c) as al (forward factors), be (right-hand sides scaled) and cp
+// (backward factors) of len layers, with identity steps past them; be becomes
+// the solution.  Every thread of the block passes its three barriers.
+template <int LMAX, class T>
+__device__ __forceinline__ void zline_solve(T (&al)[LMAX], T (&be)[LMAX], const T (&cp)[LMAX], int len, int seg,
+                                            int nseg, int c, int cpb, int t, T* sA, T* sB) {
+    T Fa = 1, Fb = 0;
+#pragma unroll
+    for (int j = 0; j < LMAX; ++j) {
+        Fb = al[j] * Fb + be[j];
+        Fa = al[j] * Fa;
+    }
+    sA[t] = Fa;
+    sB[t] = Fb;
+    __syncthreads();
+    T y = 0;
+    // the maps' loads do not depend on the carried value: unrolled, they issue together
+#pragma unroll 8
+    for (int q = 0; q < seg; ++q) y = sA[q * cpb + c] * y + sB[q * cpb + c];
+    // forward values d'_k (kept in be); then this segment's backward map.
+    // Positions past the segment's end are identity steps in both passes
+    // (forward: al = 1, be = 0; backward: factor 1, be = 0).
+#pragma unroll
+    for (int j = 0; j < LMAX; ++j) {
+        y = al[j] * y + be[j];
+        be[j] = j < len ? y : (T)0;
+    }
+    T Ga = 1, Gb = 0;
+#pragma unroll
+    for (int j = LMAX - 1; j >= 0; --j) {
+        const T gm = j < len ? -cp[j] : (T)1;
+        al[j] = gm;
+        Gb = gm * Gb + be[j];
+        Ga = gm * Ga;
+    }
+    __syncthreads();
+    sA[t] = Ga;
+    sB[t] = Gb;
+    __syncthreads();
+    T xin = 0;
+#pragma unroll 8
+    for (int q = nseg - 1; q > seg; --q) xin = sA[q * cpb + c] * xin + sB[q * cpb + c];
+#pragma unroll
+    for (int j = LMAX - 1; j >= 0; --j) {
+        xin = al[j] * xin + be[j];
+        be[j] = xin;
+    }
+}
+
 // zline_seg_body is one block's share: columns col0 .. col0+cpb-1, thread t
 // (t >= cpb*nseg idle; every thread reaches the three barriers).  With BIN
 // the right-hand side of the segment's layers comes in registers (bin[j],
@@ -299,47 +349,10 @@ __device__ __forceinline__ void zline_seg_body(const Dims& g, const T* __restric
             be[j] = v ? r * c1 : (T)0;
         }
     }
-    T Fa = 1, Fb = 0;
+    zline_solve<LMAX, T>(al, be, cp, len, seg, nseg, c, cpb, t, sA, sB);
 #pragma unroll
-    for (int j = 0; j < LMAX; ++j) {
-        Fb = al[j] * Fb + be[j];
-        Fa = al[j] * Fa;
-    }
-    sA[t] = Fa;
-    sB[t] = Fb;
-    __syncthreads();
-    T y = 0;
-    // the maps' loads do not depend on the carried value: unrolled, they issue together
-#pragma unroll 8
-    for (int q = 0; q < seg; ++q) y = sA[q * cpb + c] * y + sB[q * cpb + c];
-    // forward values d'_k (kept in be); then this segment's backward map.
-    // Positions past the segment's end are identity steps in both passes
-    // (forward: al = 1, be = 0; backward: factor 1, be = 0).
-#pragma unroll
-    for (int j = 0; j < LMAX; ++j) {
-        y = al[j] * y + be[j];
-        be[j] = j < len ? y : (T)0;
-    }
-    T Ga = 1, Gb = 0;
-#pragma unroll
-    for (int j = LMAX - 1; j >= 0; --j) {
-        const T gm = j < len ? -cp[j] : (T)1;
-        al[j] = gm;
-        Gb = gm * Gb + be[j];
-        Ga = gm * Ga;
-    }
-    __syncthreads();
-    sA[t] = Ga;
-    sB[t] = Gb;
-    __syncthreads();
-    T xin = 0;
-#pragma unroll 8
-    for (int q = nseg - 1; q > seg; --q) xin = sA[q * cpb + c] * xin + sB[q * cpb + c];
-#pragma unroll
-    for (int j = LMAX - 1; j >= 0; --j) {
-        xin = al[j] * xin + be[j];
-        if (j < len) x[i0 + (int64_t)j * lstr] = xin;
-    }
+    for (int j = LMAX - 1; j >= 0; --j)
+        if (j < len) x[i0 + (int64_t)j * lstr] = be[j];
 }
 
 template <int LMAX, class T, bool ZERO_INIT>
@@ -637,6 +650,187 @@ struct F_k_resid_restrict {
     template <class... A>
     __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
         k_resid_restrict_d<T, RB, LAT>(wg, a...);
+    }
+};
+
+// The way down from a level in one launch: the colour-1 half-sweep that ends
+// its pre-smoothing, the restriction of the residual, and the next level's
+// first colour-0 half-sweep (from x = 0, so from its right-hand side alone).
+// A workgroup takes a tile of TX x TY fine columns: it solves the tile's
+// colour-1 lines and those of a ring around it (which its neighbours solve as
+// well: 48 lines for the 32 of 8 x 8, 18 for 8 of 8 x 2), keeps them in LDS, forms the tile's coarse cells from its colour-0 rows and solves
+// the coarse colour-0 lines in the tile.  The colour-0 values and both
+// right-hand sides it reads are not written by the launch, so workgroups do
+// not depend on one another; the arithmetic is that of the three launches.
+//
+// The three launches it replaces are bound by latency on small levels (3.5-4
+// us each): here it is one memory round trip, as the coefficients of all
+// three parts are loaded before the first solve.  What bounds it then is the
+// rate at which one compute unit draws from beyond its caches, hence the
+// choice of the tile (mg_down_tile).  Measured on levels of 95x192x5, 48x96x5
+// and 24x48x5 cells: 8.1, 5.6 and 4.3 us for 11.0, 10.8 and 10.7 by three
+// launches; a timestep of the first 9.3 -> 8.5 ms.
+constexpr int kDownLen = 2;
+template <class T> struct MgDown {
+    Dims f, c;                       // the level and the next
+    int cz, nbx;                     // layers a coarse cell, tiles in x
+    int nseg, nsegc;                 // segments (of kDownLen layers) of the level's lines and of the next level's
+    const T *A, *aux, *b;
+    T *x, *bc;
+    const T* auxc;                   // null: the next level's half-sweep is not done
+    T* xc;
+};
+template <int TX, int TY, class T, bool LAT>
+__device__ __forceinline__ void k_mg_down_d(const Blk& wg, const MgDown<T>& a) {
+    constexpr int kSideX = TX + 2, kSideY = TY + 2;        // the tile with its ring
+    constexpr int kRow = kSideX / 2, kCols = kSideY * kRow;     // its colour-1 columns (two corners idle)
+    constexpr int CX = TX / 2, CY = TY / 2;                // coarse columns
+    constexpr int kLines = CX * CY / 2, kLineRow = CX / 2; // and colour-0 ones of them
+    static_assert(CX % 2 == 0, "rows of a coarse tile start on one colour");
+    constexpr int LMAX = kDownLen;
+    extern __shared__ __align__(16) char down_lds[];
+    const int t = (int)threadIdx.x, nt = (int)blockDim.x;
+    T* const sA = reinterpret_cast<T*>(down_lds);
+    T* const sB = sA + nt;
+    T* const xs = sB + nt;                            // colour-1 values: layer kCols + column
+    T* const bs = xs + kCols * a.f.nz;            // coarse right-hand sides: layer CX CY + column
+    const Dims& f = a.f;
+    const Dims& c = a.c;
+    const int tile = (int)xcd_block(wg), by = tile / a.nbx, bx = tile - by * a.nbx;
+    const int hx = (f.nx + 1) >> 1, lstr = hx * f.ny;
+    const int64_t half = (int64_t)lstr * f.nz, n = 2 * half;
+
+    // a colour-1 line's segment
+    const int seg = t / kCols, col = t - seg * kCols;
+    const int ly = col / kRow, lx = 2 * (col - ly * kRow) + ((ly + 1) & 1);
+    const int ix = bx * TX + lx - 1, iy = by * TY + ly - 1;
+    const bool rx = lx == 0 || lx == kSideX - 1, ry = ly == 0 || ly == kSideY - 1;
+    const bool active = seg < a.nseg && ix >= 0 && ix < f.nx && iy >= 0 && iy < f.ny && !(rx && ry);
+    const int k0 = seg * LMAX, len = active ? max(0, min(LMAX, f.nz - k0)) : 0;
+    const int64_t i0 = len > 0 ? half + (int64_t)iy * hx + (ix >> 1) + (int64_t)k0 * lstr : 0;
+    T al[LMAX], be[LMAX], cp[LMAX];
+#pragma unroll
+    for (int j = 0; j < LMAX; ++j) {
+        cp[j] = 0;
+        al[j] = 1;
+        be[j] = 0;
+    }
+    if (len > 0) {
+        const bool xm = ix > 0, xp = ix + 1 < f.nx, ym = iy > 0, yp = iy + 1 < f.ny;
+        const int64_t oxm = xm ? -half + (((ix - 1) >> 1) - (ix >> 1)) : 0;
+        const int64_t oxp = xp ? -half + (((ix + 1) >> 1) - (ix >> 1)) : 0;
+        const int64_t oym = ym ? -half - hx : 0, oyp = yp ? -half + hx : 0;
+#pragma unroll
+        for (int j = 0; j < LMAX; ++j) {
+            const bool v = j < len;
+            const int64_t i = i0 + (int64_t)(v ? j : len - 1) * lstr;
+            T r = a.b[i];
+            const T a1 = a.A[n + i], a2 = a.A[2 * n + i], a3 = a.A[3 * n + i], a4 = a.A[4 * n + i];
+            const T x1 = a.x[i + oxm], x2 = a.x[i + oxp], x3 = a.x[i + oym], x4 = a.x[i + oyp];
+            r -= (xm ? a1 * x1 : (T)0) + (xp ? a2 * x2 : (T)0) + (ym ? a3 * x3 : (T)0) + (yp ? a4 * x4 : (T)0);
+            const T c0 = a.aux[i], c1 = a.aux[n + i], c2 = a.aux[2 * n + i];
+            cp[j] = v ? c0 : (T)0;
+            al[j] = v ? c2 : (T)1;
+            be[j] = v ? r * c1 : (T)0;
+        }
+    }
+
+    // a coarse cell: its colour-0 cells lie on the diagonal of the 2 x 2 columns
+    const int cx = t & (CX - 1), cy = (t / CX) & (CY - 1);
+    const int IZ = t / (CX * CY);
+    const int IX = bx * CX + cx, IY = by * CY + cy;
+    const bool cell = IX < c.nx && IY < c.ny && IZ < c.nz;
+    T w[4][4], r0[4];                                 // lateral coefficients; b - A x of the line itself
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int p = q & 1, jx = 2 * IX + p, jy = 2 * IY + p, jz = IZ * a.cz + (q >> 1);
+        const bool v = cell && (q >> 1) < a.cz && jx < f.nx && jy < f.ny && jz < f.nz;
+        const int64_t i = v ? (int64_t)jz * lstr + (int64_t)jy * hx + (jx >> 1) : 0;
+        const bool ex[4] = {v && jx > 0, v && jx + 1 < f.nx, v && jy > 0, v && jy + 1 < f.ny};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const T ak = a.A[(k + 1) * n + i];
+            w[q][k] = ex[k] ? ak : (T)0;
+        }
+        r0[q] = 0;
+        if constexpr (!LAT) {
+            const bool zm = v && jz > 0, zp = v && jz + 1 < f.nz;
+            const T z = (zm ? a.A[5 * n + i] * a.x[i - lstr] : (T)0) + (zp ? a.A[6 * n + i] * a.x[i + lstr] : (T)0);
+            r0[q] = v ? a.b[i] - a.A[i] * a.x[i] - z : (T)0;
+        }
+    }
+
+    // a coarse colour-0 line's segment
+    const int cc = t & (kLines - 1), cseg = t / kLines;
+    const int ccy = cc / kLineRow, JY = by * CY + ccy, ccx = 2 * (cc - ccy * kLineRow) + (JY & 1), JX = bx * CX + ccx;
+    const int hc = (c.nx + 1) >> 1, cstr = hc * c.ny;
+    const int kc = cseg * LMAX;
+    const int clen = a.auxc && cseg < a.nsegc && JX < c.nx && JY < c.ny ? max(0, min(LMAX, c.nz - kc)) : 0;
+    const int64_t j0 = clen > 0 ? (int64_t)JY * hc + (JX >> 1) + (int64_t)kc * cstr : 0, nc = 2 * (int64_t)cstr * c.nz;
+    T ca[LMAX], cb[LMAX], ccp[LMAX];
+#pragma unroll
+    for (int j = 0; j < LMAX; ++j) {
+        ccp[j] = 0;
+        ca[j] = 1;
+        cb[j] = 0;
+    }
+    if (clen > 0) {
+#pragma unroll
+        for (int j = 0; j < LMAX; ++j) {
+            const bool v = j < clen;
+            const int64_t i = j0 + (int64_t)(v ? j : clen - 1) * cstr;
+            const T c0 = a.auxc[i], c1 = a.auxc[nc + i], c2 = a.auxc[2 * nc + i];
+            ccp[j] = v ? c0 : (T)0;
+            ca[j] = v ? c2 : (T)1;
+            cb[j] = v ? c1 : (T)0;
+        }
+    }
+
+    zline_solve<LMAX, T>(al, be, cp, len, seg, a.nseg, col, kCols, t, sA, sB);
+#pragma unroll
+    for (int j = 0; j < LMAX; ++j)
+        if (j < len) {
+            xs[(k0 + j) * kCols + col] = be[j];
+            if (!rx && !ry) a.x[i0 + (int64_t)j * lstr] = be[j];
+        }
+    __syncthreads();
+    if (cell) {
+        T s = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int p = q & 1, jz = min(IZ * a.cz + (q >> 1), f.nz - 1);
+            const T* xl = xs + jz * kCols;
+            const int mx = 2 * cx + p + 1, my = 2 * cy + p + 1;      // place in the tile with its ring
+            // (a missing neighbour's place may hold anything)
+            const T x1 = xl[my * kRow + ((mx - 1) >> 1)], x2 = xl[my * kRow + ((mx + 1) >> 1)];
+            const T x3 = xl[(my - 1) * kRow + (mx >> 1)], x4 = xl[(my + 1) * kRow + (mx >> 1)];
+            const T lat = (w[q][0] != (T)0 ? w[q][0] * x1 : (T)0) + (w[q][1] != (T)0 ? w[q][1] * x2 : (T)0) +
+                          (w[q][2] != (T)0 ? w[q][2] * x3 : (T)0) + (w[q][3] != (T)0 ? w[q][3] * x4 : (T)0);
+            s += r0[q] - lat;
+        }
+        a.bc[lv_index(c, IX, IY, IZ)] = s;
+        bs[IZ * (CX * CY) + cy * CX + cx] = s;
+    }
+    if (!a.auxc) return;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < LMAX; ++j)
+        cb[j] *= j < clen ? bs[(kc + j) * (CX * CY) + ccy * CX + ccx] : (T)0;
+    zline_solve<LMAX, T>(ca, cb, ccp, clen, cseg, a.nsegc, cc, kLines, t, sA, sB);
+#pragma unroll
+    for (int j = 0; j < LMAX; ++j)
+        if (j < clen) a.xc[j0 + (int64_t)j * cstr] = cb[j];
+}
+template <int TX, int TY, class T, bool LAT>
+__global__ __launch_bounds__(1024) void k_mg_down(MgDown<T> a) {
+    k_mg_down_d<TX, TY, T, LAT>(PF_BLK, a);
+}
+template <int TX, int TY, class T, bool LAT>
+struct F_k_mg_down {
+    static constexpr int kLB = 1024;
+    template <class... A>
+    __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
+        k_mg_down_d<TX, TY, T, LAT>(wg, a...);
     }
 };
 
@@ -2227,11 +2421,15 @@ void zline_sweep(Sim& s, const MGLevel& L, int colour, int zero_init) {
 // column of a colour fits it with the level's segment length; false
 // (nothing launched) otherwise.  (Longer segments to make a larger level
 // fit were slower than its two launches per sweep.)
+bool zline_full_fits(const Sim& s, const MGLevel& L) {
+    const ZlShape z = zline_shape(s, L);
+    return z.len <= 8 && (int64_t)((L.nx + 1) / 2) * L.ny * z.nseg <= 1024;
+}
 template <class T>
 bool zline_full_sweeps(Sim& s, const MGLevel& L, int zero_init, int sweeps) {
+    if (!zline_full_fits(s, L)) return false;
     const ZlShape z = zline_shape(s, L);
     const int64_t cols = (int64_t)((L.nx + 1) / 2) * L.ny;
-    if (z.len > 8 || cols * z.nseg > 1024) return false;
     const Dims g = dims_of(L);
     const T* A = Lv<T>::A(L);
     const T* aux = Lv<T>::aux(L);
@@ -2252,6 +2450,75 @@ bool zline_full_sweeps(Sim& s, const MGLevel& L, int zero_init, int sweeps) {
 #undef PF_ZF
     PF_LAUNCH_CHECK();
     return true;
+}
+
+// The tile with which k_mg_down takes the way down from level l, or none for
+// launches of their own.  It needs 2 x 2 columns an aggregate and lines that
+// fit a workgroup in segments of kDownLen layers.  The costs are modelled (us):
+// a launch on a small level takes 3.5, the three of them a traffic that the
+// whole GPU draws at 3.7 TB/s; this one 4.2, and what a tile makes its compute
+// unit fetch, in pieces of 64 bytes of its short rows, at 20 KB a us, times the
+// tiles that a compute unit gets.  So low levels gain, and tall ones, whose
+// lines a compute unit has to hold from end to end, do not: on 101x77x33 the
+// best tile (4 x 4) took 21.9 us where the three launches take 15, on
+// 33x26x47 2 x 2 took 8.6 for 11 from x = 0 and 13.5 for 13.9 after another
+// cycle, for the same timestep.
+struct DownTile {
+    int x, y;
+};
+constexpr DownTile kDownTiles[] = {{8, 8}, {8, 2}, {4, 2}};
+template <class T>
+DownTile mg_down_tile(const Sim& s, int l, bool lat, bool next) {
+    DownTile best{0, 0};
+    if (l + 1 >= (int)s.mg.size()) return best;
+    const MGLevel& L = s.mg[l];
+    const int nseg = (L.nz + kDownLen - 1) / kDownLen;
+    if (L.cx != 2 || L.cy != 2 || nseg > 64) return best;
+    // values a cell: right-hand side, lateral coefficients, factors, neighbours; rows of colour 0
+    const double v1 = 10, v0 = lat ? 4 : 10, sz = sizeof(T);
+    double cost = (next ? 10.5 : 7.0) + 0.5 * (v1 + v0) * sz * (double)L.n / 3.7e6;
+    for (const DownTile& t : kDownTiles) {
+        const int row = (t.x + 2) / 2, lines = row * (t.y + 2);
+        if (lines * nseg > 1024) continue;
+        const double fetched = (t.y + 2) * v1 * (row * sz + 64 - sz) + t.y * v0 * (t.x / 2 * sz + 64 - sz);
+        const double tiles = (double)((L.nx + t.x - 1) / t.x) * ((L.ny + t.y - 1) / t.y);
+        const double c = 4.2 + fetched * L.nz / 20e3 * std::max(1.0, tiles / 256);
+        if (c < cost) {
+            cost = c;
+            best = t;
+        }
+    }
+    return best;
+}
+template <class T>
+void launch_mg_down(Sim& s, int l, const DownTile& tile, bool lat, bool next) {
+    const MGLevel &L = s.mg[l], &C = s.mg[l + 1];
+    MgDown<T> a;
+    a.f = dims_of(L);
+    a.c = dims_of(C);
+    a.cz = L.cz;
+    a.nbx = (L.nx + tile.x - 1) / tile.x;
+    a.nseg = (L.nz + kDownLen - 1) / kDownLen;
+    a.nsegc = (C.nz + kDownLen - 1) / kDownLen;
+    a.A = Lv<T>::A(L); a.aux = Lv<T>::aux(L); a.b = Lv<T>::b(L);
+    a.x = Lv<T>::x(L); a.bc = Lv<T>::b(C);
+    a.auxc = next ? Lv<T>::aux(C) : nullptr;
+    a.xc = Lv<T>::x(C);
+    // (threads for the fine lines' segments are enough for the coarse cells and lines)
+    const int lines = (tile.x + 2) / 2 * (tile.y + 2);
+    const unsigned threads = (unsigned)((lines * a.nseg + 63) / 64 * 64);
+    const size_t shm = (2 * threads + (size_t)lines * L.nz + (size_t)(tile.x / 2) * (tile.y / 2) * C.nz) * sizeof(T);
+    const dim3 grid((unsigned)(a.nbx * ((L.ny + tile.y - 1) / tile.y))), block(threads);
+#define PF_DN(X, Y)                                                                                          \
+    if (tile.x == X && tile.y == Y) {                                                                        \
+        if (lat) launch<F_k_mg_down<X, Y, T, true>>(s, s.stream, (k_mg_down<X, Y, T, true>), grid, block, shm, a); \
+        else launch<F_k_mg_down<X, Y, T, false>>(s, s.stream, (k_mg_down<X, Y, T, false>), grid, block, shm, a);   \
+    }
+    PF_DN(8, 8)
+    PF_DN(8, 2)
+    PF_DN(4, 2)
+#undef PF_DN
+    PF_LAUNCH_CHECK();
 }
 
 // b = Pi_r v on level 0 fused with the first V-cycle's first half-sweep;
@@ -2577,34 +2844,46 @@ void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_don
     } else {
         const int pre = pre_sweeps(s, L), post = std::max(0, s.opts.mg_post);
         MGLevel& C = s.mg[l + 1];
+        // after a single sweep from x = 0 the colour-0 rows' residuals are
+        // their lateral terms alone
+        const bool lat = pre == 1 && zero_init0;
+        // whether the next level's first half-sweep can follow its restriction
+        // at once (a level of one workgroup with more sweeps to do does them all)
+        const int pc = l + 1 < std::min(nt, nl - 1) ? pre_sweeps(s, C) : 0;
+        const bool next = pc == 1 || (pc > 1 && !zline_full_fits(s, C));
+        const DownTile tile = mg_down_tile<T>(s, l, lat, next);
         // a level that fits one workgroup takes all its pre-sweeps in one launch
-        const bool whole = l > 0 && !first_done && zline_full_sweeps<T>(s, L, zero_init0, pre);
+        // (a single one is half done by the launch before and the one after)
+        const bool whole = l > 0 && !first_done && !(pre == 1 && tile.x) && zline_full_sweeps<T>(s, L, zero_init0, pre);
+        const bool down = tile.x && !whole;
         for (int it = 0; it < (whole ? 0 : pre); ++it) {
             const int zi = (it == 0 && zero_init0) ? 1 : 0;
             if (!(it == 0 && first_done)) {
                 ProfScope ps(s, l == 0 ? PF_K_ZLINE : 0);
                 zline_sweep<T>(s, L, 0, zi);
             }
-            zline_sweep<T>(s, L, 1, 0);
+            if (it + 1 < pre || !down) zline_sweep<T>(s, L, 1, 0);
         }
         // pre-smoothing ended with a colour-1 half-sweep: those rows' residuals
-        // are zero; after a single sweep from x = 0 the colour-0 rows' are
-        // their lateral terms alone
-        const bool lat = pre == 1 && zero_init0;
-#define PF_RR(RB, LAT)                                                                                        \
-    launch<F_k_resid_restrict<T, RB, LAT>>(s, s.stream, (k_resid_restrict<T, RB, LAT>), dim3(grid_for(C.n)), \
-                                           dim3(kBlock), 0, g, dims_of(C), L.cx, L.cy, L.cz, Lv<T>::A(L),     \
-                                           Lv<T>::x(L), Lv<T>::b(L), Lv<T>::b(C), 1)
-        if (L.cx == 2 && L.cy == 2) {
-            if (lat) PF_RR(true, true);
-            else PF_RR(true, false);
+        // are zero
+        if (down) {
+            launch_mg_down<T>(s, l, tile, lat, next);
         } else {
-            if (lat) PF_RR(false, true);
-            else PF_RR(false, false);
-        }
+#define PF_RR(RB, LAT)                                                                                        \
+        launch<F_k_resid_restrict<T, RB, LAT>>(s, s.stream, (k_resid_restrict<T, RB, LAT>), dim3(grid_for(C.n)), \
+                                               dim3(kBlock), 0, g, dims_of(C), L.cx, L.cy, L.cz, Lv<T>::A(L),     \
+                                               Lv<T>::x(L), Lv<T>::b(L), Lv<T>::b(C), 1)
+            if (L.cx == 2 && L.cy == 2) {
+                if (lat) PF_RR(true, true);
+                else PF_RR(true, false);
+            } else {
+                if (lat) PF_RR(false, true);
+                else PF_RR(false, false);
+            }
 #undef PF_RR
-        PF_LAUNCH_CHECK();
-        vcycle<T>(s, l + 1);
+            PF_LAUNCH_CHECK();
+        }
+        vcycle<T>(s, l + 1, 1, nullptr, down && next);
         if (post == 0 && nl <= kMaxChain) {
             // no post-smoothing: the whole upward pass is prolongation, done once from level 0
             if (l == 0) {

@@ -341,7 +341,7 @@ void launch_equilibrium(Sim& s, double datum_depth, double datum_p, double fwl_d
 // Blocks of a reduction over n entries: one entry a thread up to kRedBlocks
 // blocks, a grid-stride loop beyond.  (Entries fall to the same partial sums
 // as with the full grid, whose other blocks would only add zeros: for eight
-// members of 4 to 20 thousand cells at once the products of a column took
+// members of 26 to 44 thousand cells at once the products of a column took
 // 22.7 us with it and take 10.7, the update 12.3 and 7.0.)
 inline int red_grid(int64_t n) {
     const int64_t g = (n + kBlock - 1) / kBlock;
