@@ -31,16 +31,18 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 # algorithmic bytes per cell and launch of the timed kernels (FP64)
 KERNEL_BYTES = {
-    "assemble": ("PF_K_ASSEMBLE", 1, 552),        # x 24 + Mn 24 + T 24 + PVr 8 in; R 24 + J 448 out (8 of 9 entries per block)
+    # x 24 + Mn 24 + T 24 + PVr 8 in; R 24 + J 400 out (diagonal block 8 of 9 entries, face blocks 7 values; 448
+    # in natural order)
+    "assemble": ("PF_K_ASSEMBLE", 1, 504),
     # the (oil, C) entry of every block of J is zero and not read: 8 of 9 entries per block
     "spmv": ("PF_K_SPMV", 2, 496),                # J 448 + x 24 in; y 24 out (x FP32 in mixed: 484)
     "zline": ("PF_K_ZLINE", 3, None),             # level-0 half-sweep, per active column set (below)
     "ilu": ("PF_K_ILU", 6, None),
-    # last ILU phase (after which the red rows of w = J z are those of v): Lc 384 + inverse diagonal 72
+    # last ILU phase (after which the red rows of w = J z are those of v): Lc 336 + inverse diagonal 72
     # + black z 24 + v 24 + border map 4 in, z 24 out, per red cell (half the cells)
-    "red_spmv": ("PF_K_RED_SPMV", 8, (384 + 72 + 24 + 24 + 4 + 24) // 2),
-    # black rows of w = J z: Lc 384 + J diagonal 64 + z 24 + red z 24 + border map 4 in, w 24 out, per black cell
-    "black_spmv": ("PF_K_BLACK_SPMV", 9, (384 + 64 + 24 + 24 + 4 + 24) // 2),
+    "red_spmv": ("PF_K_RED_SPMV", 8, (336 + 72 + 24 + 24 + 4 + 24) // 2),
+    # black rows of w = J z: Lc 336 + J diagonal 64 + z 24 + red z 24 + border map 4 in, w 24 out, per black cell
+    "black_spmv": ("PF_K_BLACK_SPMV", 9, (336 + 64 + 24 + 24 + 4 + 24) // 2),
     # FP64 first ILU phase on the pressure stage's residual, from the colour-split copies of J: off-diagonal
     # P-columns 144 + v 24 + black p 8 + border map 4 + D_r^{-1} 72 in, z 24 out, per red cell (the black rows'
     # residual is formed in the forward black phase)

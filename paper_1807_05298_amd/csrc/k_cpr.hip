@@ -111,8 +111,8 @@ __device__ __forceinline__ void k_extract_ap_cs_d(const Blk& wg, Dims g, const d
     const int64_t nsl = (int64_t)((g.nx + 1) >> 1) * g.ny * g.nz, cl = (ix + iy + iz) & 1;
     const int64_t sl = ((int64_t)iy + (int64_t)g.ny * iz) * ((g.nx + 1) >> 1) + (ix >> 1);
     for (int d = 0; d < 7; ++d) {
-        const double* Jd = d == 0 ? Jdc + cl * 9 * nsl + sl : Lc + (cl * 54 + (d - 1) * 9) * nsl + sl;
-        A[(int64_t)d * ns + j] = Jd[0 * nsl] + Jd[3 * nsl];   // (water + oil) rows, P column
+        const double* Jd = d == 0 ? Jdc + cl * 9 * nsl + sl : Lc + lc_at(nsl, cl, sl) + (d - 1) * kFaceVals * 64;
+        A[(int64_t)d * ns + j] = Jd[0] + Jd[3 * (d == 0 ? nsl : 64)];   // (water + oil) rows, P column
     }
 }
 __global__ void k_extract_ap_cs(Dims g, const double* __restrict__ Lc, const double* __restrict__ Jdc,
@@ -1539,7 +1539,9 @@ __device__ __forceinline__ void decode(const DevModel& m, int64_t i, int64_t& ix
 // where the colour has floor(nx/2) cells), so a phase that works on one
 // colour streams contiguous factor storage instead of every other element.
 //   Dc[(c*9 + e)*ns + s]        inverse (modified) diagonal blocks, FP64
-//   Lc[(c*54 + q*9 + e)*ns + s] off-diagonal blocks q = 0..5 (-x..+z)
+//   Lc[lc_at(ns, c, s) + (q*7 + v)*64]  off-diagonal blocks q = 0..5 (-x..+z),
+//                               FP64, seven values each (pf_internal.h)
+//   L16[(c*54 + q*9 + e)*ns + s]  the same, BF16, whole blocks
 //   Jdc[(c*9 + e)*ns + s]       diagonal blocks of J (FP64 ILU), so that the
 //                               product w = J z can stream colour-split storage
 // Entry e = 5 (oil row, C column) of every block of J is zero: the oil
@@ -1748,11 +1750,14 @@ __device__ __forceinline__ void k_ilu_setup_d(const Blk& wg, DevModel m, const d
     for (int f = 0; f < 6; ++f) {
         double Jbr[9];
         for (int e = 0; e < 9; ++e) Jbr[e] = e == 5 ? 0.0 : J[((int64_t)(f + 1) * 9 + e) * n + i];
-        if (Lc)
-            for (int e = 0; e < 9; ++e) {
-                if (e != 5) __builtin_nontemporal_store(Jbr[e], &Lc[((int64_t)colour * 54 + f * 9 + e) * ns + s]);
-            }
-        else
+        if (Lc) {
+            // g from the larger part of the row that it multiplies (both zero: any)
+            const bool byP = fabs(Jbr[0]) >= fabs(Jbr[1]);
+            const double d = byP ? Jbr[0] : Jbr[1], g = d != 0.0 ? (byP ? Jbr[6] : Jbr[7]) / d : 0.0;
+            const double v[kFaceVals] = {Jbr[0], Jbr[1], Jbr[2], Jbr[3], Jbr[4], g, Jbr[8]};
+            double* Lf = Lc + lc_at(ns, colour, s) + f * kFaceVals * 64;
+            for (int e = 0; e < kFaceVals; ++e) __builtin_nontemporal_store(v[e], &Lf[e * 64]);
+        } else
             for (int e = 0; e < 9; ++e) {
                 if (e != 5)
                     __builtin_nontemporal_store(f32_to_bf16((float)Jbr[e]),
@@ -1792,6 +1797,20 @@ struct F_k_ilu_setup {
     }
 };
 
+// A face's block from its stored values.
+__device__ __forceinline__ void face_block(const double* __restrict__ v, double B[9]) {
+    const double g = v[5 * 64];
+    B[0] = v[0 * 64];
+    B[1] = v[1 * 64];
+    B[2] = v[2 * 64];
+    B[3] = v[3 * 64];
+    B[4] = v[4 * 64];
+    B[5] = 0.0;
+    B[6] = g * B[0];
+    B[7] = g * B[1];
+    B[8] = v[6 * 64];
+}
+
 // The inverse diagonal blocks of red-black ILU(0) from J in the colour-split
 // storage (FP64): a cell reads its diagonal block from Jdc, a black cell its
 // face blocks and its red neighbours' diagonal and back-pointing blocks from
@@ -1826,10 +1845,10 @@ __device__ __forceinline__ void k_ilu_diag_d(const Blk& wg, DevModel m, const do
             const int fr = f ^ 1;       // direction from r back to i
             double Jbr[9], Drr[9], Jrb[9], Dr[9], T[9];
             for (int e = 0; e < 9; ++e) {
-                Jbr[e] = e == 5 ? 0.0 : Lc[((int64_t)54 + f * 9 + e) * ns + s];
                 Drr[e] = e == 5 ? 0.0 : Jdc[(int64_t)e * ns + sr];
-                Jrb[e] = e == 5 ? 0.0 : Lc[((int64_t)fr * 9 + e) * ns + sr];
             }
+            face_block(Lc + lc_at(ns, 1, s) + f * kFaceVals * 64, Jbr);
+            face_block(Lc + lc_at(ns, 0, sr) + fr * kFaceVals * 64, Jrb);
             inv3(Drr, Dr);
             // T = Dr * Jrb;  a -= Jbr * T
             for (int p = 0; p < 3; ++p)
@@ -1871,9 +1890,13 @@ __device__ __forceinline__ void k_j_natural_d(const Blk& wg, DevModel m, const d
     const int64_t cl = (ix + iy + iz) & 1;
     const int64_t s = (iy + m.ny * iz) * nxh + (ix >> 1);
     for (int d = 0; d < 7; ++d) {
-        const double* src = d == 0 ? Jdc + cl * 9 * ns + s : Lc + (cl * 54 + (d - 1) * 9) * ns + s;
+        double B[9];
+        if (d == 0)
+            for (int e = 0; e < 9; ++e) B[e] = e == 5 ? 0.0 : Jdc[(cl * 9 + e) * ns + s];
+        else
+            face_block(Lc + lc_at(ns, cl, s) + (d - 1) * kFaceVals * 64, B);
         for (int e = 0; e < 9; ++e)
-            if (e != 5) J[((int64_t)d * 9 + e) * n + i] = src[(int64_t)e * ns];
+            if (e != 5) J[((int64_t)d * 9 + e) * n + i] = B[e];
     }
 }
 __global__ __launch_bounds__(256) void k_j_natural(DevModel m, const double* __restrict__ Lc,
@@ -1894,6 +1917,15 @@ struct F_k_j_natural {
 __device__ __forceinline__ double ilu_ld(const double* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ float ilu_ld(const float* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ float ilu_ld(const uint16_t* p) { return bf16_to_f32(__builtin_nontemporal_load(p)); }
+
+// s += the stored face block times (a, b, c)
+__device__ __forceinline__ void face_product(const double* v, double a, double b, double c, double& s0, double& s1,
+                                             double& s2) {
+    const double w = ilu_ld(v + 0 * 64) * a + ilu_ld(v + 1 * 64) * b;      // water row, P and S
+    s0 += w + ilu_ld(v + 2 * 64) * c;
+    s1 += ilu_ld(v + 3 * 64) * a + ilu_ld(v + 4 * 64) * b;                 // entry (oil, C) is zero
+    s2 += ilu_ld(v + 5 * 64) * w + ilu_ld(v + 6 * 64) * c;
+}
 
 // Phase 0 (red, forward):   y_r = D_r^{-1} f_r
 // phase 1 (black, forward): y_b = D~_b^{-1} (f_b - sum J_br y_r)
@@ -1925,10 +1957,14 @@ __device__ __forceinline__ void k_ilu_apply_t_d(const Blk& wg, DevModel m, const
             if (!ex[q]) continue;
             const int64_t j = i + off[q];
             const TV a = z[j], b = z[n + j], c = z[2 * n + j];
-            const TL* B = Lc + ((int64_t)colour * 54 + q * 9) * ns + s;
-            s0 += ilu_ld(B + 0 * ns) * a + ilu_ld(B + 1 * ns) * b + ilu_ld(B + 2 * ns) * c;
-            s1 += ilu_ld(B + 3 * ns) * a + ilu_ld(B + 4 * ns) * b;   // entry (oil, C) is zero
-            s2 += ilu_ld(B + 6 * ns) * a + ilu_ld(B + 7 * ns) * b + ilu_ld(B + 8 * ns) * c;
+            if constexpr (sizeof(TL) == 8) {
+                face_product(Lc + lc_at(ns, colour, s) + q * kFaceVals * 64, a, b, c, s0, s1, s2);
+            } else {
+                const TL* B = Lc + ((int64_t)colour * 54 + q * 9) * ns + s;
+                s0 += ilu_ld(B + 0 * ns) * a + ilu_ld(B + 1 * ns) * b + ilu_ld(B + 2 * ns) * c;
+                s1 += ilu_ld(B + 3 * ns) * a + ilu_ld(B + 4 * ns) * b;   // entry (oil, C) is zero
+                s2 += ilu_ld(B + 6 * ns) * a + ilu_ld(B + 7 * ns) * b + ilu_ld(B + 8 * ns) * c;
+            }
         }
         t0 -= s0; t1 -= s1; t2 -= s2;
     }
@@ -1971,11 +2007,12 @@ struct F_k_ilu_apply_t {
 // The red p are not needed at all, and since w_r = v_r the red part of every
 // Krylov vector is a multiple of the first one's (v_r = alpha u), so that the
 // Arnoldi process stores and reads the black cells and wells alone.
-// All four kernels are bound by HBM, by the blocks they stream (276, 560, 532
-// and 524 bytes a cell of their colour).  On 300^3, against the forms that
-// carried the red p and w_r and left B pb to launches of their own:
-// k_stage_red 888 -> 769 us, k_ilu_black_stage 1675 -> 1598, k_ilu_red_spmv
-// 1689 -> 1510, k_black_spmv 1550 -> 1492; on 300 cells two launches fewer of
+// All four kernels are bound by HBM, by the blocks they stream (276, 512, 484
+// and 476 bytes a cell of their colour).  On 300^3, against the forms that
+// carried the red p and w_r and left B pb to launches of their own, and then
+// against face blocks of eight values in planes: k_stage_red 888 -> 769 -> 771
+// us, k_ilu_black_stage 1675 -> 1598 -> 1448, k_ilu_red_spmv 1689 -> 1510 ->
+// 1363, k_black_spmv 1550 -> 1492 -> 1349; on 300 cells two launches fewer of
 // 17 an iteration.
 //
 // The well border, B pb, by way of a cell's entry in pc_map (-1: none).
@@ -2054,16 +2091,18 @@ __device__ __forceinline__ void k_stage_red_d(const Blk& wg, DevModel m, const d
     }
     const double al = *v.alpha;
     const int32_t pc = pc_map[s];
+    const double* Ls = Lc + lc_at(ns, 0, s);
     double t0 = al * v.u[s], t1 = al * v.u[ns + s], t2 = al * v.u[2 * ns + s];
     const bool ex[6] = {ix > 0, ix + 1 < m.nx, iy > 0, iy + 1 < m.ny, iz > 0, iz + 1 < m.nz};
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
         if (!ex[q]) continue;
         const double pj = p[cs_nbr(m, s, ix, q)];
-        const double* Bq = Lc + (int64_t)(q * 9) * ns + s;
-        t0 -= ilu_ld(Bq + 0 * ns) * pj;
-        t1 -= ilu_ld(Bq + 3 * ns) * pj;
-        t2 -= ilu_ld(Bq + 6 * ns) * pj;
+        const double* Lf = Ls + q * kFaceVals * 64;
+        const double w = ilu_ld(Lf + 0 * 64) * pj;
+        t0 -= w;
+        t1 -= ilu_ld(Lf + 3 * 64) * pj;
+        t2 -= ilu_ld(Lf + 5 * 64) * w;
     }
     sub_border(pc_first, perf_well, B, pb, pc, t0, t1, t2);
     const double* D = Dc + s;
@@ -2087,8 +2126,9 @@ struct F_k_stage_red {
     }
 };
 
-// sums of the off-diagonal blocks of one colour's cell times the neighbours' z
-__device__ __forceinline__ void off_diagonal(const DevModel& m, const double* __restrict__ L,
+// sums of the off-diagonal blocks of one colour's cell (Ls: its first value)
+// times the neighbours' z
+__device__ __forceinline__ void off_diagonal(const DevModel& m, const double* __restrict__ Ls,
                                              const double* __restrict__ z, int64_t ns, int64_t s, int64_t ix,
                                              int64_t iy, int64_t iz, double& s0, double& s1, double& s2) {
     const bool ex[6] = {ix > 0, ix + 1 < m.nx, iy > 0, iy + 1 < m.ny, iz > 0, iz + 1 < m.nz};
@@ -2096,11 +2136,7 @@ __device__ __forceinline__ void off_diagonal(const DevModel& m, const double* __
     for (int q = 0; q < 6; ++q) {
         if (!ex[q]) continue;
         const int64_t r = cs_nbr(m, s, ix, q);
-        const double a = z[r], b = z[ns + r], c = z[2 * ns + r];
-        const double* Bq = L + (int64_t)(q * 9) * ns + s;
-        s0 += ilu_ld(Bq + 0 * ns) * a + ilu_ld(Bq + 1 * ns) * b + ilu_ld(Bq + 2 * ns) * c;
-        s1 += ilu_ld(Bq + 3 * ns) * a + ilu_ld(Bq + 4 * ns) * b;       // entry (oil, C) is zero
-        s2 += ilu_ld(Bq + 6 * ns) * a + ilu_ld(Bq + 7 * ns) * b + ilu_ld(Bq + 8 * ns) * c;
+        face_product(Ls + q * kFaceVals * 64, z[r], z[ns + r], z[2 * ns + r], s0, s1, s2);
     }
 }
 
@@ -2129,7 +2165,7 @@ __device__ __forceinline__ void k_ilu_black_stage_d(const Blk& wg, DevModel m, c
     double t1 = v.b[ns + s] - ilu_ld(Jd + 3 * ns) * pi;
     double t2 = v.b[2 * ns + s] - ilu_ld(Jd + 6 * ns) * pi;
     double s0 = 0, s1 = 0, s2 = 0;
-    off_diagonal(m, Lc + 54 * ns, z, ns, s, ix, iy, iz, s0, s1, s2);
+    off_diagonal(m, Lc + lc_at(ns, 1, s), z, ns, s, ix, iy, iz, s0, s1, s2);
     sub_border(pc_first, perf_well, B, pb, pc, t0, t1, t2);
     t0 -= s0;
     t1 -= s1;
@@ -2175,7 +2211,7 @@ __device__ __forceinline__ void k_ilu_red_spmv_d(const Blk& wg, DevModel m, cons
     const int32_t pc = pc_map[s];
     double t0 = al * v.u[s], t1 = al * v.u[ns + s], t2 = al * v.u[2 * ns + s];
     double s0 = 0, s1 = 0, s2 = 0;
-    off_diagonal(m, Lc, z + 3 * ns, ns, s, ix, iy, iz, s0, s1, s2);
+    off_diagonal(m, Lc + lc_at(ns, 0, s), z + 3 * ns, ns, s, ix, iy, iz, s0, s1, s2);
     sub_border(pc_first, perf_well, B, pb, pc, t0, t1, t2);
     t0 -= s0;
     t1 -= s1;
@@ -2247,7 +2283,7 @@ __device__ __forceinline__ void k_black_spmv_d(const Blk& wg, DevModel m, const 
     double y0 = ilu_ld(Jd + 0 * ns) * z0 + ilu_ld(Jd + 1 * ns) * z1 + ilu_ld(Jd + 2 * ns) * z2;
     double y1 = ilu_ld(Jd + 3 * ns) * z0 + ilu_ld(Jd + 4 * ns) * z1;       // entry (oil, C) is zero
     double y2 = ilu_ld(Jd + 6 * ns) * z0 + ilu_ld(Jd + 7 * ns) * z1 + ilu_ld(Jd + 8 * ns) * z2;
-    off_diagonal(m, Lc + 54 * ns, z, ns, s, ix, iy, iz, y0, y1, y2);
+    off_diagonal(m, Lc + lc_at(ns, 1, s), z, ns, s, ix, iy, iz, y0, y1, y2);
     y0 = -y0; y1 = -y1; y2 = -y2;
     sub_border(pc_first, perf_well, B, pb, pc, y0, y1, y2);
     w[s] = -y0;
@@ -2619,7 +2655,7 @@ void cpr_plan(Sim& s, Bump& b) {
     const int64_t ns = ilu_slot_count(s.m);
     // block Jacobi: 9 natural planes; ILU: 2 colours x 9 planes of ns slots (>= 9N)
     s.Dinv = b.take<double>(ilu ? 18 * ns : 9 * s.m.n);
-    s.Lc = (ilu && !mixed) ? b.take<double>(108 * ns) : nullptr;
+    s.Lc = (ilu && !mixed) ? b.take<double>(2 * lc_colour(ns)) : nullptr;
     s.Jdc = (ilu && !mixed) ? b.take<double>(18 * ns) : nullptr;
     if (mixed) {
         s.coarse_inv32 = b.take<float>((size_t)nc * nc);

@@ -211,11 +211,12 @@ __device__ __forceinline__ void accumulation(const DevModel& m, const CellP& p, 
 // Face flux (kg/s, L -> R, Sec. 3.2) and its derivatives w.r.t. the
 // unknowns of the two cells.  dA: derivatives w.r.t. cell "a" (the cell
 // doing the gather), dB: w.r.t. the neighbour "b".  aIsL tells which of the
-// two is the lower-index cell L.  Derivative arrays are [eq*3 + var].
+// two is the lower-index cell L.  Derivative arrays are [eq*3 + var].  g: the
+// factor of the polymer's P and S derivatives to the water's.
 __device__ __forceinline__ void face_flux(const DevModel& m, double T, double wL, double gdz, bool aIsL,
                                           double Pa, double Ca, const CellP& a,
                                           double Pb, double Cb, const CellP& b,
-                                          double F[3], double dA[9], double dB[9]) {
+                                          double F[3], double dA[9], double dB[9], double& g) {
     // orient: L/R quantities
     const double PL = aIsL ? Pa : Pb, PR = aIsL ? Pb : Pa;
     const double wR = 1.0 - wL;
@@ -282,6 +283,7 @@ __device__ __forceinline__ void face_flux(const DevModel& m, double T, double wL
     const double mp = krw * irk * imup;
     const double cf = Cup * m.inv_rho_w0;
     F[2] = Gw * mp * cf;
+    g = cf * muw * imup;
     dA[6] = -T * mp * cf * (wa * a.drw * dpw + rw * ddpw_a);
     dB[6] = -T * mp * cf * (wb * b.drw * dpw + rw * ddpw_b);
     const double dmp_S = Gw * cf * dkrw * irk * imup;
@@ -418,7 +420,7 @@ __device__ __forceinline__ void k_assemble_d(const Blk& wg, DevModel m, const do
     // colour-split storage that the smoother and the product stream, instead of
     // the natural-order planes of J: cell colour (ix+iy+iz)&1, slot
     // (iy + ny*iz)*ceil(nx/2) + ix/2; diagonal blocks in Jdcs (9 planes per
-    // colour), face f's block in Lcs (54 planes per colour).  The threads are
+    // colour), face f's block in Lcs (lc_at).  The threads are
     // then colour-major: a wavefront takes 64 consecutive slots of one colour
     // and the next one the same slots of the other colour, so that every store
     // into that storage is one whole run and the pair reads the same lines of
@@ -492,26 +494,33 @@ __device__ __forceinline__ void k_assemble_d(const Blk& wg, DevModel m, const do
             face_geom(f + 1, ex_n, j_n, T_n, lo_n);
             nP = x[j_n]; nS = x[n + j_n]; nC = x[2 * n + j_n]; npv = pvr[j_n]; nT = T_n[lo_n];
         }
-        // entry e of face f's block: natural-order plane, or the colour-split copy
-        double* Jd = cs ? Lcs + (cl * 54 + f * 9) * nsl + sl : J + (int64_t)(f + 1) * 9 * n + i;
-        const int64_t je = cs ? nsl : n;
+        // entry e of face f's block: natural-order plane; or the colour-split copy's values
+        double* Jd = J + (int64_t)(f + 1) * 9 * n + i;
+        double* Lf = cs ? Lcs + lc_at(nsl, cl, sl) + f * kFaceVals * 64 : nullptr;
         if (!exists) {
-            if (with_jac)
+            if (with_jac && cs)
+                for (int v = 0; v < kFaceVals; ++v) __builtin_nontemporal_store(0.0, &Lf[v * 64]);
+            else if (with_jac)
                 for (int e = 0; e < 9; ++e)
-                    if (e != 5) __builtin_nontemporal_store(0.0, &Jd[e * je]);
+                    if (e != 5) __builtin_nontemporal_store(0.0, &Jd[e * n]);
             continue;
         }
         const double wL = (plus ? pv : pvj) * rcp_nr(pv + pvj);
         const double gdz = ((f >> 1) == 2) ? m.grav * m.dz : 0.0;
         const CellP b = cell_props<VAR>(m, pvj * m.inv_vol, Pj, Sj, Cj, j);
-        double F[3], dA[9], dB[9];
-        face_flux(m, T, wL, gdz, plus, P, C, a, Pj, Cj, b, F, dA, dB);
+        double F[3], dA[9], dB[9], g;
+        face_flux(m, T, wL, gdz, plus, P, C, a, Pj, Cj, b, F, dA, dB, g);
         const double sg = plus ? dt : -dt;               // outflow from L, inflow to R
         for (int e = 0; e < 3; ++e) r[e] += sg * F[e];
         for (int e = 0; e < 9; ++e) jd[e] += sg * dA[e];
-        if (with_jac)
+        if (with_jac && cs) {
+            for (int e = 0; e < 5; ++e) __builtin_nontemporal_store(sg * dB[e] * sc[e / 3], &Lf[e * 64]);
+            __builtin_nontemporal_store(g * (m.rho_w0 * m.inv_c_ref), &Lf[5 * 64]);
+            __builtin_nontemporal_store(sg * dB[8] * sc[2], &Lf[6 * 64]);
+        } else if (with_jac) {
             for (int e = 0; e < 9; ++e)
-                if (e != 5) __builtin_nontemporal_store(sg * dB[e] * sc[e / 3], &Jd[e * je]);
+                if (e != 5) __builtin_nontemporal_store(sg * dB[e] * sc[e / 3], &Jd[e * n]);
+        }
     }
     for (int e = 0; e < 3; ++e) __builtin_nontemporal_store(r[e] * sc[e], &R[e * n + i]);
     double* J0 = cs ? Jdcs + cl * 9 * nsl + sl : J + i;

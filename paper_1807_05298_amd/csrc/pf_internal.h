@@ -255,7 +255,7 @@ struct Sim {
     double *coarse_inv_t;            // ... and transposed
     float *coarse_inv_t32;
     float *Jp32;                     // mixed: FP32 P-columns of J (21 planes)
-    double *Lc;                      // FP64 ILU: colour-split off-diagonal blocks (2 x 54 planes)
+    double *Lc;                      // FP64 ILU: colour-split off-diagonal blocks (lc_at)
     double *Jdc;                     // FP64 ILU: colour-split diagonal blocks of J (2 x 9 planes)
     uint16_t *Joff16;                // mixed ILU: colour-split BF16 off-diagonal blocks (2 x 54 planes)
     float *Dinv32;                   // mixed: FP32 smoother inverse diagonals
@@ -470,6 +470,24 @@ __device__ __forceinline__ int64_t cs_index(const DevModel& m, int64_t i) {
     const int64_t iy = rem / m.nx;
     const int64_t ix = rem - iy * m.nx;
     return ((ix + iy + iz) & 1) * 3 * cs_ns(m) + (iy + m.ny * iz) * ((m.nx + 1) >> 1) + (ix >> 1);
+}
+
+// Storage of the off-diagonal blocks in that order (Lc).  Of a face's block,
+// rows water, oil, polymer by columns P, S, C, the entry (oil, C) is zero, and
+// as the polymer travels with the water the polymer row's P and S entries are
+// those of the water row times one factor g (the upstream concentration, the
+// viscosities' ratio and the rows' scales).  So kFaceVals values are kept:
+// water P, S, C, oil P, S, g and polymer C.  They lie in blocks of 64 slots,
+// all faces' values of a block together: a wavefront reads one run of 21.5 KB
+// instead of 42 runs of 512 bytes in as many pages (reads of 48 values a slot
+// alone: 5.55 TB/s for 5.26).  On 300^3, against eight values in planes: the
+// assembly 3.34 ms for 3.95, k_ilu_diag 2.71 for 3.03, the smoother's and the
+// product's kernels 9-10 % less.  Value v of face q of a slot is at
+// lc_at(...) + (q kFaceVals + v) 64.
+constexpr int kFaceVals = 7;
+__host__ __device__ __forceinline__ int64_t lc_colour(int64_t ns) { return (ns + 63) / 64 * (64 * 6 * kFaceVals); }
+__device__ __forceinline__ int64_t lc_at(int64_t ns, int64_t colour, int64_t s) {
+    return colour * lc_colour(ns) + (s >> 6) * (64 * 6 * kFaceVals) + (s & 63);
 }
 
 // XCD-aware block order: workgroups are dispatched round-robin over the 8
