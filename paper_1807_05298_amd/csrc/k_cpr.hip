@@ -1914,17 +1914,22 @@ struct F_k_j_natural {
 // Factor loads are streamed (each off-diagonal block is read once per
 // application): non-temporal, so they do not evict the vectors and the
 // P-columns of J that the stage residual has just brought into the caches.
-__device__ __forceinline__ double ilu_ld(const double* p) { return __builtin_nontemporal_load(p); }
-__device__ __forceinline__ float ilu_ld(const float* p) { return __builtin_nontemporal_load(p); }
+// (NT false: a model small enough for its blocks to stay in the memory-side
+// cache, stream_past_caches.)
+template <bool NT = true> __device__ __forceinline__ double ilu_ld(const double* p) {
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
 __device__ __forceinline__ float ilu_ld(const uint16_t* p) { return bf16_to_f32(__builtin_nontemporal_load(p)); }
 
 // s += the stored face block times (a, b, c)
+template <bool NT>
 __device__ __forceinline__ void face_product(const double* v, double a, double b, double c, double& s0, double& s1,
                                              double& s2) {
-    const double w = ilu_ld(v + 0 * 64) * a + ilu_ld(v + 1 * 64) * b;      // water row, P and S
-    s0 += w + ilu_ld(v + 2 * 64) * c;
-    s1 += ilu_ld(v + 3 * 64) * a + ilu_ld(v + 4 * 64) * b;                 // entry (oil, C) is zero
-    s2 += ilu_ld(v + 5 * 64) * w + ilu_ld(v + 6 * 64) * c;
+    const double w = ilu_ld<NT>(v + 0 * 64) * a + ilu_ld<NT>(v + 1 * 64) * b;      // water row, P and S
+    s0 += w + ilu_ld<NT>(v + 2 * 64) * c;
+    s1 += ilu_ld<NT>(v + 3 * 64) * a + ilu_ld<NT>(v + 4 * 64) * b;                 // entry (oil, C) is zero
+    s2 += ilu_ld<NT>(v + 5 * 64) * w + ilu_ld<NT>(v + 6 * 64) * c;
 }
 
 // Phase 0 (red, forward):   y_r = D_r^{-1} f_r
@@ -1954,11 +1959,12 @@ __device__ __forceinline__ void k_ilu_apply_t_d(const Blk& wg, DevModel m, const
         TV s0 = 0, s1 = 0, s2 = 0;
 #pragma unroll
         for (int q = 0; q < 6; ++q) {
-            if (!ex[q]) continue;
-            const int64_t j = i + off[q];
-            const TV a = z[j], b = z[n + j], c = z[2 * n + j];
+            // (a missing neighbour's block is zero, and its load comes from the cell itself)
+            const int64_t j = ex[q] ? i + off[q] : i;
+            const TV za = z[j], zb = z[n + j], zc = z[2 * n + j];
+            const TV a = ex[q] ? za : (TV)0, b = ex[q] ? zb : (TV)0, c = ex[q] ? zc : (TV)0;
             if constexpr (sizeof(TL) == 8) {
-                face_product(Lc + lc_at(ns, colour, s) + q * kFaceVals * 64, a, b, c, s0, s1, s2);
+                face_product<true>(Lc + lc_at(ns, colour, s) + q * kFaceVals * 64, a, b, c, s0, s1, s2);
             } else {
                 const TL* B = Lc + ((int64_t)colour * 54 + q * 9) * ns + s;
                 s0 += ilu_ld(B + 0 * ns) * a + ilu_ld(B + 1 * ns) * b + ilu_ld(B + 2 * ns) * c;
@@ -2074,6 +2080,7 @@ struct F_k_pc_map_cs {
 };
 
 // z^f_r on the red slots.
+template <bool NT>
 __device__ __forceinline__ void k_stage_red_d(const Blk& wg, DevModel m, const double* __restrict__ Lc,
                                               const double* __restrict__ Dc, CsVec v, const double* __restrict__ p,
                                               const double* __restrict__ pb, const double* __restrict__ B,
@@ -2096,13 +2103,12 @@ __device__ __forceinline__ void k_stage_red_d(const Blk& wg, DevModel m, const d
     const bool ex[6] = {ix > 0, ix + 1 < m.nx, iy > 0, iy + 1 < m.ny, iz > 0, iz + 1 < m.nz};
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
-        if (!ex[q]) continue;
-        const double pj = p[cs_nbr(m, s, ix, q)];
+        const double pq = p[ex[q] ? cs_nbr(m, s, ix, q) : s], pj = ex[q] ? pq : 0.0;
         const double* Lf = Ls + q * kFaceVals * 64;
-        const double w = ilu_ld(Lf + 0 * 64) * pj;
+        const double w = ilu_ld<NT>(Lf + 0 * 64) * pj;
         t0 -= w;
-        t1 -= ilu_ld(Lf + 3 * 64) * pj;
-        t2 -= ilu_ld(Lf + 5 * 64) * w;
+        t1 -= ilu_ld<NT>(Lf + 3 * 64) * pj;
+        t2 -= ilu_ld<NT>(Lf + 5 * 64) * w;
     }
     sub_border(pc_first, perf_well, B, pb, pc, t0, t1, t2);
     const double* D = Dc + s;
@@ -2110,37 +2116,44 @@ __device__ __forceinline__ void k_stage_red_d(const Blk& wg, DevModel m, const d
     z[ns + s] = D[3 * ns] * t0 + D[4 * ns] * t1 + D[5 * ns] * t2;
     z[2 * ns + s] = D[6 * ns] * t0 + D[7 * ns] * t1 + D[8 * ns] * t2;
 }
+template <bool NT>
 __global__ __launch_bounds__(256) void k_stage_red(DevModel m, const double* __restrict__ Lc,
                                                    const double* __restrict__ Dc, CsVec v,
                                                    const double* __restrict__ p, const double* __restrict__ pb,
                                                    const double* __restrict__ B, const int32_t* __restrict__ pc_map,
                                                    const int32_t* __restrict__ pc_first,
                                                    const int32_t* __restrict__ perf_well, double* __restrict__ z) {
-    k_stage_red_d(PF_BLK, m, Lc, Dc, v, p, pb, B, pc_map, pc_first, perf_well, z);
+    k_stage_red_d<NT>(PF_BLK, m, Lc, Dc, v, p, pb, B, pc_map, pc_first, perf_well, z);
 }
+template <bool NT>
 struct F_k_stage_red {
     static constexpr int kLB = 256;
     template <class... A>
     __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
-        k_stage_red_d(wg, a...);
+        k_stage_red_d<NT>(wg, a...);
     }
 };
 
 // sums of the off-diagonal blocks of one colour's cell (Ls: its first value)
-// times the neighbours' z
+// times the neighbours' z.  Branch-free, so that all six blocks' loads issue
+// together (2-3 % less time on 300^3, 3-7 % on 1.1M cells than with a branch a
+// face): a missing neighbour's block is stored as zeros, and its z is taken
+// from the slot itself and masked.
+template <bool NT>
 __device__ __forceinline__ void off_diagonal(const DevModel& m, const double* __restrict__ Ls,
                                              const double* __restrict__ z, int64_t ns, int64_t s, int64_t ix,
                                              int64_t iy, int64_t iz, double& s0, double& s1, double& s2) {
     const bool ex[6] = {ix > 0, ix + 1 < m.nx, iy > 0, iy + 1 < m.ny, iz > 0, iz + 1 < m.nz};
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
-        if (!ex[q]) continue;
-        const int64_t r = cs_nbr(m, s, ix, q);
-        face_product(Ls + q * kFaceVals * 64, z[r], z[ns + r], z[2 * ns + r], s0, s1, s2);
+        const int64_t r = ex[q] ? cs_nbr(m, s, ix, q) : s;
+        const double a = z[r], b = z[ns + r], c = z[2 * ns + r];
+        face_product<NT>(Ls + q * kFaceVals * 64, ex[q] ? a : 0.0, ex[q] ? b : 0.0, ex[q] ? c : 0.0, s0, s1, s2);
     }
 }
 
 // z_b on the black slots, from z^f on the red ones.
+template <bool NT>
 __device__ __forceinline__ void k_ilu_black_stage_d(const Blk& wg, DevModel m, const double* __restrict__ Lc,
                                                     const double* __restrict__ Jdc, const double* __restrict__ Dc,
                                                     CsVec v, const double* __restrict__ p,
@@ -2161,11 +2174,11 @@ __device__ __forceinline__ void k_ilu_black_stage_d(const Blk& wg, DevModel m, c
     const double pi = p[s];
     const int32_t pc = pc_map[ns + s];
     const double* Jd = Jdc + 9 * ns + s;
-    double t0 = v.b[s] - ilu_ld(Jd + 0 * ns) * pi;
-    double t1 = v.b[ns + s] - ilu_ld(Jd + 3 * ns) * pi;
-    double t2 = v.b[2 * ns + s] - ilu_ld(Jd + 6 * ns) * pi;
+    double t0 = v.b[s] - ilu_ld<NT>(Jd + 0 * ns) * pi;
+    double t1 = v.b[ns + s] - ilu_ld<NT>(Jd + 3 * ns) * pi;
+    double t2 = v.b[2 * ns + s] - ilu_ld<NT>(Jd + 6 * ns) * pi;
     double s0 = 0, s1 = 0, s2 = 0;
-    off_diagonal(m, Lc + lc_at(ns, 1, s), z, ns, s, ix, iy, iz, s0, s1, s2);
+    off_diagonal<NT>(m, Lc + lc_at(ns, 1, s), z, ns, s, ix, iy, iz, s0, s1, s2);
     sub_border(pc_first, perf_well, B, pb, pc, t0, t1, t2);
     t0 -= s0;
     t1 -= s1;
@@ -2175,6 +2188,7 @@ __device__ __forceinline__ void k_ilu_black_stage_d(const Blk& wg, DevModel m, c
     zb[ns + s] = D[3 * ns] * t0 + D[4 * ns] * t1 + D[5 * ns] * t2;
     zb[2 * ns + s] = D[6 * ns] * t0 + D[7 * ns] * t1 + D[8 * ns] * t2;
 }
+template <bool NT>
 __global__ __launch_bounds__(256) void k_ilu_black_stage(DevModel m, const double* __restrict__ Lc,
                                                          const double* __restrict__ Jdc,
                                                          const double* __restrict__ Dc, CsVec v,
@@ -2184,17 +2198,19 @@ __global__ __launch_bounds__(256) void k_ilu_black_stage(DevModel m, const doubl
                                                          const int32_t* __restrict__ pc_first,
                                                          const int32_t* __restrict__ perf_well,
                                                          double* __restrict__ z) {
-    k_ilu_black_stage_d(PF_BLK, m, Lc, Jdc, Dc, v, p, pb, B, pc_map, pc_first, perf_well, z);
+    k_ilu_black_stage_d<NT>(PF_BLK, m, Lc, Jdc, Dc, v, p, pb, B, pc_map, pc_first, perf_well, z);
 }
+template <bool NT>
 struct F_k_ilu_black_stage {
     static constexpr int kLB = 256;
     template <class... A>
     __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
-        k_ilu_black_stage_d(wg, a...);
+        k_ilu_black_stage_d<NT>(wg, a...);
     }
 };
 
 // z_r on the red slots, from z_b (the red rows of J z are then v_r).
+template <bool NT>
 __device__ __forceinline__ void k_ilu_red_spmv_d(const Blk& wg, DevModel m, const double* __restrict__ Lc,
                                                  const double* __restrict__ Dc, CsVec v,
                                                  const double* __restrict__ pb, const double* __restrict__ B,
@@ -2211,7 +2227,7 @@ __device__ __forceinline__ void k_ilu_red_spmv_d(const Blk& wg, DevModel m, cons
     const int32_t pc = pc_map[s];
     double t0 = al * v.u[s], t1 = al * v.u[ns + s], t2 = al * v.u[2 * ns + s];
     double s0 = 0, s1 = 0, s2 = 0;
-    off_diagonal(m, Lc + lc_at(ns, 0, s), z + 3 * ns, ns, s, ix, iy, iz, s0, s1, s2);
+    off_diagonal<NT>(m, Lc + lc_at(ns, 0, s), z + 3 * ns, ns, s, ix, iy, iz, s0, s1, s2);
     sub_border(pc_first, perf_well, B, pb, pc, t0, t1, t2);
     t0 -= s0;
     t1 -= s1;
@@ -2221,6 +2237,7 @@ __device__ __forceinline__ void k_ilu_red_spmv_d(const Blk& wg, DevModel m, cons
     z[ns + s] = D[3 * ns] * t0 + D[4 * ns] * t1 + D[5 * ns] * t2;
     z[2 * ns + s] = D[6 * ns] * t0 + D[7 * ns] * t1 + D[8 * ns] * t2;
 }
+template <bool NT>
 __global__ __launch_bounds__(256) void k_ilu_red_spmv(DevModel m, const double* __restrict__ Lc,
                                                       const double* __restrict__ Dc, CsVec v,
                                                       const double* __restrict__ pb, const double* __restrict__ B,
@@ -2228,19 +2245,21 @@ __global__ __launch_bounds__(256) void k_ilu_red_spmv(DevModel m, const double* 
                                                       const int32_t* __restrict__ pc_first,
                                                       const int32_t* __restrict__ perf_well,
                                                       double* __restrict__ z) {
-    k_ilu_red_spmv_d(PF_BLK, m, Lc, Dc, v, pb, B, pc_map, pc_first, perf_well, z);
+    k_ilu_red_spmv_d<NT>(PF_BLK, m, Lc, Dc, v, pb, B, pc_map, pc_first, perf_well, z);
 }
+template <bool NT>
 struct F_k_ilu_red_spmv {
     static constexpr int kLB = 256;
     template <class... A>
     __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
-        k_ilu_red_spmv_d(wg, a...);
+        k_ilu_red_spmv_d<NT>(wg, a...);
     }
 };
 
 // w_b = J_bb z_b + sum J_br z_r + B pb on the black slots (blocks [0, ncb));
 // in the nw blocks after those the well entries z_w = pb and the well rows
 // w_w = sum C z_cell + D pb, one wavefront per well.
+template <bool NT>
 __device__ __forceinline__ void k_black_spmv_d(const Blk& wg, DevModel m, const double* __restrict__ Lc,
                                                const double* __restrict__ Jdc, const double* __restrict__ pb,
                                                const double* __restrict__ B, const int32_t* __restrict__ pc_map,
@@ -2280,16 +2299,17 @@ __device__ __forceinline__ void k_black_spmv_d(const Blk& wg, DevModel m, const 
     const double z0 = zb[s], z1 = zb[ns + s], z2 = zb[2 * ns + s];
     const int32_t pc = pc_map[ns + s];
     const double* Jd = Jdc + 9 * ns + s;
-    double y0 = ilu_ld(Jd + 0 * ns) * z0 + ilu_ld(Jd + 1 * ns) * z1 + ilu_ld(Jd + 2 * ns) * z2;
-    double y1 = ilu_ld(Jd + 3 * ns) * z0 + ilu_ld(Jd + 4 * ns) * z1;       // entry (oil, C) is zero
-    double y2 = ilu_ld(Jd + 6 * ns) * z0 + ilu_ld(Jd + 7 * ns) * z1 + ilu_ld(Jd + 8 * ns) * z2;
-    off_diagonal(m, Lc + lc_at(ns, 1, s), z, ns, s, ix, iy, iz, y0, y1, y2);
+    double y0 = ilu_ld<NT>(Jd + 0 * ns) * z0 + ilu_ld<NT>(Jd + 1 * ns) * z1 + ilu_ld<NT>(Jd + 2 * ns) * z2;
+    double y1 = ilu_ld<NT>(Jd + 3 * ns) * z0 + ilu_ld<NT>(Jd + 4 * ns) * z1;       // entry (oil, C) is zero
+    double y2 = ilu_ld<NT>(Jd + 6 * ns) * z0 + ilu_ld<NT>(Jd + 7 * ns) * z1 + ilu_ld<NT>(Jd + 8 * ns) * z2;
+    off_diagonal<NT>(m, Lc + lc_at(ns, 1, s), z, ns, s, ix, iy, iz, y0, y1, y2);
     y0 = -y0; y1 = -y1; y2 = -y2;
     sub_border(pc_first, perf_well, B, pb, pc, y0, y1, y2);
     w[s] = -y0;
     w[ns + s] = -y1;
     w[2 * ns + s] = -y2;
 }
+template <bool NT>
 __global__ __launch_bounds__(256) void k_black_spmv(DevModel m, const double* __restrict__ Lc,
                                                     const double* __restrict__ Jdc, const double* __restrict__ pb,
                                                     const double* __restrict__ B, const int32_t* __restrict__ pc_map,
@@ -2300,14 +2320,15 @@ __global__ __launch_bounds__(256) void k_black_spmv(DevModel m, const double* __
                                                     const int32_t* __restrict__ wp_idx, const double* __restrict__ Cw,
                                                     const double* __restrict__ Dw, int ncb, double* __restrict__ z,
                                                     double* __restrict__ w) {
-    k_black_spmv_d(PF_BLK, m, Lc, Jdc, pb, B, pc_map, pc_first, perf_well, perf_cell, wp_first, wp_idx, Cw, Dw, ncb, z,
+    k_black_spmv_d<NT>(PF_BLK, m, Lc, Jdc, pb, B, pc_map, pc_first, perf_well, perf_cell, wp_first, wp_idx, Cw, Dw, ncb, z,
                    w);
 }
+template <bool NT>
 struct F_k_black_spmv {
     static constexpr int kLB = 256;
     template <class... A>
     __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
-        k_black_spmv_d(wg, a...);
+        k_black_spmv_d<NT>(wg, a...);
     }
 };
 
@@ -3133,37 +3154,45 @@ void cpr_apply_spmv(Sim& s, const double* v, double* z, double* w) {
     launch_spmv(s, z, w);
 }
 
-// The same in the colour-split layout (PF order, red-black ILU(0)); of w the
-// black rows and the wells: the red rows are those of v.
-void cpr_apply_spmv(Sim& s, const CsVec& v, double* z, double* w) {
+namespace {
+template <bool NT>
+void colour_split_apply(Sim& s, const CsVec& v, double* z, double* w) {
     const DevModel& m = s.m;
     const double* p = pressure_cycles<double>(s, nullptr, &v);
     const int ncb = (int)grid_for(ilu_slot_count(m));
     {
         ProfScope ps(s, PF_K_STAGE_RESID);
-        launch<F_k_stage_red>(s, s.stream, k_stage_red, dim3(ncb), dim3(kBlock), 0, m, s.Lc, s.Dinv, v, p, s.pb, s.B,
+        launch<F_k_stage_red<NT>>(s, s.stream, k_stage_red<NT>, dim3(ncb), dim3(kBlock), 0, m, s.Lc, s.Dinv, v, p, s.pb, s.B,
                               s.pc_map_cs, s.pc_first, s.perf_well, z);
         PF_LAUNCH_CHECK();
     }
     {
         ProfScope ps(s, PF_K_ILU);
-        launch<F_k_ilu_black_stage>(s, s.stream, k_ilu_black_stage, dim3(ncb), dim3(kBlock), 0, m, s.Lc, s.Jdc,
+        launch<F_k_ilu_black_stage<NT>>(s, s.stream, k_ilu_black_stage<NT>, dim3(ncb), dim3(kBlock), 0, m, s.Lc, s.Jdc,
                                     s.Dinv, v, p, s.pb, s.B, s.pc_map_cs, s.pc_first, s.perf_well, z);
         PF_LAUNCH_CHECK();
     }
     {
         ProfScope ps(s, PF_K_RED_SPMV);
-        launch<F_k_ilu_red_spmv>(s, s.stream, k_ilu_red_spmv, dim3(ncb), dim3(kBlock), 0, m, s.Lc, s.Dinv, v, s.pb,
+        launch<F_k_ilu_red_spmv<NT>>(s, s.stream, k_ilu_red_spmv<NT>, dim3(ncb), dim3(kBlock), 0, m, s.Lc, s.Dinv, v, s.pb,
                                  s.B, s.pc_map_cs, s.pc_first, s.perf_well, z);
         PF_LAUNCH_CHECK();
     }
     {
         ProfScope ps(s, PF_K_BLACK_SPMV);
-        launch<F_k_black_spmv>(s, s.stream, k_black_spmv, dim3(ncb + m.nw), dim3(kBlock), 0, m, s.Lc, s.Jdc, s.pb, s.B,
+        launch<F_k_black_spmv<NT>>(s, s.stream, k_black_spmv<NT>, dim3(ncb + m.nw), dim3(kBlock), 0, m, s.Lc, s.Jdc, s.pb, s.B,
                                s.pc_map_cs, s.pc_first, s.perf_well, s.perf_cell, s.wp_first, s.wp_idx, s.Cw, s.Dw,
                                ncb, z, w);
         PF_LAUNCH_CHECK();
     }
+}
+}  // namespace
+
+// The same in the colour-split layout (PF order, red-black ILU(0)); of w the
+// black rows and the wells: the red rows are those of v.
+void cpr_apply_spmv(Sim& s, const CsVec& v, double* z, double* w) {
+    if (stream_past_caches(2 * lc_colour(ilu_slot_count(s.m)) * (int64_t)sizeof(double))) colour_split_apply<true>(s, v, z, w);
+    else colour_split_apply<false>(s, v, z, w);
 }
 
 // Mixed precision: FP32 multigrid and stage residual, BF16/FP32 smoother,

@@ -490,6 +490,14 @@ __device__ __forceinline__ int64_t lc_at(int64_t ns, int64_t colour, int64_t s) 
     return colour * lc_colour(ns) + (s >> 6) * (64 * 6 * kFaceVals) + (s & 63);
 }
 
+// Whether kernels stream J past the caches (non-temporal loads): where a copy
+// of bytes bytes does not stay in the 256 MB memory-side cache from one of
+// them to the next, so that it would only push out the vectors.  Measured, the
+// four kernels of an iteration in us, streamed / not: 394k cells (copy of 132
+// MB) 71.4 / 63.1, 648k (218 MB) 100.8 / 105.4, 2M 314 / 337, 5.2M 894 / 942,
+// 13.5M 2407 / 2401, 27M 4847 / 4810.
+inline bool stream_past_caches(int64_t bytes) { return bytes > ((int64_t)160 << 20); }
+
 // XCD-aware block order: workgroups are dispatched round-robin over the 8
 // XCDs (each with its own L2); renumbering them so that XCD x processes one
 // contiguous range of blocks keeps stencil neighbours in the same L2.
