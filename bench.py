@@ -35,7 +35,7 @@ KERNEL_BYTES = {
     # in natural order)
     "assemble": ("PF_K_ASSEMBLE", 1, 504),
     # the (oil, C) entry of every block of J is zero and not read: 8 of 9 entries per block
-    "spmv": ("PF_K_SPMV", 2, 496),                # J 448 + x 24 in; y 24 out (x FP32 in mixed: 484)
+    "spmv": ("PF_K_SPMV", 2, 500),                # J 448 + x 24 + border map 4 in; y 24 out (x FP32 in mixed: 488)
     "zline": ("PF_K_ZLINE", 3, None),             # level-0 half-sweep, per active column set (below)
     "ilu": ("PF_K_ILU", 6, None),
     # last ILU phase (after which the red rows of w = J z are those of v): Lc 336 + inverse diagonal 72

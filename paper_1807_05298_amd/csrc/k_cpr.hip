@@ -3118,8 +3118,7 @@ void cpr_apply(Sim& s, const double* v, double* z) {
     } else {
         // Algorithm 2: y = S(v); r = v - J y; y += Pi_p M_g^{-1} Pi_r r
         smoother_apply(s, v, z);
-        launch_spmv(s, z, s.t2);
-        launch_axpby(s, s.nv, 1.0, v, -1.0, s.t2);
+        launch_residual(s, v, z, s.t2);
         const double* p = pressure_stage<double>(s, s.t2);
         launch<F_k_add_pressure<double>>(s, s.stream, k_add_pressure<double>, dim3(grid_for(m.n + m.nw)),
                                          dim3(kBlock), 0, m.n, m.nw, p, s.pb, z);
@@ -3232,8 +3231,7 @@ void cpr_apply(Sim& s, const double* v, float* z) {
     } else {
         cast(s, s.nv, v, s.t32);
         smoother_apply_m(s, s.t32, z);
-        launch_spmv(s, z, s.t2);
-        launch_axpby(s, s.nv, 1.0, v, -1.0, s.t2);
+        launch_residual(s, v, z, s.t2);
         const float* p = pressure_stage<float>(s, s.t2);
         launch<F_k_add_pressure<float>>(s, s.stream, k_add_pressure<float>, dim3(grid_for(m.n + m.nw)), dim3(kBlock),
                                         0, m.n, m.nw, p, s.pb, z);

@@ -24,16 +24,13 @@ template <bool NT> __device__ __forceinline__ double jld(const double* p) {
 // those 7 planes are not read.  x may be FP32 (the preconditioned vectors of the mixed-precision mode);
 // the product is FP64.
 template <class TX, bool NT>
-__device__ __forceinline__ void k_spmv_d(const Blk& wg, DevModel m, const double* __restrict__ J,
-                                         const TX* __restrict__ x, double* __restrict__ y) {
-    const int64_t i = xcd_block(wg) * blockDim.x + threadIdx.x;
-    if (i >= m.n) return;
+__device__ __forceinline__ void j_row(const DevModel& m, const double* __restrict__ J, const TX* __restrict__ x,
+                                      int64_t i, double& y0, double& y1, double& y2) {
     const int64_t n = m.n;
     const int64_t iz = i / m.nxy;
     const int64_t rem = i - iz * m.nxy;
     const int64_t iy = rem / m.nx;
     const int64_t ix = rem - iy * m.nx;
-    double y0, y1, y2;
     {
         const double a = (double)x[i], b = (double)x[n + i], c = (double)x[2 * n + i];
         y0 = jld<NT>(J + 0 * n + i) * a + jld<NT>(J + 1 * n + i) * b + jld<NT>(J + 2 * n + i) * c;
@@ -53,14 +50,69 @@ __device__ __forceinline__ void k_spmv_d(const Blk& wg, DevModel m, const double
         y1 += jld<NT>(B + 3 * n) * a + jld<NT>(B + 4 * n) * b;
         y2 += jld<NT>(B + 6 * n) * a + jld<NT>(B + 7 * n) * b + jld<NT>(B + 8 * n) * c;
     }
-    y[i] = y0;
-    y[n + i] = y1;
-    y[2 * n + i] = y2;
+}
+// With the well border: a perforated cell, found through pc_map, adds B * Pb;
+// the nw blocks after the cells' ncb take the well rows, sum C * x_cell + D *
+// Pb (lanes over the perforations, fixed-order shuffle reduction).  v given:
+// y = v - J x.  One launch for what were up to three: on 300k cells 24.9 us for
+// 23.7 + 4.5 (the border's own launch) + 5.2 (the difference's).
+template <class TX, bool NT>
+__device__ __forceinline__ void k_spmv_d(const Blk& wg, DevModel m, int ncb, const double* __restrict__ J,
+                                         const int32_t* __restrict__ pc_map, const int32_t* __restrict__ pc_first,
+                                         const int32_t* __restrict__ perf_well,
+                                         const int32_t* __restrict__ perf_cell,
+                                         const int32_t* __restrict__ wp_first, const int32_t* __restrict__ wp_idx,
+                                         const double* __restrict__ B, const double* __restrict__ Cw,
+                                         const double* __restrict__ Dw, const TX* __restrict__ x,
+                                         const double* __restrict__ v, double* __restrict__ y) {
+    const int64_t n = m.n;
+    if ((int)wg.x >= ncb) {
+        const int w = (int)wg.x - ncb;
+        if (threadIdx.x >= 64) return;
+        double s = 0.0;
+        for (int k = wp_first[w] + (int)threadIdx.x; k < wp_first[w + 1]; k += 64) {
+            const int p = wp_idx[k];
+            const int64_t c = perf_cell[p];
+            s += Cw[3 * p] * (double)x[c] + Cw[3 * p + 1] * (double)x[n + c] + Cw[3 * p + 2] * (double)x[2 * n + c];
+        }
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+        if (threadIdx.x == 0) {
+            const double yw = s + Dw[w] * (double)x[3 * n + w];
+            y[3 * n + w] = v ? v[3 * n + w] - yw : yw;
+        }
+        return;
+    }
+    const int64_t i = xcd_block(Blk{wg.x, (uint32_t)ncb}) * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    double y0, y1, y2;
+    j_row<TX, NT>(m, J, x, i, y0, y1, y2);
+    const int32_t k = pc_map[i];
+    if (k >= 0) {
+        double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+        for (int64_t q = pc_first[k]; q < pc_first[k + 1]; ++q) {
+            const double pb = (double)x[3 * n + perf_well[q]];
+            a0 += B[3 * q] * pb;
+            a1 += B[3 * q + 1] * pb;
+            a2 += B[3 * q + 2] * pb;
+        }
+        y0 += a0;
+        y1 += a1;
+        y2 += a2;
+    }
+    y[i] = v ? v[i] - y0 : y0;
+    y[n + i] = v ? v[n + i] - y1 : y1;
+    y[2 * n + i] = v ? v[2 * n + i] - y2 : y2;
 }
 template <class TX, bool NT>
-__global__ __launch_bounds__(256) void k_spmv(DevModel m, const double* __restrict__ J, const TX* __restrict__ x,
-                                              double* __restrict__ y) {
-    k_spmv_d<TX, NT>(PF_BLK, m, J, x, y);
+__global__ __launch_bounds__(256) void k_spmv(DevModel m, int ncb, const double* __restrict__ J,
+                                              const int32_t* __restrict__ pc_map, const int32_t* __restrict__ pc_first,
+                                              const int32_t* __restrict__ perf_well,
+                                              const int32_t* __restrict__ perf_cell,
+                                              const int32_t* __restrict__ wp_first, const int32_t* __restrict__ wp_idx,
+                                              const double* __restrict__ B, const double* __restrict__ Cw,
+                                              const double* __restrict__ Dw, const TX* __restrict__ x,
+                                              const double* __restrict__ v, double* __restrict__ y) {
+    k_spmv_d<TX, NT>(PF_BLK, m, ncb, J, pc_map, pc_first, perf_well, perf_cell, wp_first, wp_idx, B, Cw, Dw, x, v, y);
 }
 template <class TX, bool NT>
 struct F_k_spmv {
@@ -68,67 +120,6 @@ struct F_k_spmv {
     template <class... A>
     __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
         k_spmv_d<TX, NT>(wg, a...);
-    }
-};
-
-// Well border of y = J x: perforated cells add B * Pb (one thread per
-// perforated cell, blocks [0, ncb)); well rows are sum C * x_cell + D * Pb
-// (one 64-lane block per well after those, lanes over the perforations,
-// fixed-order shuffle reduction).
-template <class TX>
-__device__ __forceinline__ void k_spmv_border_d(const Blk& wg, DevModel m, int ncb,
-                                                const int32_t* __restrict__ pc_cell,
-                                                const int32_t* __restrict__ pc_first,
-                                                const int32_t* __restrict__ perf_well,
-                                                const int32_t* __restrict__ perf_cell,
-                                                const int32_t* __restrict__ wp_first,
-                                                const int32_t* __restrict__ wp_idx, const double* __restrict__ B,
-                                                const double* __restrict__ Cw, const double* __restrict__ Dw,
-                                                const TX* __restrict__ x, double* __restrict__ y) {
-    const int64_t n = m.n;
-    if ((int)wg.x < ncb) {
-        const int64_t t = (int64_t)wg.x * blockDim.x + threadIdx.x;
-        if (t >= m.npc) return;
-        const int64_t i = pc_cell[t];
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-        for (int64_t k = pc_first[t]; k < pc_first[t + 1]; ++k) {
-            const double pb = (double)x[3 * n + perf_well[k]];
-            a0 += B[3 * k] * pb;
-            a1 += B[3 * k + 1] * pb;
-            a2 += B[3 * k + 2] * pb;
-        }
-        y[i] += a0;
-        y[n + i] += a1;
-        y[2 * n + i] += a2;
-        return;
-    }
-    const int w = (int)wg.x - ncb;
-    double s = 0.0;
-    for (int k = wp_first[w] + (int)threadIdx.x; k < wp_first[w + 1]; k += 64) {
-        const int p = wp_idx[k];
-        const int64_t c = perf_cell[p];
-        s += Cw[3 * p] * (double)x[c] + Cw[3 * p + 1] * (double)x[n + c] + Cw[3 * p + 2] * (double)x[2 * n + c];
-    }
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-    if (threadIdx.x == 0) y[3 * n + w] = s + Dw[w] * (double)x[3 * n + w];
-}
-template <class TX>
-__global__ __launch_bounds__(64) void k_spmv_border(DevModel m, int ncb, const int32_t* __restrict__ pc_cell,
-                                                    const int32_t* __restrict__ pc_first,
-                                                    const int32_t* __restrict__ perf_well,
-                                                    const int32_t* __restrict__ perf_cell,
-                                                    const int32_t* __restrict__ wp_first,
-                                                    const int32_t* __restrict__ wp_idx, const double* __restrict__ B,
-                                                    const double* __restrict__ Cw, const double* __restrict__ Dw,
-                                                    const TX* __restrict__ x, double* __restrict__ y) {
-    k_spmv_border_d<TX>(PF_BLK, m, ncb, pc_cell, pc_first, perf_well, perf_cell, wp_first, wp_idx, B, Cw, Dw, x, y);
-}
-template <class TX>
-struct F_k_spmv_border {
-    static constexpr int kLB = 64;
-    template <class... A>
-    __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
-        k_spmv_border_d<TX>(wg, a...);
     }
 };
 
@@ -709,32 +700,26 @@ unsigned stream_grid(int64_t n) {
 
 namespace {
 template <class TX>
-void spmv_border_t(Sim& s, const TX* x, double* y) {
-    const DevModel& m = s.m;
-    const int ncb = (int)((m.npc + 63) / 64);
-    if (ncb + m.nw > 0) {
-        launch<F_k_spmv_border<TX>>(s, s.stream, k_spmv_border<TX>, dim3(ncb + m.nw), dim3(64), 0, m, ncb, s.pc_cell,
-                                    s.pc_first, s.perf_well, s.perf_cell, s.wp_first, s.wp_idx, s.B, s.Cw, s.Dw, x, y);
-        PF_LAUNCH_CHECK();
-    }
-}
-template <class TX>
-void spmv_t(Sim& s, const TX* x, double* y) {
+void spmv_t(Sim& s, const TX* x, const double* v, double* y) {
     const DevModel& m = s.m;
     ensure_j_natural(s);
-    {
-        ProfScope ps(s, PF_K_SPMV);
-        if (stream_past_caches(56 * m.n * (int64_t)sizeof(double)))
-            launch<F_k_spmv<TX, true>>(s, s.stream, (k_spmv<TX, true>), dim3(grid_for(m.n)), dim3(kBlock), 0, m, s.J, x,
-                                       y);
-        else
-            launch<F_k_spmv<TX, false>>(s, s.stream, (k_spmv<TX, false>), dim3(grid_for(m.n)), dim3(kBlock), 0, m, s.J,
-                                        x, y);
-        PF_LAUNCH_CHECK();
-    }
-    spmv_border_t<TX>(s, x, y);
+    const int ncb = (int)grid_for(m.n);
+    const dim3 grid(ncb + m.nw), block(kBlock);
+    ProfScope ps(s, PF_K_SPMV);
+#define PF_SPMV(NT)                                                                                             \
+    launch<F_k_spmv<TX, NT>>(s, s.stream, (k_spmv<TX, NT>), grid, block, 0, m, ncb, s.J, s.pc_map, s.pc_first,  \
+                             s.perf_well, s.perf_cell, s.wp_first, s.wp_idx, s.B, s.Cw, s.Dw, x, v, y)
+    if (stream_past_caches(56 * m.n * (int64_t)sizeof(double))) PF_SPMV(true);
+    else PF_SPMV(false);
+#undef PF_SPMV
+    PF_LAUNCH_CHECK();
 }
 }  // namespace
+
+void launch_spmv(Sim& s, const double* x, double* y) { spmv_t<double>(s, x, nullptr, y); }
+void launch_spmv(Sim& s, const float* x, double* y) { spmv_t<float>(s, x, nullptr, y); }
+void launch_residual(Sim& s, const double* v, const double* x, double* t) { spmv_t<double>(s, x, v, t); }
+void launch_residual(Sim& s, const double* v, const float* x, double* t) { spmv_t<float>(s, x, v, t); }
 
 void launch_to_cs(Sim& s, const double* x, double* y, double scale) {
     launch<F_k_to_cs>(s, s.stream, k_to_cs, dim3(grid_for(s.nvc)), dim3(kBlock), 0, s.m, x, y, scale);
@@ -745,8 +730,6 @@ void launch_from_cs(Sim& s, const double* x, double* y) {
     launch<F_k_from_cs>(s, s.stream, k_from_cs, dim3(grid_for(s.nv)), dim3(kBlock), 0, s.m, x, y);
     PF_LAUNCH_CHECK();
 }
-void launch_spmv(Sim& s, const double* x, double* y) { spmv_t<double>(s, x, y); }
-void launch_spmv(Sim& s, const float* x, double* y) { spmv_t<float>(s, x, y); }
 
 void launch_axpby(Sim& s, int64_t n, double a, const double* x, double b, double* y) {
     launch<F_k_axpby>(s, s.stream, k_axpby, dim3(stream_grid(n)), dim3(kBlock), 0, n, a, x, b, y);

@@ -397,8 +397,7 @@ int fgmres(Sim& s, const double* b_nat, double tol, double* x_nat, double* rel, 
                 launch_axpby(s, s.nx, 1.0, b, -1.0, s.t2);
                 r0 = s.t2;
             } else {
-                launch_spmv(s, x, s.t1);
-                launch_axpby(s, s.nx, 1.0, b, -1.0, s.t1);
+                launch_residual(s, b, x, s.t1);
                 r0 = s.t1;
             }
         }

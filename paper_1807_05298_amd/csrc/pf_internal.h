@@ -351,6 +351,8 @@ inline int red_grid(int64_t n) {
 // ---- linear algebra (k_linalg.hip) ----------------------------------------
 void launch_spmv(Sim& s, const double* x, double* y);
 void launch_spmv(Sim& s, const float* x, double* y);
+void launch_residual(Sim& s, const double* v, const double* x, double* t);        // t = v - J x
+void launch_residual(Sim& s, const double* v, const float* x, double* t);
 void launch_to_cs(Sim& s, const double* x, double* y, double scale = 1.0);   // natural -> colour-split, times scale
 void launch_from_cs(Sim& s, const double* x, double* y);          // colour-split -> natural layout
 void launch_axpby(Sim& s, int64_t n, double a, const double* x, double b, double* y);
