@@ -57,29 +57,42 @@ KERNEL_BYTES = {
 TRAFFIC_FILES = {
     "spmv": ("profiles/k_spmv_c2_fp64_hbm_counters.md",
              [("paper_1807_05298_amd/csrc/k_linalg.hip", "k_spmv_d"),
+              ("paper_1807_05298_amd/csrc/k_linalg.hip", "j_row"),
               ("paper_1807_05298_amd/csrc/k_linalg.hip", "jld"),
               ("paper_1807_05298_amd/csrc/pf_internal.h", "xcd_block")]),
     "red_spmv": ("profiles/k_ilu_red_spmv_c2_fp64_hbm_counters.md",
                  [("paper_1807_05298_amd/csrc/k_cpr.hip", "k_ilu_red_spmv_d"),
-                  ("paper_1807_05298_amd/csrc/k_cpr.hip", "strip_slot"),
-                  ("paper_1807_05298_amd/csrc/pf_internal.h", "strip_order"),
+                  ("paper_1807_05298_amd/csrc/k_cpr.hip", "face_product"),
                   ("paper_1807_05298_amd/csrc/k_cpr.hip", "ilu_ld"),
+                  ("paper_1807_05298_amd/csrc/k_cpr.hip", "off_diagonal"),
+                  ("paper_1807_05298_amd/csrc/k_cpr.hip", "sub_border"),
+                  ("paper_1807_05298_amd/csrc/k_cpr.hip", "cs_nbr"),
+                  ("paper_1807_05298_amd/csrc/k_cpr.hip", "strip_slot"),
                   ("paper_1807_05298_amd/csrc/k_cpr.hip", "ilu_slot_cell"),
+                  ("paper_1807_05298_amd/csrc/pf_internal.h", "lc_at"),
+                  ("paper_1807_05298_amd/csrc/pf_internal.h", "strip_order"),
                   ("paper_1807_05298_amd/csrc/pf_internal.h", "xcd_block")]),
     "black_spmv": ("profiles/k_black_spmv_c2_fp64_hbm_counters.md",
                    [("paper_1807_05298_amd/csrc/k_cpr.hip", "k_black_spmv_d"),
-                    ("paper_1807_05298_amd/csrc/k_cpr.hip", "strip_slot"),
-                    ("paper_1807_05298_amd/csrc/pf_internal.h", "strip_order"),
+                    ("paper_1807_05298_amd/csrc/k_cpr.hip", "face_product"),
                     ("paper_1807_05298_amd/csrc/k_cpr.hip", "ilu_ld"),
+                    ("paper_1807_05298_amd/csrc/k_cpr.hip", "off_diagonal"),
+                    ("paper_1807_05298_amd/csrc/k_cpr.hip", "sub_border"),
+                    ("paper_1807_05298_amd/csrc/k_cpr.hip", "cs_nbr"),
+                    ("paper_1807_05298_amd/csrc/k_cpr.hip", "strip_slot"),
                     ("paper_1807_05298_amd/csrc/k_cpr.hip", "ilu_slot_cell"),
+                    ("paper_1807_05298_amd/csrc/pf_internal.h", "lc_at"),
+                    ("paper_1807_05298_amd/csrc/pf_internal.h", "strip_order"),
                     ("paper_1807_05298_amd/csrc/pf_internal.h", "xcd_block")]),
     "stage_resid": ("profiles/k_stage_red_c2_fp64_hbm_counters.md",
                     [("paper_1807_05298_amd/csrc/k_cpr.hip", "k_stage_red_d"),
-                     ("paper_1807_05298_amd/csrc/k_cpr.hip", "strip_slot"),
-                     ("paper_1807_05298_amd/csrc/pf_internal.h", "strip_order"),
-                     ("paper_1807_05298_amd/csrc/k_cpr.hip", "stage_border"),
                      ("paper_1807_05298_amd/csrc/k_cpr.hip", "ilu_ld"),
+                     ("paper_1807_05298_amd/csrc/k_cpr.hip", "sub_border"),
+                     ("paper_1807_05298_amd/csrc/k_cpr.hip", "cs_nbr"),
+                     ("paper_1807_05298_amd/csrc/k_cpr.hip", "strip_slot"),
                      ("paper_1807_05298_amd/csrc/k_cpr.hip", "ilu_slot_cell"),
+                     ("paper_1807_05298_amd/csrc/pf_internal.h", "lc_at"),
+                     ("paper_1807_05298_amd/csrc/pf_internal.h", "strip_order"),
                      ("paper_1807_05298_amd/csrc/pf_internal.h", "xcd_block")]),
     "assemble": ("profiles/k_assemble_c2_fp64_hbm_counters.md",
                  [("paper_1807_05298_amd/csrc/k_physics.hip", f) for f in
