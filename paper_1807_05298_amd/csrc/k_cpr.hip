@@ -717,9 +717,11 @@ __device__ __forceinline__ void k_mg_down_d(const Blk& wg, const MgDown<T>& a) {
     }
     if (len > 0) {
         const bool xm = ix > 0, xp = ix + 1 < f.nx, ym = iy > 0, yp = iy + 1 < f.ny;
-        const int64_t oxm = xm ? -half + (((ix - 1) >> 1) - (ix >> 1)) : 0;
-        const int64_t oxp = xp ? -half + (((ix + 1) >> 1) - (ix >> 1)) : 0;
-        const int64_t oym = ym ? -half - hx : 0, oyp = yp ? -half + hx : 0;
+        // (a missing neighbour's load comes from the same slot of colour 0: a colour-1 value may be being
+        // written by another workgroup)
+        const int64_t oxm = -half + (xm ? ((ix - 1) >> 1) - (ix >> 1) : 0);
+        const int64_t oxp = -half + (xp ? ((ix + 1) >> 1) - (ix >> 1) : 0);
+        const int64_t oym = -half - (ym ? hx : 0), oyp = -half + (yp ? hx : 0);
 #pragma unroll
         for (int j = 0; j < LMAX; ++j) {
             const bool v = j < len;
