@@ -2061,26 +2061,6 @@ __device__ __forceinline__ int64_t cs_nbr(const DevModel& m, int64_t s, int64_t 
     }
 }
 
-// pc_map in the colour-split slots (2 ns, -1 in the pads)
-__device__ __forceinline__ void k_pc_map_cs_d(const Blk& wg, DevModel m, const int32_t* __restrict__ map,
-                                              int32_t* __restrict__ out) {
-    const int64_t q = (int64_t)wg.x * blockDim.x + threadIdx.x, ns = ilu_slots(m);
-    if (q >= 2 * ns) return;
-    const int c = q >= ns ? 1 : 0;
-    int64_t ix, iy, iz;
-    out[q] = ilu_slot_cell(m, c, q - c * ns, ix, iy, iz) ? map[ix + m.nx * iy + m.nxy * iz] : -1;
-}
-__global__ void k_pc_map_cs(DevModel m, const int32_t* __restrict__ map, int32_t* __restrict__ out) {
-    k_pc_map_cs_d(PF_BLK, m, map, out);
-}
-struct F_k_pc_map_cs {
-    static constexpr int kLB = 1024;
-    template <class... A>
-    __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
-        k_pc_map_cs_d(wg, a...);
-    }
-};
-
 // z^f_r on the red slots.
 template <bool NT>
 __device__ __forceinline__ void k_stage_red_d(const Blk& wg, DevModel m, const double* __restrict__ Lc,
@@ -3141,12 +3121,6 @@ void ensure_j_natural(Sim& s) {
     launch<F_k_j_natural>(s, s.stream, k_j_natural, dim3(grid_for(s.m.n)), dim3(kBlock), 0, s.m, s.Lc, s.Jdc, s.J);
     PF_LAUNCH_CHECK();
     s.j_nat = true;
-}
-
-void launch_pc_map_cs(Sim& s) {
-    launch<F_k_pc_map_cs>(s, s.stream, k_pc_map_cs, dim3(grid_for(2 * ilu_slot_count(s.m))), dim3(kBlock), 0, s.m,
-                          s.pc_map, s.pc_map_cs);
-    PF_LAUNCH_CHECK();
 }
 
 // z = M^{-1} v and w = J~ z (FP64), natural layout.

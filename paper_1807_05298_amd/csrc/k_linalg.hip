@@ -150,6 +150,29 @@ struct F_k_to_cs {
     }
 };
 
+// pc_map in the colour-split slots (2 ns, -1 in the pads).
+__device__ __forceinline__ void k_pc_map_cs_d(const Blk& wg, DevModel m, const int32_t* __restrict__ map,
+                                              int32_t* __restrict__ out) {
+    const int64_t ns = cs_ns(m);
+    const int64_t q = (int64_t)wg.x * blockDim.x + threadIdx.x;
+    if (q >= 2 * ns) return;
+    const int c = q >= ns ? 1 : 0;
+    const int64_t sl = q - c * ns, hx = (m.nx + 1) >> 1;
+    const int64_t line = sl / hx, t = sl - line * hx;
+    const int64_t iz = line / m.ny, iy = line - iz * m.ny, ix = 2 * t + ((iy + iz + c) & 1);
+    out[q] = ix < m.nx ? map[ix + m.nx * iy + m.nxy * iz] : -1;
+}
+__global__ void k_pc_map_cs(DevModel m, const int32_t* __restrict__ map, int32_t* __restrict__ out) {
+    k_pc_map_cs_d(PF_BLK, m, map, out);
+}
+struct F_k_pc_map_cs {
+    static constexpr int kLB = 1024;
+    template <class... A>
+    __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
+        k_pc_map_cs_d(wg, a...);
+    }
+};
+
 __device__ __forceinline__ void k_from_cs_d(const Blk& wg, DevModel m, const double* __restrict__ x,
                                             double* __restrict__ y) {
     const int64_t ns = cs_ns(m);
@@ -720,6 +743,12 @@ void launch_spmv(Sim& s, const double* x, double* y) { spmv_t<double>(s, x, null
 void launch_spmv(Sim& s, const float* x, double* y) { spmv_t<float>(s, x, nullptr, y); }
 void launch_residual(Sim& s, const double* v, const double* x, double* t) { spmv_t<double>(s, x, v, t); }
 void launch_residual(Sim& s, const double* v, const float* x, double* t) { spmv_t<float>(s, x, v, t); }
+
+void launch_pc_map_cs(Sim& s) {
+    launch<F_k_pc_map_cs>(s, s.stream, k_pc_map_cs, dim3(grid_for(2 * cs_ns(s.m))), dim3(kBlock), 0, s.m, s.pc_map,
+                          s.pc_map_cs);
+    PF_LAUNCH_CHECK();
+}
 
 void launch_to_cs(Sim& s, const double* x, double* y, double scale) {
     launch<F_k_to_cs>(s, s.stream, k_to_cs, dim3(grid_for(s.nvc)), dim3(kBlock), 0, s.m, x, y, scale);

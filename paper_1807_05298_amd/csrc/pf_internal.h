@@ -353,6 +353,7 @@ void launch_spmv(Sim& s, const double* x, double* y);
 void launch_spmv(Sim& s, const float* x, double* y);
 void launch_residual(Sim& s, const double* v, const double* x, double* t);        // t = v - J x
 void launch_residual(Sim& s, const double* v, const float* x, double* t);
+void launch_pc_map_cs(Sim& s);        // pc_map_cs from pc_map
 void launch_to_cs(Sim& s, const double* x, double* y, double scale = 1.0);   // natural -> colour-split, times scale
 void launch_from_cs(Sim& s, const double* x, double* y);          // colour-split -> natural layout
 void launch_axpby(Sim& s, int64_t n, double a, const double* x, double b, double* y);
@@ -389,7 +390,6 @@ struct CsVec {
 };
 void cpr_apply_spmv(Sim& s, const CsVec& v, double* z, double* wb);
 void cpr_apply_spmv(Sim& s, const double* v, double* z, double* w);   // natural layout: z = M^{-1} v, w = J z
-void launch_pc_map_cs(Sim& s);        // pc_map_cs from pc_map
 bool cpr_colour_split(const Sim& s);  // the FP64 solve runs in the colour-split layout
 void mg_smooth_once(Sim& s, int level, int colour, int zero_init);   // test hook
 int64_t mg_slot(const MGLevel& L, int ix, int iy, int iz);             // cell -> slot of a level
