@@ -2515,17 +2515,12 @@ DownTile mg_down_tile(const Sim& s, int l, bool lat, bool next) {
     if (L.cx != 2 || L.cy != 2 || nseg > 64) return best;
     // values a cell: right-hand side, lateral coefficients, factors, neighbours; rows of colour 0
     const double v1 = 10, v0 = lat ? 4 : 10, sz = sizeof(T);
-    // a fusion group's launch holds the tiles of several members: counted as if of eight, whatever the group
-    // (a member's route, and so its rounding, does not depend on the others).  Eight members of 31-52 x 37 x 23
-    // cells: their finest level 25.5 us after another cycle counted alone, against 17 by three launches; a
-    // timestep of them 17.94 -> 17.55 ms, twelve served jobs 50.1 -> 49.6 ms.
-    const double members = s.fu ? 8 : 1;
-    double cost = (next ? 10.5 : 7.0) + members * 0.5 * (v1 + v0) * sz * (double)L.n / 3.7e6;
+    double cost = (next ? 10.5 : 7.0) + 0.5 * (v1 + v0) * sz * (double)L.n / 3.7e6;
     for (const DownTile& t : kDownTiles) {
         const int row = (t.x + 2) / 2, lines = row * (t.y + 2);
         if (lines * nseg > 1024) continue;
         const double fetched = (t.y + 2) * v1 * (row * sz + 64 - sz) + t.y * v0 * (t.x / 2 * sz + 64 - sz);
-        const double tiles = members * ((L.nx + t.x - 1) / t.x) * ((L.ny + t.y - 1) / t.y);
+        const double tiles = (double)((L.nx + t.x - 1) / t.x) * ((L.ny + t.y - 1) / t.y);
         const double c = 4.2 + fetched * L.nz / 20e3 * std::max(1.0, tiles / 256);
         if (c < cost) {
             cost = c;
