@@ -255,7 +255,9 @@ pf_status pf_create_static(const pf_model_desc* model, const pf_solver_opts* opt
                            pf_sim** out);
 
 /* Replace the solver options (same workspace; precision/smoother/restart
- * may not grow beyond what the workspace was sized for). */
+ * may not grow beyond what the workspace was sized for: PF_EINVAL for another
+ * precision, a longer restart, and red-black ILU(0) on a simulator created
+ * with block Jacobi). */
 pf_status pf_set_opts(pf_sim* sim, const pf_solver_opts* opts);
 
 /* Initial state (Sec. 3, solution flowchart item 3: the simulator starts

@@ -865,6 +865,9 @@ pf_status pf_set_opts(pf_sim* h, const pf_solver_opts* o) {
     if (o->precision != s.opts.precision) throw InvalidArg{"precision is fixed at creation"};
     if (o->max_lin_it < 1 || o->max_newton < 1 || o->max_cuts < 0) throw InvalidArg{"bad iteration limits"};
     if (o->smoother != PF_SMOOTH_BJAC && o->smoother != PF_SMOOTH_RBILU0) throw InvalidArg{"bad smoother"};
+    // the factors' copies of J (FP64 or BF16) are planned at creation only for red-black ILU(0)
+    if (o->smoother == PF_SMOOTH_RBILU0 && !s.Lc && !s.Joff16)
+        throw InvalidArg{"the workspace was sized for the block-Jacobi smoother"};
     if (o->cpr_order != PF_CPR_PF && o->cpr_order != PF_CPR_FP) throw InvalidArg{"bad CPR order"};
     s.opts = *o;
     return PF_OK;

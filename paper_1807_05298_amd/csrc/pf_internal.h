@@ -255,9 +255,9 @@ struct Sim {
     double *coarse_inv_t;            // ... and transposed
     float *coarse_inv_t32;
     float *Jp32;                     // mixed: FP32 P-columns of J (21 planes)
-    double *Lc;                      // FP64 ILU: colour-split off-diagonal blocks (lc_at)
+    double *Lc = nullptr;            // FP64 ILU: colour-split off-diagonal blocks (lc_at)
     double *Jdc;                     // FP64 ILU: colour-split diagonal blocks of J (2 x 9 planes)
-    uint16_t *Joff16;                // mixed ILU: colour-split BF16 off-diagonal blocks (2 x 54 planes)
+    uint16_t *Joff16 = nullptr;      // mixed ILU: colour-split BF16 off-diagonal blocks (2 x 54 planes)
     float *Dinv32;                   // mixed: FP32 smoother inverse diagonals
     float *t32;                      // mixed: FP32 stage residual
     float *Z32;                      // mixed: FP32 preconditioned Krylov vectors
