@@ -187,7 +187,8 @@ typedef struct {
     int32_t reorth;        /* 1: always re-orthogonalise (CGS2); 0: when a CGS pass removed more than
                               90 % of the vector's norm */
     int32_t mg_cycles;     /* V-cycles per pressure-stage application (1..8) */
-    int32_t zline_len;     /* layers per z-line smoother segment (0: by level size; at most 64 segments) */
+    int32_t zline_len;     /* layers per z-line smoother segment on every level (0: by level size, with
+                              low and small levels' sweeps merged into fewer launches; at most 64 segments) */
     int32_t mg_pre_small;  /* pre-smoothing sweeps on levels of at most max(mg_small_cells, n0 / 32)
                               cells (n0: cells of the finest level), when n0 is at least
                               10 mg_small_cells (0: 5) */
@@ -337,11 +338,19 @@ pf_status pf_linear_solve(pf_sim* sim, const double* b, double rtol, double* dx,
  * neighbours as zero.  pf_pressure_vcycle applies the pressure stage's
  * multigrid (mg_cycles V-cycles from x = 0, in the simulator's precision) to
  * a right-hand side b on the cells of level 0 and writes the result x; both
- * are host arrays of N in natural cell order. */
+ * are host arrays of N in natural cell order.  pf_pressure_route tells which
+ * launches take a level on the way down of a cycle (from 0; later ones are
+ * alike): route[0] is PF_MG_SWEEPS (a launch a half-sweep), PF_MG_WHOLE (all
+ * pre-sweeps in one), PF_MG_DOWN (the last half-sweep with the restriction in
+ * one, by tiles of route[1] x route[2] columns, and if route[3] the next
+ * level's first half-sweep), PF_MG_TAIL (one launch from the first such level
+ * to the coarsest and back) or PF_MG_DENSE (the coarsest level). */
 int32_t pf_pressure_level(pf_sim* sim, int32_t level, int32_t* dims, double* A);
 pf_status pf_pressure_smooth(pf_sim* sim, int32_t level, int32_t colour, int32_t zero_init,
                              const double* b, double* x);
 pf_status pf_pressure_vcycle(pf_sim* sim, const double* b, double* x);
+enum { PF_MG_SWEEPS = 0, PF_MG_WHOLE = 1, PF_MG_DOWN = 2, PF_MG_TAIL = 3, PF_MG_DENSE = 4 };
+pf_status pf_pressure_route(pf_sim* sim, int32_t level, int32_t cycle, int32_t route[4]);
 
 /* Second-stage smoother test hook (Sec. 3.4, the block smoother of the CPR
  * preconditioner; valid after the preconditioner has been set up):

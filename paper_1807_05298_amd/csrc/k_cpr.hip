@@ -2456,17 +2456,15 @@ void zline_sweep(Sim& s, const MGLevel& L, int colour, int zero_init) {
     PF_LAUNCH_CHECK();
 }
 
-// sweeps full z-line sweeps (both colours) in one workgroup where every
-// column of a colour fits it with the level's segment length; false
-// (nothing launched) otherwise.  (Longer segments to make a larger level
+// sweeps full z-line sweeps (both colours) in one workgroup, where every
+// column of a colour fits it with the level's segment length.  (Longer segments to make a larger level
 // fit were slower than its two launches per sweep.)
 bool zline_full_fits(const Sim& s, const MGLevel& L) {
     const ZlShape z = zline_shape(s, L);
     return z.len <= 8 && (int64_t)((L.nx + 1) / 2) * L.ny * z.nseg <= 1024;
 }
 template <class T>
-bool zline_full_sweeps(Sim& s, const MGLevel& L, int zero_init, int sweeps) {
-    if (!zline_full_fits(s, L)) return false;
+void zline_full_sweeps(Sim& s, const MGLevel& L, int zero_init, int sweeps) {
     const ZlShape z = zline_shape(s, L);
     const int64_t cols = (int64_t)((L.nx + 1) / 2) * L.ny;
     const Dims g = dims_of(L);
@@ -2488,12 +2486,12 @@ bool zline_full_sweeps(Sim& s, const MGLevel& L, int zero_init, int sweeps) {
     else { PF_ZF(8) }
 #undef PF_ZF
     PF_LAUNCH_CHECK();
-    return true;
 }
 
 // The tile with which k_mg_down takes the way down from level l, or none for
 // launches of their own.  It needs 2 x 2 columns an aggregate and lines that
-// fit a workgroup in segments of kDownLen layers.  The costs are modelled (us):
+// fit a workgroup in segments of kDownLen layers, where the caller has not set
+// their length (zline_len).  The costs are modelled (us):
 // a launch on a small level takes 3.5, the three of them a traffic that the
 // whole GPU draws at 3.7 TB/s; this one 4.2, and what a tile makes its compute
 // unit fetch, in pieces of 64 bytes of its short rows, at 20 KB a us, times the
@@ -2512,7 +2510,7 @@ DownTile mg_down_tile(const Sim& s, int l, bool lat, bool next) {
     if (l + 1 >= (int)s.mg.size()) return best;
     const MGLevel& L = s.mg[l];
     const int nseg = (L.nz + kDownLen - 1) / kDownLen;
-    if (L.cx != 2 || L.cy != 2 || nseg > 64) return best;
+    if (L.cx != 2 || L.cy != 2 || nseg > 64 || s.opts.zline_len > 0) return best;
     // values a cell: right-hand side, lateral coefficients, factors, neighbours; rows of colour 0
     const double v1 = 10, v0 = lat ? 4 : 10, sz = sizeof(T);
     double cost = (next ? 10.5 : 7.0) + 0.5 * (v1 + v0) * sz * (double)L.n / 3.7e6;
@@ -2563,12 +2561,14 @@ void launch_mg_down(Sim& s, int l, const DownTile& tile, bool lat, bool next) {
 // b = Pi_r v on level 0 fused with the first V-cycle's first half-sweep;
 // false (nothing launched) where level 0 is the coarsest or its segments
 // take the memory-staged kernel.
+bool restrict_p_zline_fits(const Sim& s) {
+    return s.mg.size() >= 2 && s.mg[0].split && zline_shape(s, s.mg[0]).len <= 8;
+}
 template <class T>
 bool restrict_p_zline(Sim& s, const double* v, const CsVec& cv) {
+    if (!restrict_p_zline_fits(s)) return false;
     const MGLevel& L = s.mg[0];
-    if (s.mg.size() < 2 || !L.split) return false;
     const ZlShape z = zline_shape(s, L);
-    if (z.len > 8) return false;
     const Dims g = dims_of(L);
     const T *A = Lv<T>::A(L), *aux = Lv<T>::aux(L);
     T *b = Lv<T>::b(L), *x = Lv<T>::x(L);
@@ -2859,6 +2859,34 @@ void join_coarse(Sim& s) {
     s.coarse_pending = false;
 }
 
+// levels [0, first_of_tail) have launches of their own, the rest is one launch
+int first_of_tail(const Sim& s) {
+    const int nl = (int)s.mg.size();
+    return nl <= kMaxChain ? mg_tail_first(s) : nl;
+}
+
+// How the way down from level l goes.  whole: its pre-sweeps in one launch;
+// tile: its end by k_mg_down (x 0: launches of their own), and next: the next
+// level's first half-sweep with it.
+struct DownRoute {
+    DownTile tile;
+    bool next, whole;
+};
+template <class T>
+DownRoute down_route(const Sim& s, int l, int nt, bool lat, bool first_done) {
+    const MGLevel &L = s.mg[l], &C = s.mg[l + 1];
+    // whether the next level's first half-sweep can follow its restriction
+    // at once (a level of one workgroup with more sweeps to do does them all)
+    const int pc = l + 1 < std::min(nt, (int)s.mg.size() - 1) ? pre_sweeps(s, C) : 0;
+    const bool next = pc == 1 || (pc > 1 && !zline_full_fits(s, C));
+    const DownTile tile = mg_down_tile<T>(s, l, lat, next);
+    // a level that fits one workgroup takes all its pre-sweeps in one launch
+    // (a single one is half done by the launch before and the one after)
+    if (l > 0 && !first_done && !(pre_sweeps(s, L) == 1 && tile.x) && zline_full_fits(s, L))
+        return DownRoute{{0, 0}, false, true};
+    return DownRoute{tile, next, false};
+}
+
 // One V-cycle from level l.  At level 0 of the last cycle, pout receives the
 // level-0 correction: in natural cell order, or with vw (the well rows of a
 // colour-split v) on the black cells, and the well pressures.  first_done: the
@@ -2870,8 +2898,7 @@ void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_don
     const int nl = (int)s.mg.size();
     MGLevel& L = s.mg[l];
     const Dims g = dims_of(L);
-    // levels [0, nt) have launches of their own, the rest is one launch
-    const int nt = nl <= kMaxChain ? mg_tail_first(s) : nl;
+    const int nt = first_of_tail(s);
     if (l == nt && nt < nl) {
         join_coarse(s);
         launch_mg_tail(s, l, 1, nullptr, nullptr, (T*)nullptr);
@@ -2886,16 +2913,10 @@ void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_don
         // after a single sweep from x = 0 the colour-0 rows' residuals are
         // their lateral terms alone
         const bool lat = pre == 1 && zero_init0;
-        // whether the next level's first half-sweep can follow its restriction
-        // at once (a level of one workgroup with more sweeps to do does them all)
-        const int pc = l + 1 < std::min(nt, nl - 1) ? pre_sweeps(s, C) : 0;
-        const bool next = pc == 1 || (pc > 1 && !zline_full_fits(s, C));
-        const DownTile tile = mg_down_tile<T>(s, l, lat, next);
-        // a level that fits one workgroup takes all its pre-sweeps in one launch
-        // (a single one is half done by the launch before and the one after)
-        const bool whole = l > 0 && !first_done && !(pre == 1 && tile.x) && zline_full_sweeps<T>(s, L, zero_init0, pre);
-        const bool down = tile.x && !whole;
-        for (int it = 0; it < (whole ? 0 : pre); ++it) {
+        const DownRoute way = down_route<T>(s, l, nt, lat, first_done);
+        const bool down = way.tile.x > 0;
+        if (way.whole) zline_full_sweeps<T>(s, L, zero_init0, pre);
+        for (int it = 0; it < (way.whole ? 0 : pre); ++it) {
             const int zi = (it == 0 && zero_init0) ? 1 : 0;
             if (!(it == 0 && first_done)) {
                 ProfScope ps(s, l == 0 ? PF_K_ZLINE : 0);
@@ -2906,7 +2927,7 @@ void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_don
         // pre-smoothing ended with a colour-1 half-sweep: those rows' residuals
         // are zero
         if (down) {
-            launch_mg_down<T>(s, l, tile, lat, next);
+            launch_mg_down<T>(s, l, way.tile, lat, way.next);
         } else {
 #define PF_RR(RB, LAT)                                                                                        \
         launch<F_k_resid_restrict<T, RB, LAT>>(s, s.stream, (k_resid_restrict<T, RB, LAT>), dim3(grid_for(C.n)), \
@@ -2922,7 +2943,7 @@ void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_don
 #undef PF_RR
             PF_LAUNCH_CHECK();
         }
-        vcycle<T>(s, l + 1, 1, nullptr, down && next);
+        vcycle<T>(s, l + 1, 1, nullptr, down && way.next);
         if (post == 0 && nl <= kMaxChain) {
             // no post-smoothing: the whole upward pass is prolongation, done once from level 0
             if (l == 0) {
@@ -2954,6 +2975,28 @@ void vcycle(Sim& s, int l, int zero_init0 = 1, T* pout = nullptr, bool first_don
 }  // namespace
 
 int mg_pre_sweeps(const Sim& s, int level) { return pre_sweeps(s, s.mg[level]); }
+
+namespace {
+template <class T>
+MgRoute route_of(const Sim& s, int level, int cycle) {
+    const int nl = (int)s.mg.size(), nt = first_of_tail(s);
+    if (level >= nt && nt < nl) return MgRoute{PF_MG_TAIL, 0, 0, 0};
+    if (level == nl - 1) return MgRoute{PF_MG_DENSE, 0, 0, 0};
+    bool first_done = cycle == 0 && restrict_p_zline_fits(s);
+    for (int l = 0;; ++l) {
+        const bool lat = pre_sweeps(s, s.mg[l]) == 1 && (l > 0 || cycle == 0);
+        const DownRoute w = down_route<T>(s, l, nt, lat, first_done);
+        if (l == level)
+            return MgRoute{w.whole ? PF_MG_WHOLE : w.tile.x ? PF_MG_DOWN : PF_MG_SWEEPS, w.tile.x, w.tile.y,
+                           w.tile.x && w.next};
+        first_done = w.tile.x && w.next;
+    }
+}
+}  // namespace
+
+MgRoute mg_route(const Sim& s, int level, int cycle) {
+    return s.opts.precision == PF_PREC_MIXED ? route_of<float>(s, level, cycle) : route_of<double>(s, level, cycle);
+}
 
 void mg_smooth_once(Sim& s, int level, int colour, int zero_init) {
     zline_sweep<double>(s, s.mg[level], colour, zero_init);

@@ -521,11 +521,12 @@ size_t tail_plan(const Sim& s, int l0, Tail<T>& t) {
     return off * sizeof(T);
 }
 
-// The first level the launch takes: the finest that fits.
+// The first level the launch takes: the finest that fits.  (Its segments are
+// its own, so a caller who sets their length gets launches of their own.)
 template <class T>
 int tail_first(const Sim& s) {
     const int nl = (int)s.mg.size();
-    if (nl < 2 || s.opts.mg_post > 0 || s.mg.back().n > kTailCoarse) return nl;
+    if (nl < 2 || s.opts.mg_post > 0 || s.opts.zline_len > 0 || s.mg.back().n > kTailCoarse) return nl;
     Tail<T> t{};
     for (int l = std::max(0, nl - 1 - kTailLevels); l + 1 < nl; ++l) {
         if (s.mg[l].n > 2 * kTailLen * kTailThreads) continue;

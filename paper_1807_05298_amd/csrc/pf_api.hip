@@ -1156,6 +1156,16 @@ pf_status pf_pressure_smooth(pf_sim* h, int32_t level, int32_t colour, int32_t z
     PF_API_END
 }
 
+pf_status pf_pressure_route(pf_sim* h, int32_t level, int32_t cycle, int32_t route[4]) {
+    PF_API_BEGIN
+    if (!h || !route) throw InvalidArg{"null argument"};
+    if (level < 0 || level >= (int)h->s.mg.size() || cycle < 0) throw InvalidArg{"no such level or cycle"};
+    const MgRoute r = mg_route(h->s, level, cycle);
+    route[0] = r.kind; route[1] = r.tx; route[2] = r.ty; route[3] = r.next;
+    return PF_OK;
+    PF_API_END
+}
+
 pf_status pf_smoother_apply(pf_sim* h, const double* f, double* z) {
     PF_API_BEGIN
     if (!h || !f || !z) throw InvalidArg{"null argument"};

@@ -394,6 +394,12 @@ bool cpr_colour_split(const Sim& s);  // the FP64 solve runs in the colour-split
 void mg_smooth_once(Sim& s, int level, int colour, int zero_init);   // test hook
 int64_t mg_slot(const MGLevel& L, int ix, int iy, int iz);             // cell -> slot of a level
 int mg_pre_sweeps(const Sim& s, int level);                            // pre-smoothing sweeps of a level
+// test hook: what takes a level on the way down of a pressure stage's cycle
+// (PF_MG_*), k_mg_down's tile, and whether the next level's first half-sweep goes with it
+struct MgRoute {
+    int32_t kind, tx, ty, next;
+};
+MgRoute mg_route(const Sim& s, int level, int cycle);
 void mg_cycles_once(Sim& s, const double* v);   // test hook: s.pnat(32) = V-cycles(Pi_r v)
 void smoother_once(Sim& s, const double* f);    // test hook: s.t1 (FP64) / s.Z32 (mixed) = S f
 

@@ -37,6 +37,8 @@ PREC_FP64, PREC_MIXED = 0, 1
 CPR_PF, CPR_FP = 0, 1
 SMOOTH_BJAC, SMOOTH_RBILU0 = 0, 1
 WELL_Z, WELL_X = 0, 1
+# what takes a multigrid level on the way down (PF_MG_* in the header)
+MG_SWEEPS, MG_WHOLE, MG_DOWN, MG_TAIL, MG_DENSE = range(5)
 
 _d = ctypes.c_double
 _i = ctypes.c_int32
@@ -152,6 +154,7 @@ _lib.pf_pressure_level.restype = _i
 _lib.pf_pressure_level.argtypes = [_vp, _i, _vp, _vp]
 _lib.pf_pressure_smooth.argtypes = [_vp, _i, _i, _i, _vp, _vp]
 _lib.pf_pressure_vcycle.argtypes = [_vp, _vp, _vp]
+_lib.pf_pressure_route.argtypes = [_vp, _i, _i, _vp]
 _lib.pf_smoother_apply.argtypes = [_vp, _vp, _vp]
 _lib.pf_precond_apply.argtypes = [_vp, _vp, _vp, _vp]
 _lib.pf_profile_end.argtypes = [_vp, ctypes.POINTER(_i), ctypes.POINTER(_d)]
@@ -161,7 +164,7 @@ _lib.pf_set_well_operation.argtypes = [_vp, _i, _i, _d, _d, _d]
 EXPORTED = ["pf_default_opts", "pf_workspace_size", "pf_create", "pf_destroy", "pf_set_opts", "pf_set_state",
             "pf_get_state", "pf_begin_step", "pf_newton_iteration", "pf_step", "pf_assemble", "pf_spmv",
             "pf_linear_solve", "pf_get_static", "pf_n_perf", "pf_last_error", "pf_profile_begin", "pf_profile_end",
-            "pf_pressure_level", "pf_pressure_smooth", "pf_pressure_vcycle", "pf_smoother_apply",
+            "pf_pressure_level", "pf_pressure_smooth", "pf_pressure_vcycle", "pf_pressure_route", "pf_smoother_apply",
             "pf_precond_apply", "pf_server_create", "pf_server_submit", "pf_server_poll",
             "pf_server_wait", "pf_server_release", "pf_server_info", "pf_server_destroy", "pf_well_status", "pf_set_well_operation",
             "pf_fusion_create", "pf_fusion_join", "pf_fusion_leave", "pf_fusion_step", "pf_fusion_stats",
@@ -410,6 +413,14 @@ class Simulator:
         x = np.empty(self.n)
         _check(_lib.pf_pressure_vcycle(self.h, b.ctypes.data, x.ctypes.data))
         return x
+
+    def pressure_route(self, cycle: int = 0) -> list:
+        """(MG_* kind, tile x, tile y, next level's half-sweep with it) of every level on the way down of a cycle."""
+        nl = int(_lib.pf_pressure_level(self.h, -1, None, None))
+        out = np.zeros((nl, 4), np.int32)
+        for l in range(nl):
+            _check(_lib.pf_pressure_route(self.h, l, cycle, out[l].ctypes.data))
+        return [tuple(int(v) for v in r) for r in out]
 
     def static(self) -> dict:
         n, npf = self.n, max(self.n_perf, 1)
