@@ -3209,7 +3209,8 @@ void colour_split_apply(Sim& s, const CsVec& v, double* z, double* w) {
 // The same in the colour-split layout (PF order, red-black ILU(0)); of w the
 // black rows and the wells: the red rows are those of v.
 void cpr_apply_spmv(Sim& s, const CsVec& v, double* z, double* w) {
-    if (stream_past_caches(2 * lc_colour(ilu_slot_count(s.m)) * (int64_t)sizeof(double))) colour_split_apply<true>(s, v, z, w);
+    if (stream_past_caches(s, 2 * lc_colour(ilu_slot_count(s.m)) * (int64_t)sizeof(double)))
+        colour_split_apply<true>(s, v, z, w);
     else colour_split_apply<false>(s, v, z, w);
 }
 

@@ -31,6 +31,7 @@ struct Fusion {
     std::mutex mu;
     std::condition_variable cv;
     std::vector<Sim*> members;
+    std::atomic<int64_t> cells{0};   // of the members together
     int waiting = 0;                 // members at a synchronisation point
     bool flushing = false;
     std::atomic<uint64_t> gen{0};    // issued batches of recorded work
@@ -286,6 +287,7 @@ void drop(Sim& s) {
     std::unique_lock<std::mutex> lk(F.mu);
     F.cv.wait(lk, [&] { return !F.flushing; });
     F.members.erase(std::find(F.members.begin(), F.members.end(), &s));
+    F.cells -= s.m.n;
     s.fu = nullptr;
     // the others may all be waiting for this member
     if (!F.members.empty() && F.waiting == (int)F.members.size()) issue_all(F, lk);
@@ -322,6 +324,8 @@ void fusion_host(Sim& s, std::function<void(hipStream_t)> fn) {
     op.host = std::move(fn);
     s.ops.push_back(std::move(op));
 }
+
+int64_t fusion_cells(const Sim& s) { return s.fu ? s.fu->cells.load(std::memory_order_relaxed) : s.m.n; }
 
 void fusion_sync(Sim& s) {
     Fusion& F = *s.fu;
@@ -445,6 +449,7 @@ pf_status pf_fusion_join(pf_fusion* h, pf_sim* sim) {
     std::unique_lock<std::mutex> lk(F.mu);
     F.cv.wait(lk, [&] { return !F.flushing; });
     F.members.push_back(&s);
+    F.cells += s.m.n;
     s.fu = &F;
     return PF_OK;
 }

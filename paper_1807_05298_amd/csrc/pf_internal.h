@@ -430,6 +430,7 @@ struct HipError { std::string msg; };
 // ---- fusion group hooks (pf_fuse.hip) -----------------------------------------
 void fusion_record(Sim& s, MultiFn f, uint32_t nb, uint32_t threads, size_t shm, const void* entry, size_t len);
 void fusion_host(Sim& s, std::function<void(hipStream_t)> op);
+int64_t fusion_cells(const Sim& s);  // cells of the group's members together (its own without a group)
 void fusion_sync(Sim& s);            // every member at a synchronisation point: the group's work is issued
 
 // Launch of kernel k (functor F) on stream st, or its record in s's fusion group.
@@ -503,8 +504,15 @@ __device__ __forceinline__ int64_t lc_at(int64_t ns, int64_t colour, int64_t s) 
 // them to the next, so that it would only push out the vectors.  Measured, the
 // four kernels of an iteration in us, streamed / not: 394k cells (copy of 132
 // MB) 71.4 / 63.1, 648k (218 MB) 100.8 / 105.4, 2M 314 / 337, 5.2M 894 / 942,
-// 13.5M 2407 / 2401, 27M 4847 / 4810.
-inline bool stream_past_caches(int64_t bytes) { return bytes > ((int64_t)160 << 20); }
+// 13.5M 2407 / 2401, 27M 4847 / 4810.  The members of a fusion group take
+// turns at the cache, kernel by kernel, so their copies count together (a
+// timestep of a group in ms, streamed / not: 8 members of 50k cells, 136 MB in
+// all, 8.61 / 8.58; 8 of 101k, 271 MB, 8.62 / 9.04; 4 of 202k, 271 MB, 11.34 /
+// 11.91; 4 of 397k, 533 MB, 14.86 / 15.21; 16 of 397k 48.2 / 48.6).  The
+// values loaded and their order are the same either way.
+inline bool stream_past_caches(const Sim& s, int64_t bytes) {
+    return (double)bytes * (double)fusion_cells(s) > (double)s.m.n * (double)((int64_t)160 << 20);
+}
 
 // XCD-aware block order: workgroups are dispatched round-robin over the 8
 // XCDs (each with its own L2); renumbering them so that XCD x processes one

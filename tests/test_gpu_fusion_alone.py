@@ -20,3 +20,14 @@ def test_fused_state_is_the_direct_one(opts):
         for c, m in zip(group, _fused(_pf(), group, o, 1)[0]):
             for name, a, b in zip("P S C Pb".split(), m, _direct(_pf(), c, o, 1)):
                 assert np.array_equal(a, b), (c.name, len(group), name)
+
+
+@pytest.mark.parametrize("opts", [{}, {"precision": 1}, {"smoother": 0}])
+def test_members_that_share_the_cache(opts):
+    """Six members of 101k cells: together their copies of J are too large for the memory-side cache, one's is not."""
+    pf = _pf()
+    o = pf.default_opts(**opts)
+    c = I.box_case(58, 58, 30, seed=61, dts=[0.5 * I.DAY])
+    ref = _direct(pf, c, o, 1)
+    for m in _fused(pf, [c] * 6, o, 1)[0]:
+        assert all(np.array_equal(a, b) for a, b in zip(m, ref))
