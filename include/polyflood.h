@@ -394,7 +394,7 @@ pf_status pf_profile_end(pf_sim* sim, int32_t* launches, double* total_ms);
 /* ---- Fused launches across simulators ------------------------------------
  * A fusion group merges the device work of its member simulators into
  * shared launches, for many small realisations whose own launches are too
- * short to fill the GPU (one FGMRES iteration issues about 80).  A member
+ * short to fill the GPU (one FGMRES iteration issues 10 to 60).  A member
  * records its kernel launches and copies instead of issuing them.  Each
  * member is driven by its own host thread: a call that synchronises (every
  * call that returns host data, and the convergence tests inside pf_step)
@@ -403,8 +403,11 @@ pf_status pf_profile_end(pf_sim* sim, int32_t* launches, double* total_ms);
  * launch per kernel over a table of (member, block range) entries for the
  * operations of the same kernel and block size at the heads of the
  * members' queues, the rest one by one, each member's operations in its
- * own order.  A member computes exactly what it computes alone: the same
- * kernels with the same arguments, block counts and reductions.
+ * own order.  A member computes exactly what it computes alone, bit for bit:
+ * the same operations and reductions in the same order (which of them share a
+ * launch, and the caching of loads, follow the size of the group).  A thread
+ * that waits looks for the end of its work for up to 2 ms before it sleeps, in
+ * a group and alone.
  * pf_fusion_create: hip_stream is the group's stream, on the current device
  * (PF_EINVAL for a stream of another device).
  * pf_fusion_join: add a simulator created on the group's device (its own

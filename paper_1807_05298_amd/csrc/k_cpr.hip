@@ -658,10 +658,12 @@ struct F_k_resid_restrict {
 // first colour-0 half-sweep (from x = 0, so from its right-hand side alone).
 // A workgroup takes a tile of TX x TY fine columns: it solves the tile's
 // colour-1 lines and those of a ring around it (which its neighbours solve as
-// well: 48 lines for the 32 of 8 x 8, 18 for 8 of 8 x 2), keeps them in LDS, forms the tile's coarse cells from its colour-0 rows and solves
-// the coarse colour-0 lines in the tile.  The colour-0 values and both
-// right-hand sides it reads are not written by the launch, so workgroups do
-// not depend on one another; the arithmetic is that of the three launches.
+// well: 48 lines for the 32 of 8 x 8, 18 for 8 of 8 x 2), keeps them in LDS,
+// forms the tile's coarse cells from its colour-0 rows and solves the coarse
+// colour-0 lines in the tile.  The colour-0 values and both right-hand sides
+// it reads are not written by the launch, so workgroups do not depend on one
+// another.  The arithmetic is that of the three launches, in their order, so
+// that the values do not depend on which of the two ways a level takes.
 //
 // The three launches it replaces are bound by latency on small levels (3.5-4
 // us each): here it is one memory round trip, as the coefficients of all
@@ -742,7 +744,8 @@ __device__ __forceinline__ void k_mg_down_d(const Blk& wg, const MgDown<T>& a) {
     const int IZ = t / (CX * CY);
     const int IX = bx * CX + cx, IY = by * CY + cy;
     const bool cell = IX < c.nx && IY < c.ny && IZ < c.nz;
-    T w[4][4], r0[4];                                 // lateral coefficients; b - A x of the line itself
+    // lateral coefficients; what the line itself takes off the right-hand side (rz: its neighbours in z)
+    T w[4][4], r0[4], rz[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int p = q & 1, jx = 2 * IX + p, jy = 2 * IY + p, jz = IZ * a.cz + (q >> 1);
@@ -754,11 +757,11 @@ __device__ __forceinline__ void k_mg_down_d(const Blk& wg, const MgDown<T>& a) {
             const T ak = a.A[(k + 1) * n + i];
             w[q][k] = ex[k] ? ak : (T)0;
         }
-        r0[q] = 0;
+        r0[q] = rz[q] = 0;
         if constexpr (!LAT) {
             const bool zm = v && jz > 0, zp = v && jz + 1 < f.nz;
-            const T z = (zm ? a.A[5 * n + i] * a.x[i - lstr] : (T)0) + (zp ? a.A[6 * n + i] * a.x[i + lstr] : (T)0);
-            r0[q] = v ? a.b[i] - a.A[i] * a.x[i] - z : (T)0;
+            rz[q] = (zm ? a.A[5 * n + i] * a.x[i - lstr] : (T)0) + (zp ? a.A[6 * n + i] * a.x[i + lstr] : (T)0);
+            r0[q] = v ? a.b[i] - a.A[i] * a.x[i] : (T)0;
         }
     }
 
@@ -808,7 +811,7 @@ __device__ __forceinline__ void k_mg_down_d(const Blk& wg, const MgDown<T>& a) {
             const T x3 = xl[(my - 1) * kRow + (mx >> 1)], x4 = xl[(my + 1) * kRow + (mx >> 1)];
             const T lat = (w[q][0] != (T)0 ? w[q][0] * x1 : (T)0) + (w[q][1] != (T)0 ? w[q][1] * x2 : (T)0) +
                           (w[q][2] != (T)0 ? w[q][2] * x3 : (T)0) + (w[q][3] != (T)0 ? w[q][3] * x4 : (T)0);
-            s += r0[q] - lat;
+            s += r0[q] - lat - rz[q];                 // in the order of cell_residual
         }
         a.bc[lv_index(c, IX, IY, IZ)] = s;
         bs[IZ * (CX * CY) + cy * CX + cx] = s;
@@ -2490,19 +2493,26 @@ void zline_full_sweeps(Sim& s, const MGLevel& L, int zero_init, int sweeps) {
 
 // The tile with which k_mg_down takes the way down from level l, or none for
 // launches of their own.  It needs 2 x 2 columns an aggregate and lines that
-// fit a workgroup in segments of kDownLen layers, where the caller has not set
-// their length (zline_len).  The costs are modelled (us):
-// a launch on a small level takes 3.5, the three of them a traffic that the
-// whole GPU draws at 3.7 TB/s; this one 4.2, and what a tile makes its compute
-// unit fetch, in pieces of 64 bytes of its short rows, at 20 KB a us, times the
-// tiles that a compute unit gets.  So low levels gain, and tall ones, whose
-// lines a compute unit has to hold from end to end, do not: on 101x77x33 the
-// best tile (4 x 4) took 21.9 us where the three launches take 15, on
-// 33x26x47 2 x 2 took 8.6 for 11 from x = 0 and 13.5 for 13.9 after another
-// cycle, for the same timestep.
+// fit a workgroup in segments of kDownLen layers, where the launches of their
+// own have those too and the caller has not set their length (zline_len).
+// The costs are modelled (us): a launch on a small level takes 3.5, the three
+// of them a traffic that the whole GPU draws at 3.7 TB/s; this one 4.2, and
+// what a tile makes its compute unit fetch, in pieces of 64 bytes of its short
+// rows, at 20 KB a us, times the tiles that a compute unit gets.  So low
+// levels gain, and tall ones, whose lines a compute unit has to hold from end
+// to end, do not: on 101x77x33 the best tile (4 x 4) took 21.9 us where the
+// three launches take 15, on 33x26x47 2 x 2 took 8.6 for 11 from x = 0 and
+// 13.5 for 13.9 after another cycle, for the same timestep.  A fusion group's
+// launch holds the tiles of all its members, taken to be of one size (counted
+// one by one instead: a timestep of 8 members of 58x58x30 cells 10.5 ms for
+// 9.0, of 16 17.7 for 14.7; groups of one or two are the same either way).
 struct DownTile {
     int x, y;
 };
+// whether a half-sweep's own launch has k_mg_down's segments (they set its rounding)
+bool down_segments(const Sim& s, const MGLevel& L) {
+    return zline_shape(s, L).nseg == (L.nz + kDownLen - 1) / kDownLen;
+}
 constexpr DownTile kDownTiles[] = {{8, 8}, {8, 2}, {4, 2}};
 template <class T>
 DownTile mg_down_tile(const Sim& s, int l, bool lat, bool next) {
@@ -2510,15 +2520,16 @@ DownTile mg_down_tile(const Sim& s, int l, bool lat, bool next) {
     if (l + 1 >= (int)s.mg.size()) return best;
     const MGLevel& L = s.mg[l];
     const int nseg = (L.nz + kDownLen - 1) / kDownLen;
-    if (L.cx != 2 || L.cy != 2 || nseg > 64 || s.opts.zline_len > 0) return best;
+    if (L.cx != 2 || L.cy != 2 || !down_segments(s, L) || s.opts.zline_len > 0) return best;
     // values a cell: right-hand side, lateral coefficients, factors, neighbours; rows of colour 0
     const double v1 = 10, v0 = lat ? 4 : 10, sz = sizeof(T);
-    double cost = (next ? 10.5 : 7.0) + 0.5 * (v1 + v0) * sz * (double)L.n / 3.7e6;
+    const double members = (double)fusion_cells(s) / (double)s.m.n;
+    double cost = (next ? 10.5 : 7.0) + members * 0.5 * (v1 + v0) * sz * (double)L.n / 3.7e6;
     for (const DownTile& t : kDownTiles) {
         const int row = (t.x + 2) / 2, lines = row * (t.y + 2);
         if (lines * nseg > 1024) continue;
         const double fetched = (t.y + 2) * v1 * (row * sz + 64 - sz) + t.y * v0 * (t.x / 2 * sz + 64 - sz);
-        const double tiles = (double)((L.nx + t.x - 1) / t.x) * ((L.ny + t.y - 1) / t.y);
+        const double tiles = members * ((L.nx + t.x - 1) / t.x) * ((L.ny + t.y - 1) / t.y);
         const double c = 4.2 + fetched * L.nz / 20e3 * std::max(1.0, tiles / 256);
         if (c < cost) {
             cost = c;
@@ -2878,7 +2889,7 @@ DownRoute down_route(const Sim& s, int l, int nt, bool lat, bool first_done) {
     // whether the next level's first half-sweep can follow its restriction
     // at once (a level of one workgroup with more sweeps to do does them all)
     const int pc = l + 1 < std::min(nt, (int)s.mg.size() - 1) ? pre_sweeps(s, C) : 0;
-    const bool next = pc == 1 || (pc > 1 && !zline_full_fits(s, C));
+    const bool next = (pc == 1 || (pc > 1 && !zline_full_fits(s, C))) && down_segments(s, C);
     const DownTile tile = mg_down_tile<T>(s, l, lat, next);
     // a level that fits one workgroup takes all its pre-sweeps in one launch
     // (a single one is half done by the launch before and the one after)

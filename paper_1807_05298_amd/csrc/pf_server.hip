@@ -15,8 +15,8 @@
 // fusion groups (pf_fuse.hip), each on a stream of its own: the active
 // realisations of a group are its members for their steps, their launches
 // merged into shared launches, and the groups' streams overlap on the
-// device.  Every realisation runs the same kernels with the same arguments
-// as when alone, so its results do not depend on the mix.
+// device.  Every realisation's arithmetic is what it is alone, so its results
+// do not depend on the mix.
 #include "pf_internal.h"
 
 #include <algorithm>
