@@ -1117,9 +1117,9 @@ void launch_equilibrium(Sim& s, double datum_depth, double datum_p, double fwl_d
     std::vector<int32_t> ctrl(s.h_ctrl0), ktop(nw);
     for (int w = 0; w < nw; ++w) ktop[w] = s.h_wktop[w];
     if (nw > 0) {
-        PF_HIP(hipMemcpyAsync(wc, ctrl.data(), nw * 4, hipMemcpyHostToDevice, s.stream));
-        PF_HIP(hipMemcpyAsync(wk, ktop.data(), nw * 4, hipMemcpyHostToDevice, s.stream));
-        PF_HIP(hipMemcpyAsync(wt, s.h_target0.data(), nw * 8, hipMemcpyHostToDevice, s.stream));
+        copy_h2d(s, wc, ctrl.data(), nw * 4);
+        copy_h2d(s, wk, ktop.data(), nw * 4);
+        copy_h2d(s, wt, s.h_target0.data(), nw * 8);
     }
     launch<F_k_equilibrium_layers>(s, s.stream, k_equilibrium_layers, dim3(grid_for(s.m.nz, 64)), dim3(64), 0, s.m,
                                    datum_depth, datum_p, fwl_depth, lp, ls);
@@ -1127,7 +1127,7 @@ void launch_equilibrium(Sim& s, double datum_depth, double datum_p, double fwl_d
     launch<F_k_equilibrium_fill>(s, s.stream, k_equilibrium_fill, dim3(grid_for(s.m.n + s.m.nw)), dim3(kBlock), 0,
                                  s.m, lp, ls, wc, wt, wk, s.x);
     PF_LAUNCH_CHECK();
-    PF_HIP(hipStreamSynchronize(s.stream));     // the host vectors above outlive their copies
+    stream_sync(s);                             // the host vectors above outlive their copies
 }
 
 void launch_assemble(Sim& s, double dt, bool with_jacobian) {

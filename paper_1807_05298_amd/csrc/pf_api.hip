@@ -900,7 +900,7 @@ pf_status pf_set_equilibrium_state(pf_sim* h, double datum_depth, double datum_p
     {
         // the capillary-pressure table must decrease strictly to be inverted
         std::vector<double> tab(kTabSlots * PF_TABLE_MAX);
-        PF_HIP(hipMemcpyAsync(tab.data(), s.tab, tab.size() * 8, hipMemcpyDeviceToHost, s.stream));
+        copy_d2h(s, tab.data(), s.tab, tab.size() * 8);
         sync(s);
         for (int k = 1; k < s.m.n_pc; ++k)
             if (!(tab[kTabPcV * PF_TABLE_MAX + k] < tab[kTabPcV * PF_TABLE_MAX + k - 1]))
@@ -920,10 +920,10 @@ pf_status pf_get_state(pf_sim* h, double* P, double* S, double* C, double* Pb) {
     if (!h) throw InvalidArg{"null argument"};
     Sim& s = h->s;
     const int64_t n = s.m.n;
-    if (P) PF_HIP(hipMemcpyAsync(P, s.x, n * 8, hipMemcpyDeviceToHost, s.stream));
-    if (S) PF_HIP(hipMemcpyAsync(S, s.x + n, n * 8, hipMemcpyDeviceToHost, s.stream));
-    if (C) PF_HIP(hipMemcpyAsync(C, s.x + 2 * n, n * 8, hipMemcpyDeviceToHost, s.stream));
-    if (Pb && s.m.nw > 0) PF_HIP(hipMemcpyAsync(Pb, s.x + 3 * n, s.m.nw * 8, hipMemcpyDeviceToHost, s.stream));
+    if (P) copy_d2h(s, P, s.x, n * 8);
+    if (S) copy_d2h(s, S, s.x + n, n * 8);
+    if (C) copy_d2h(s, C, s.x + 2 * n, n * 8);
+    if (Pb && s.m.nw > 0) copy_d2h(s, Pb, s.x + 3 * n, s.m.nw * 8);
     sync(s);
     return PF_OK;
     PF_API_END
@@ -1041,16 +1041,16 @@ pf_status pf_assemble(pf_sim* h, double dt, double* R, double* J, double* border
     Sim& s = h->s;
     launch_assemble(s, dt, true);
     const int64_t n = s.m.n, np = s.m.np;
-    PF_HIP(hipMemcpyAsync(R, s.R, s.nv * 8, hipMemcpyDeviceToHost, s.stream));
+    copy_d2h(s, R, s.R, s.nv * 8);
     if (J) {
         ensure_j_natural(s);
-        PF_HIP(hipMemcpyAsync(J, s.J, 63 * n * 8, hipMemcpyDeviceToHost, s.stream));
+        copy_d2h(s, J, s.J, 63 * n * 8);
     }
     if (border && np > 0) {
         std::vector<double> Bh(3 * np), Ch(3 * np), Dh(std::max(s.m.nw, 1));
-        PF_HIP(hipMemcpyAsync(Bh.data(), s.B, 3 * np * 8, hipMemcpyDeviceToHost, s.stream));
-        PF_HIP(hipMemcpyAsync(Ch.data(), s.Cw, 3 * np * 8, hipMemcpyDeviceToHost, s.stream));
-        PF_HIP(hipMemcpyAsync(Dh.data(), s.Dw, s.m.nw * 8, hipMemcpyDeviceToHost, s.stream));
+        copy_d2h(s, Bh.data(), s.B, 3 * np * 8);
+        copy_d2h(s, Ch.data(), s.Cw, 3 * np * 8);
+        copy_d2h(s, Dh.data(), s.Dw, s.m.nw * 8);
         sync(s);
         for (int64_t k = 0; k < np; ++k) {
             for (int e = 0; e < 3; ++e) border[7 * k + e] = Bh[3 * k + e];
@@ -1069,7 +1069,7 @@ pf_status pf_spmv(pf_sim* h, const double* x, double* y) {
     Sim& s = h->s;
     upload(s, s.t1, x, s.nv * 8);
     launch_spmv(s, s.t1, s.t2);
-    PF_HIP(hipMemcpyAsync(y, s.t2, s.nv * 8, hipMemcpyDeviceToHost, s.stream));
+    copy_d2h(s, y, s.t2, s.nv * 8);
     sync(s);
     return PF_OK;
     PF_API_END
@@ -1083,7 +1083,7 @@ pf_status pf_linear_solve(pf_sim* h, const double* b, double rtol, double* dx, i
     cpr_setup(s);
     double r = 0.0;
     const int its = fgmres(s, s.rhs, rtol, s.dx, &r, s.opts.max_lin_it);
-    PF_HIP(hipMemcpyAsync(dx, s.dx, s.nv * 8, hipMemcpyDeviceToHost, s.stream));
+    copy_d2h(s, dx, s.dx, s.nv * 8);
     sync(s);
     if (iters) *iters = its;
     if (rel) *rel = r;
@@ -1097,12 +1097,12 @@ pf_status pf_get_static(pf_sim* h, double* row_scale, double* Tx, double* Ty, do
     if (!h) throw InvalidArg{"null argument"};
     Sim& s = h->s;
     const int64_t n = s.m.n, np = s.m.np;
-    if (row_scale) PF_HIP(hipMemcpyAsync(row_scale, s.rscale, s.nv * 8, hipMemcpyDeviceToHost, s.stream));
-    if (Tx) PF_HIP(hipMemcpyAsync(Tx, s.Tx, n * 8, hipMemcpyDeviceToHost, s.stream));
-    if (Ty) PF_HIP(hipMemcpyAsync(Ty, s.Ty, n * 8, hipMemcpyDeviceToHost, s.stream));
-    if (Tz) PF_HIP(hipMemcpyAsync(Tz, s.Tz, n * 8, hipMemcpyDeviceToHost, s.stream));
-    if (PVr) PF_HIP(hipMemcpyAsync(PVr, s.pvr, n * 8, hipMemcpyDeviceToHost, s.stream));
-    if (perf_wi && np > 0) PF_HIP(hipMemcpyAsync(perf_wi, s.perf_wi, np * 8, hipMemcpyDeviceToHost, s.stream));
+    if (row_scale) copy_d2h(s, row_scale, s.rscale, s.nv * 8);
+    if (Tx) copy_d2h(s, Tx, s.Tx, n * 8);
+    if (Ty) copy_d2h(s, Ty, s.Ty, n * 8);
+    if (Tz) copy_d2h(s, Tz, s.Tz, n * 8);
+    if (PVr) copy_d2h(s, PVr, s.pvr, n * 8);
+    if (perf_wi && np > 0) copy_d2h(s, perf_wi, s.perf_wi, np * 8);
     sync(s);
     if (perf_well) std::copy(s.h_perf_well.begin(), s.h_perf_well.end(), perf_well);
     if (perf_cell) std::copy(s.h_perf_cell.begin(), s.h_perf_cell.end(), perf_cell);
@@ -1122,9 +1122,8 @@ int32_t pf_pressure_level(pf_sim* h, int32_t level, int32_t* dims, double* A) {
     if (A) {
         try {
             std::vector<double> slots((size_t)(7 * L.ns));
-            if (hipMemcpyAsync(slots.data(), L.A, 7 * L.ns * 8, hipMemcpyDeviceToHost, s.stream) != hipSuccess ||
-                hipStreamSynchronize(s.stream) != hipSuccess)
-                return -1;
+            copy_d2h(s, slots.data(), L.A, 7 * L.ns * 8);
+            sync(s);
             for_level_cells(L, [&](int64_t i, int64_t j) {
                 for (int d = 0; d < 7; ++d) A[d * L.n + i] = slots[d * L.ns + j];
             });
@@ -1149,7 +1148,7 @@ pf_status pf_pressure_smooth(pf_sim* h, int32_t level, int32_t colour, int32_t z
     upload(s, L.b, bs.data(), L.ns * 8);
     upload(s, L.x, xs.data(), L.ns * 8);
     mg_smooth_once(s, level, colour, zero_init);
-    PF_HIP(hipMemcpyAsync(xs.data(), L.x, L.ns * 8, hipMemcpyDeviceToHost, s.stream));
+    copy_d2h(s, xs.data(), L.x, L.ns * 8);
     sync(s);
     for_level_cells(L, [&](int64_t i, int64_t j) { x[i] = xs[j]; });
     return PF_OK;
@@ -1175,11 +1174,11 @@ pf_status pf_smoother_apply(pf_sim* h, const double* f, double* z) {
     smoother_once(s, s.t2);
     if (s.opts.precision == PF_PREC_MIXED) {
         std::vector<float> z32((size_t)s.nv);
-        PF_HIP(hipMemcpyAsync(z32.data(), s.Z32, s.nv * 4, hipMemcpyDeviceToHost, s.stream));
+        copy_d2h(s, z32.data(), s.Z32, s.nv * 4);
         sync(s);
         for (int64_t i = 0; i < s.nv; ++i) z[i] = z32[i];
     } else {
-        PF_HIP(hipMemcpyAsync(z, s.t1, s.nv * 8, hipMemcpyDeviceToHost, s.stream));
+        copy_d2h(s, z, s.t1, s.nv * 8);
         sync(s);
     }
     return PF_OK;
@@ -1199,10 +1198,10 @@ pf_status pf_precond_apply(pf_sim* h, const double* v, double* z, double* w) {
         cpr_apply(s, vd, s.Z32);
         launch_spmv(s, s.Z32, wd);
         std::vector<float> z32((size_t)s.nv);
-        PF_HIP(hipMemcpyAsync(z32.data(), s.Z32, s.nv * 4, hipMemcpyDeviceToHost, s.stream));
+        copy_d2h(s, z32.data(), s.Z32, s.nv * 4);
         sync(s);
         for (int64_t i = 0; i < s.nv; ++i) z[i] = z32[i];
-        if (w) PF_HIP(hipMemcpyAsync(w, wd, s.nv * 8, hipMemcpyDeviceToHost, s.stream));
+        if (w) copy_d2h(s, w, wd, s.nv * 8);
     } else if (cpr_colour_split(s)) {
         // the solver's layout: v in, z and w out through the colour-split one
         upload(s, s.t1, v, s.nv * 8);
@@ -1213,13 +1212,13 @@ pf_status pf_precond_apply(pf_sim* h, const double* v, double* z, double* w) {
         launch_copy(s, red, vd, wd);         // the red rows of the product are those of v
         launch_from_cs(s, s.Z, s.t1);
         launch_from_cs(s, wd, s.t2);
-        PF_HIP(hipMemcpyAsync(z, s.t1, s.nv * 8, hipMemcpyDeviceToHost, s.stream));
-        if (w) PF_HIP(hipMemcpyAsync(w, s.t2, s.nv * 8, hipMemcpyDeviceToHost, s.stream));
+        copy_d2h(s, z, s.t1, s.nv * 8);
+        if (w) copy_d2h(s, w, s.t2, s.nv * 8);
     } else {
         upload(s, vd, v, s.nv * 8);
         cpr_apply_spmv(s, vd, s.Z, wd);
-        PF_HIP(hipMemcpyAsync(z, s.Z, s.nv * 8, hipMemcpyDeviceToHost, s.stream));
-        if (w) PF_HIP(hipMemcpyAsync(w, wd, s.nv * 8, hipMemcpyDeviceToHost, s.stream));
+        copy_d2h(s, z, s.Z, s.nv * 8);
+        if (w) copy_d2h(s, w, wd, s.nv * 8);
     }
     sync(s);
     return PF_OK;
@@ -1239,11 +1238,11 @@ pf_status pf_pressure_vcycle(pf_sim* h, const double* b, double* x) {
     mg_cycles_once(s, s.t2);
     if (s.opts.precision == PF_PREC_MIXED) {
         std::vector<float> p32((size_t)n);
-        PF_HIP(hipMemcpyAsync(p32.data(), s.pnat32, n * 4, hipMemcpyDeviceToHost, s.stream));
+        copy_d2h(s, p32.data(), s.pnat32, n * 4);
         sync(s);
         for (int64_t i = 0; i < n; ++i) x[i] = p32[i];
     } else {
-        PF_HIP(hipMemcpyAsync(x, s.pnat, n * 8, hipMemcpyDeviceToHost, s.stream));
+        copy_d2h(s, x, s.pnat, n * 8);
         sync(s);
     }
     return PF_OK;
