@@ -372,6 +372,12 @@ pf_status pf_smoother_apply(pf_sim* sim, const double* f, double* z);
  * precision).  Uses the first two Krylov vectors as device storage. */
 pf_status pf_precond_apply(pf_sim* sim, const double* v, double* z, double* w);
 
+/* Test hook: whether the kernels that stream J load it past the caches, by
+ * its size (in a fusion group all members' together): streams[0] those on the
+ * colour-split copies (FP64 PF order with ILU(0)), streams[1] the product by
+ * the natural-order planes.  The values do not depend on it. */
+pf_status pf_streams_j(pf_sim* sim, int32_t streams[2]);
+
 /* Static data: row scales D (3N + n_wells), transmissibilities to the
  * +x/+y/+z neighbours (N each, 0 at the boundary), reference pore volumes
  * (N), and per perforation (sorted by cell) its well, cell and Peaceman

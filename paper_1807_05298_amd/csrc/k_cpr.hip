@@ -1920,7 +1920,7 @@ struct F_k_j_natural {
 // application): non-temporal, so they do not evict the vectors and the
 // P-columns of J that the stage residual has just brought into the caches.
 // (NT false: a model small enough for its blocks to stay in the memory-side
-// cache, stream_past_caches.)
+// cache, stream_split.)
 template <bool NT = true> __device__ __forceinline__ double ilu_ld(const double* p) {
     if constexpr (NT) return __builtin_nontemporal_load(p);
     else return *p;
@@ -3217,11 +3217,14 @@ void colour_split_apply(Sim& s, const CsVec& v, double* z, double* w) {
 }
 }  // namespace
 
+bool stream_split(const Sim& s) {
+    return past_caches(s, 2 * lc_colour(ilu_slot_count(s.m)) * (int64_t)sizeof(double), 145e6);
+}
+
 // The same in the colour-split layout (PF order, red-black ILU(0)); of w the
 // black rows and the wells: the red rows are those of v.
 void cpr_apply_spmv(Sim& s, const CsVec& v, double* z, double* w) {
-    if (stream_past_caches(s, 2 * lc_colour(ilu_slot_count(s.m)) * (int64_t)sizeof(double)))
-        colour_split_apply<true>(s, v, z, w);
+    if (stream_split(s)) colour_split_apply<true>(s, v, z, w);
     else colour_split_apply<false>(s, v, z, w);
 }
 

@@ -11,7 +11,7 @@ namespace pf {
 namespace {
 
 // J is streamed once per product: non-temporal loads keep the caches for x
-// where J does not fit them (stream_past_caches; 300k cells without them and
+// where J does not fit them (stream_natural; 300k cells without them and
 // with all blocks' loads in flight 23.7 us for 29.5).
 template <bool NT> __device__ __forceinline__ double jld(const double* p) {
     if constexpr (NT) return __builtin_nontemporal_load(p);
@@ -732,7 +732,7 @@ void spmv_t(Sim& s, const TX* x, const double* v, double* y) {
 #define PF_SPMV(NT)                                                                                             \
     launch<F_k_spmv<TX, NT>>(s, s.stream, (k_spmv<TX, NT>), grid, block, 0, m, ncb, s.J, s.pc_map, s.pc_first,  \
                              s.perf_well, s.perf_cell, s.wp_first, s.wp_idx, s.B, s.Cw, s.Dw, x, v, y)
-    if (stream_past_caches(s, 56 * m.n * (int64_t)sizeof(double))) PF_SPMV(true);
+    if (stream_natural(s)) PF_SPMV(true);
     else PF_SPMV(false);
 #undef PF_SPMV
     PF_LAUNCH_CHECK();

@@ -1165,6 +1165,15 @@ pf_status pf_pressure_route(pf_sim* h, int32_t level, int32_t cycle, int32_t rou
     PF_API_END
 }
 
+pf_status pf_streams_j(pf_sim* h, int32_t streams[2]) {
+    PF_API_BEGIN
+    if (!h || !streams) throw InvalidArg{"null argument"};
+    streams[0] = stream_split(h->s);
+    streams[1] = stream_natural(h->s);
+    return PF_OK;
+    PF_API_END
+}
+
 pf_status pf_smoother_apply(pf_sim* h, const double* f, double* z) {
     PF_API_BEGIN
     if (!h || !f || !z) throw InvalidArg{"null argument"};

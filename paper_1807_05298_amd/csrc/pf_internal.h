@@ -499,20 +499,29 @@ __device__ __forceinline__ int64_t lc_at(int64_t ns, int64_t colour, int64_t s) 
     return colour * lc_colour(ns) + (s >> 6) * (64 * 6 * kFaceVals) + (s & 63);
 }
 
-// Whether kernels stream J past the caches (non-temporal loads): where a copy
-// of bytes bytes does not stay in the 256 MB memory-side cache from one of
-// them to the next, so that it would only push out the vectors.  Measured, the
-// four kernels of an iteration in us, streamed / not: 394k cells (copy of 132
-// MB) 71.4 / 63.1, 648k (218 MB) 100.8 / 105.4, 2M 314 / 337, 5.2M 894 / 942,
-// 13.5M 2407 / 2401, 27M 4847 / 4810.  The members of a fusion group take
-// turns at the cache, kernel by kernel, so their copies count together (a
-// timestep of a group in ms, streamed / not: 8 members of 50k cells, 136 MB in
-// all, 8.61 / 8.58; 8 of 101k, 271 MB, 8.62 / 9.04; 4 of 202k, 271 MB, 11.34 /
-// 11.91; 4 of 397k, 533 MB, 14.86 / 15.21; 16 of 397k 48.2 / 48.6).  The
-// values loaded and their order are the same either way.
-inline bool stream_past_caches(const Sim& s, int64_t bytes) {
-    return (double)bytes * (double)fusion_cells(s) > (double)s.m.n * (double)((int64_t)160 << 20);
+// Whether the kernels stream J past the caches (non-temporal loads): where it
+// does not stay in the 256 MB memory-side cache from one of them to the next
+// beside what the other kernels read, which it would only push out.  The lines
+// are those of whole timesteps (ms with streamed / plain loads, by the size of
+// J): colour-split copies, FP64, 85 MB 3.93 / 3.83, 111 MB 5.81 / 5.68, 133 MB
+// 5.51 / 5.46, 145 MB 4.88 / 4.89, 158 MB 7.05 / 7.13, 168 MB 7.28 / 7.40, 221
+// MB 8.31 / 8.62, 327 MB 9.63 / 10.09; natural-order planes, block Jacobi in
+// Algorithm 2's order, 114 MB 5.19 / 5.01, 148 MB 6.31 / 6.11, 163 MB 6.15 /
+// 6.15, 178 MB 7.35 / 7.27, 194 MB 6.55 / 6.60, 224 MB 8.06 / 8.31, 435 MB
+// 12.82 / 13.27, and mixed precision 163 MB 5.23 / 5.14, 178 MB 6.06 / 6.00,
+// 194 MB 5.30 / 5.32, 224 MB 8.01 / 8.11.  (By themselves the kernels gain from
+// plain loads up to 200 and 250 MB: 168 MB, four of them, 91.2 / 83.9 us.  From
+// 13.5M cells on, 4.5 GB, the two are the same to 1 %.)  The members of a
+// fusion group take turns at the cache, kernel by kernel, so theirs count
+// together (a timestep of a group: 8 members of 50k cells, 136 MB in all, 8.61
+// / 8.58; 8 of 101k, 271 MB, 8.62 / 9.04; 4 of 202k, 271 MB, 11.34 / 11.91; 4
+// of 397k, 533 MB, 14.86 / 15.21; 16 of 397k 48.2 / 48.6).  The values loaded
+// and their order are the same either way.
+inline bool past_caches(const Sim& s, int64_t bytes, double line) {
+    return (double)bytes * (double)fusion_cells(s) > line * (double)s.m.n;
 }
+bool stream_split(const Sim& s);     // the colour-split copies (k_cpr.hip)
+inline bool stream_natural(const Sim& s) { return past_caches(s, 56 * s.m.n * (int64_t)sizeof(double), 185e6); }
 
 // XCD-aware block order: workgroups are dispatched round-robin over the 8
 // XCDs (each with its own L2); renumbering them so that XCD x processes one

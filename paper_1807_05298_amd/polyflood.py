@@ -155,6 +155,7 @@ _lib.pf_pressure_level.argtypes = [_vp, _i, _vp, _vp]
 _lib.pf_pressure_smooth.argtypes = [_vp, _i, _i, _i, _vp, _vp]
 _lib.pf_pressure_vcycle.argtypes = [_vp, _vp, _vp]
 _lib.pf_pressure_route.argtypes = [_vp, _i, _i, _vp]
+_lib.pf_streams_j.argtypes = [_vp, _vp]
 _lib.pf_smoother_apply.argtypes = [_vp, _vp, _vp]
 _lib.pf_precond_apply.argtypes = [_vp, _vp, _vp, _vp]
 _lib.pf_profile_end.argtypes = [_vp, ctypes.POINTER(_i), ctypes.POINTER(_d)]
@@ -165,7 +166,7 @@ EXPORTED = ["pf_default_opts", "pf_workspace_size", "pf_create", "pf_destroy", "
             "pf_get_state", "pf_begin_step", "pf_newton_iteration", "pf_step", "pf_assemble", "pf_spmv",
             "pf_linear_solve", "pf_get_static", "pf_n_perf", "pf_last_error", "pf_profile_begin", "pf_profile_end",
             "pf_pressure_level", "pf_pressure_smooth", "pf_pressure_vcycle", "pf_pressure_route", "pf_smoother_apply",
-            "pf_precond_apply", "pf_server_create", "pf_server_submit", "pf_server_poll",
+            "pf_precond_apply", "pf_streams_j", "pf_server_create", "pf_server_submit", "pf_server_poll",
             "pf_server_wait", "pf_server_release", "pf_server_info", "pf_server_destroy", "pf_well_status", "pf_set_well_operation",
             "pf_fusion_create", "pf_fusion_join", "pf_fusion_leave", "pf_fusion_step", "pf_fusion_stats",
             "pf_fusion_destroy"]
@@ -421,6 +422,12 @@ class Simulator:
         for l in range(nl):
             _check(_lib.pf_pressure_route(self.h, l, cycle, out[l].ctypes.data))
         return [tuple(int(v) for v in r) for r in out]
+
+    def streams_j(self) -> tuple:
+        """Whether J's colour-split copies and its natural-order planes are loaded past the caches."""
+        out = np.zeros(2, np.int32)
+        _check(_lib.pf_streams_j(self.h, out.ctypes.data))
+        return bool(out[0]), bool(out[1])
 
     def static(self) -> dict:
         n, npf = self.n, max(self.n_perf, 1)
