@@ -3056,11 +3056,10 @@ const T* pressure_stage(Sim& s, const double* v) {
     return p;
 }
 
-// first_phase 1: the red phase 0 was done by k_stage_ilu0
-void smoother_apply(Sim& s, const double* f, double* z, int first_phase = 0) {
+void smoother_apply(Sim& s, const double* f, double* z) {
     const DevModel& m = s.m;
     if (s.opts.smoother == PF_SMOOTH_RBILU0) {
-        for (int ph = first_phase; ph < 3; ++ph) {
+        for (int ph = 0; ph < 3; ++ph) {
             ProfScope ps(s, ph == 1 ? PF_K_ILU : 0);
             launch<F_k_ilu_apply_t<double, double, double>>(s, s.stream, (k_ilu_apply_t<double, double, double>),
                                                             dim3(grid_for(ilu_slot_count(m))), dim3(kBlock), 0, m,
@@ -3079,6 +3078,7 @@ void smoother_apply(Sim& s, const double* f, double* z, int first_phase = 0) {
     }
 }
 
+// first_phase 1: the red phase 0 was done by k_stage_ilu0
 void smoother_apply_m(Sim& s, const float* f, float* z, int first_phase = 0) {
     const DevModel& m = s.m;
     if (s.opts.smoother == PF_SMOOTH_RBILU0) {
@@ -3122,32 +3122,21 @@ void cpr_apply(Sim& s, const double* v, double* z) {
     const DevModel& m = s.m;
     ensure_j_natural(s);
     if (s.opts.cpr_order == PF_CPR_PF) {
+        // (block Jacobi: with red-black ILU(0) this order runs in the colour-split layout)
         const double* p = pressure_stage<double>(s, v);
-        if (s.opts.smoother == PF_SMOOTH_RBILU0) {
-            {
-                ProfScope ps(s, PF_K_STAGE_RESID);
-                launch<F_k_stage_ilu0<double, double, double>>(s, s.stream, (k_stage_ilu0<double, double, double>),
-                                                               dim3(grid_for(m.n + m.nw)), dim3(kBlock), 0, m, s.J, v,
-                                                               p, s.pb, s.B, s.pc_map, s.pc_first, s.perf_well,
-                                                               (const double*)s.Dinv, s.t2, z);
-                PF_LAUNCH_CHECK();
-            }
-            smoother_apply(s, s.t2, z, 1);
-        } else {
-            {
-                ProfScope ps(s, PF_K_STAGE_RESID);
-                launch<F_k_stage_resid<double, double>>(s, s.stream, (k_stage_resid<double, double>),
-                                                        dim3(grid_for(m.n)), dim3(kBlock), 0, m, s.J, v, p, s.t2);
-                PF_LAUNCH_CHECK();
-            }
-            if (m.nw > 0) {
-                launch<F_k_stage_resid_border<double>>(s, s.stream, k_stage_resid_border<double>,
-                                                       dim3(grid_for(m.npc + m.nw, 64)), dim3(64), 0, m, s.pc_cell,
-                                                       s.pc_first, s.perf_well, s.B, s.pb, s.t2);
-                PF_LAUNCH_CHECK();
-            }
-            smoother_apply(s, s.t2, z);
+        {
+            ProfScope ps(s, PF_K_STAGE_RESID);
+            launch<F_k_stage_resid<double, double>>(s, s.stream, (k_stage_resid<double, double>), dim3(grid_for(m.n)),
+                                                    dim3(kBlock), 0, m, s.J, v, p, s.t2);
+            PF_LAUNCH_CHECK();
         }
+        if (m.nw > 0) {
+            launch<F_k_stage_resid_border<double>>(s, s.stream, k_stage_resid_border<double>,
+                                                   dim3(grid_for(m.npc + m.nw, 64)), dim3(64), 0, m, s.pc_cell,
+                                                   s.pc_first, s.perf_well, s.B, s.pb, s.t2);
+            PF_LAUNCH_CHECK();
+        }
+        smoother_apply(s, s.t2, z);
         launch<F_k_add_pressure<double>>(s, s.stream, k_add_pressure<double>, dim3(grid_for(m.n + m.nw)),
                                          dim3(kBlock), 0, m.n, m.nw, p, s.pb, z);
         PF_LAUNCH_CHECK();

@@ -279,33 +279,6 @@ struct F_k_bjac_setup {
     }
 };
 
-// z = D^{-1} r per cell block; wells z = r / Dw
-__device__ __forceinline__ void k_bjac_apply_d(const Blk& wg, int64_t n, int nw, const double* __restrict__ Dinv,
-                                               const double* __restrict__ Dw, const double* __restrict__ r,
-                                               double* __restrict__ z) {
-    const int64_t i = (int64_t)wg.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        const double a = r[i], b = r[n + i], c = r[2 * n + i];
-        z[i] = Dinv[0 * n + i] * a + Dinv[1 * n + i] * b + Dinv[2 * n + i] * c;
-        z[n + i] = Dinv[3 * n + i] * a + Dinv[4 * n + i] * b + Dinv[5 * n + i] * c;
-        z[2 * n + i] = Dinv[6 * n + i] * a + Dinv[7 * n + i] * b + Dinv[8 * n + i] * c;
-    } else if (i < n + nw) {
-        const int w = (int)(i - n);
-        z[3 * n + w] = r[3 * n + w] / Dw[w];
-    }
-}
-__global__ void k_bjac_apply(int64_t n, int nw, const double* __restrict__ Dinv, const double* __restrict__ Dw,
-                             const double* __restrict__ r, double* __restrict__ z) {
-    k_bjac_apply_d(PF_BLK, n, nw, Dinv, Dw, r, z);
-}
-struct F_k_bjac_apply {
-    static constexpr int kLB = 1024;
-    template <class... A>
-    __device__ __forceinline__ void operator()(const Blk& wg, const A&... a) const {
-        k_bjac_apply_d(wg, a...);
-    }
-};
-
 // ---------------------------------------------------------------------------
 // Arnoldi.  Vectors V[k] (k = 0..j) are rows of V with leading dimension ld.
 // k_mdot: partial sums of <V[k], w> for k in the block's chunk of 16 and
@@ -777,12 +750,6 @@ void launch_fill(Sim& s, int64_t n, double v, double* y) {
 
 void launch_bjac_setup(Sim& s) {
     launch<F_k_bjac_setup>(s, s.stream, k_bjac_setup, dim3(grid_for(s.m.n)), dim3(kBlock), 0, s.m.n, s.J, s.Dinv);
-    PF_LAUNCH_CHECK();
-}
-
-void launch_bjac_apply(Sim& s, const double* r, double* z) {
-    launch<F_k_bjac_apply>(s, s.stream, k_bjac_apply, dim3(grid_for(s.m.n + s.m.nw)), dim3(kBlock), 0, s.m.n, s.m.nw,
-                           s.Dinv, s.Dw, r, z);
     PF_LAUNCH_CHECK();
 }
 

@@ -364,7 +364,6 @@ void launch_fill(Sim& s, int64_t n, double v, double* y);
 bool j_colour_split_mode(const Sim& s);
 void ensure_j_natural(Sim& s);
 void launch_bjac_setup(Sim& s);
-void launch_bjac_apply(Sim& s, const double* r, double* z);
 // Krylov helpers
 void launch_norm_to_ctl(Sim& s, const double* v, int which, const HostPost& post);   // which 0: beta0+beta, 1: beta
 void launch_scale_by_ctl(Sim& s, const double* v, double* out, int which);  // which 0: 1/beta, 1: inv_h
@@ -375,7 +374,6 @@ void launch_arnoldi_second(Sim& s, int j, double* w, const HostPost& post);
 void launch_normalise(Sim& s, int j, double* w);                   // V[j+1] = w / h(j+1, j)
 void launch_solve_small(Sim& s, int k);                             // y = H(0:k,0:k)^{-1} g
 void launch_zcomb(Sim& s, int k, double* dx, bool first = false);   // dx += Z y (first: dx = Z y)
-void launch_init_cycle(Sim& s, int first);
 
 // ---- CPR (k_cpr.hip) ---------------------------------------------------------
 void cpr_choose_levels(Sim& s);     // host: multigrid hierarchy shape
