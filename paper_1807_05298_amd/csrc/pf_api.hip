@@ -250,7 +250,7 @@ size_t plan(Sim& s, char* base) {
         s.Z32 = nullptr;
     }
     s.t1 = b.take<double>(kst); s.t2 = b.take<double>(kst);
-    s.pc_map_cs = fp64 ? b.take<int32_t>(2 * cs_ns(m)) : nullptr;
+    s.pc_map_cs = fp64 && s.opts.smoother == PF_SMOOTH_RBILU0 ? b.take<int32_t>(2 * cs_ns(m)) : nullptr;
     s.bcs = fp64 ? b.take<double>(s.nvc) : nullptr;
     s.xcs = fp64 ? b.take<double>(s.nvc) : nullptr;
     s.w = nullptr;
