@@ -31,7 +31,12 @@ struct Fusion {
     std::mutex mu;
     std::condition_variable cv;
     std::vector<Sim*> members;
-    std::atomic<int64_t> cells{0};   // of the members together
+    // cells of the members together, which their routes go by: those of the last
+    // issue's members, so that all decide alike until the next one (a batch in
+    // which some had counted a member that had just joined, and others not, would
+    // merge fewer launches); before the first issue, those that have joined
+    std::atomic<int64_t> cells{0};
+    bool issued = false;             // since the group last was empty
     int waiting = 0;                 // members at a synchronisation point
     bool flushing = false;
     std::atomic<uint64_t> gen{0};    // issued batches of recorded work
@@ -274,6 +279,10 @@ void issue_all(Fusion& F, std::unique_lock<std::mutex>& lk) {
         m->op_bytes.clear();
     }
     lk.lock();
+    int64_t cells = 0;
+    for (const Sim* m : mem) cells += m->m.n;
+    F.cells = cells;
+    F.issued = true;
     F.flushing = false;
     F.waiting = 0;
     F.err = err;
@@ -287,7 +296,11 @@ void drop(Sim& s) {
     std::unique_lock<std::mutex> lk(F.mu);
     F.cv.wait(lk, [&] { return !F.flushing; });
     F.members.erase(std::find(F.members.begin(), F.members.end(), &s));
-    F.cells -= s.m.n;
+    if (!F.issued) F.cells -= s.m.n;
+    if (F.members.empty()) {
+        F.cells = 0;
+        F.issued = false;
+    }
     s.fu = nullptr;
     // the others may all be waiting for this member
     if (!F.members.empty() && F.waiting == (int)F.members.size()) issue_all(F, lk);
@@ -325,7 +338,10 @@ void fusion_host(Sim& s, std::function<void(hipStream_t)> fn) {
     s.ops.push_back(std::move(op));
 }
 
-int64_t fusion_cells(const Sim& s) { return s.fu ? s.fu->cells.load(std::memory_order_relaxed) : s.m.n; }
+int64_t fusion_cells(const Sim& s) {
+    // (a member that has just joined a running group may be larger than the others together)
+    return s.fu ? std::max(s.m.n, s.fu->cells.load(std::memory_order_relaxed)) : s.m.n;
+}
 
 void fusion_sync(Sim& s) {
     Fusion& F = *s.fu;
@@ -450,7 +466,7 @@ pf_status pf_fusion_join(pf_fusion* h, pf_sim* sim) {
     std::unique_lock<std::mutex> lk(F.mu);
     F.cv.wait(lk, [&] { return !F.flushing; });
     F.members.push_back(&s);
-    F.cells += s.m.n;
+    if (!F.issued) F.cells += s.m.n;
     s.fu = &F;
     return PF_OK;
 }
