@@ -15,9 +15,10 @@
 // many free wave slots while the smoother's set-up fills the GPU.
 // Measured, one inverse on an otherwise busy GPU (the augmented matrix in LDS
 // with four barriers a step, and the other two launches, before): 54 cells
-// 29 us (143 + 9), 84 cells 61 us (347 + 9); eight of 84 cells side by side 56
-// us (327 + 10).  Above kCoarseReg cells a thread's tile would not fit its
-// registers, and k_gauss_jordan keeps the matrix in memory.
+// 28 us (143 + 9), 84 cells 61 to 73 us by what runs beside it (347 + 9);
+// eight of 84 cells side by side 56 us (327 + 10).  Above kCoarseReg cells a
+// thread's tile would not fit its registers, and k_gauss_jordan keeps the
+// matrix in memory.
 #include "pf_internal.h"
 
 namespace pf {

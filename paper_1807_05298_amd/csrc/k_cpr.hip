@@ -2499,10 +2499,13 @@ void zline_full_sweeps(Sim& s, const MGLevel& L, int zero_init, int sweeps) {
 // of them a traffic that the whole GPU draws at 3.7 TB/s; this one 4.2, and
 // what a tile makes its compute unit fetch, in pieces of 64 bytes of its short
 // rows, at 20 KB a us, times the tiles that a compute unit gets.  So low
-// levels gain, and tall ones, whose lines a compute unit has to hold from end
-// to end, do not: on 101x77x33 the best tile (4 x 4) took 21.9 us where the
-// three launches take 15, on 33x26x47 2 x 2 took 8.6 for 11 from x = 0 and
-// 13.5 for 13.9 after another cycle, for the same timestep.  A fusion group's
+// levels gain, levels of 15 to 39 layers and few columns a little or nothing (a
+// timestep of 60x60x64, by its 30x30x32 level, 4.89 -> 4.77 ms, of 101x37x36
+// 3.24 -> 3.16, of 101x77x33 4.30 both), and taller or wider ones, whose lines
+// a compute unit has to hold from end to end, do not: on 101x77x33 the best
+// tile (4 x 4) took 21.9 us where the three launches take 15, on 33x26x47 2 x 2
+// took 8.6 for 11 from x = 0 and 13.5 for 13.9 after another cycle, for the
+// same timestep.  A fusion group's
 // launch holds the tiles of all its members, taken to be of one size (counted
 // one by one instead: a timestep of 8 members of 58x58x30 cells 10.5 ms for
 // 9.0, of 16 17.7 for 14.7; groups of one or two are the same either way).
